@@ -200,6 +200,30 @@ __device__ static inline uint32_t wave_or_u32(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// p_l + p_(l xor s) for s = 32, 16, 8, 4, 2, 1 in turn: the fixed order of the
+// catalog's sums, every lane ending with the same value.  All in registers:
+// half and row swaps for 32 and 16, DPP below (xor 4 is the half-row mirror,
+// which is xor 7, then a quad reversal, xor 3).  The six ds_bpermute round
+// trips of __shfl_xor cost a dependent LDS latency each.
+template <int CTRL>
+__device__ static inline float dpp_all_f32(float v)
+{
+    return __uint_as_float(dpp_u32<CTRL, 0xf, 0xf, true>(__float_as_uint(v)));
+}
+__device__ static inline float wave_xor_sum(float p)
+{
+    typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+    u32x2_t w = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+    p = __uint_as_float(w.x) + __uint_as_float(w.y);
+    w = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+    p = __uint_as_float(w.x) + __uint_as_float(w.y);
+    p = p + dpp_all_f32<0x128>(p);                       // row_ror:8
+    p = p + dpp_all_f32<0x1b>(dpp_all_f32<0x141>(p));    // xor 4
+    p = p + dpp_all_f32<0x4e>(p);                        // quad_perm [2,3,0,1]
+    p = p + dpp_all_f32<0xb1>(p);                        // quad_perm [1,0,3,2]
+    return p;
+}
+
 __device__ static inline uint32_t uniform_u32(uint32_t v)
 {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
@@ -278,6 +302,41 @@ __device__ inline void ties_elect_mean(const float (&ps)[E], const float (&ns)[E
         for (int e = 0; e < E; ++e)
             acc[e] = acc[e] / (float)den[e];
     }
+}
+
+// Two deltas d0, d1 folded into their elements' TIES state with threshold
+// tau: keep d iff d >= tau (positive) or -d >= tau (negative); ps sums the
+// kept positive deltas, ns the kept negative ones, cpn counts them (low half
+// positive, high half negative).  Eight instructions per delta, the positive
+// test being the carry into the count's add (the compiler's own form takes
+// ten).  Every lane mask is read at least three instructions after the
+// compare that writes it (a VALU write of an SGPR needs two wait states
+// before a VALU reads it).  c16 holds 0x10000.
+__device__ inline void ties_fold2(float d0, float d1, float tau, uint32_t c16, float& ps0, float& ns0,
+                                  uint32_t& cpn0, float& ps1, float& ns1, uint32_t& cpn1)
+{
+    uint64_t kp0, kn0, kp1, kn1, co;
+    float t0, t1;
+    asm("v_cmp_le_f32_e64 %[kp0], %[tau], %[d0]\n\t"
+        "v_cmp_le_f32_e64 %[kn0], %[tau], -%[d0]\n\t"
+        "v_cmp_le_f32_e64 %[kp1], %[tau], %[d1]\n\t"
+        "v_cmp_le_f32_e64 %[kn1], %[tau], -%[d1]\n\t"
+        "v_cndmask_b32_e64 %[t0], 0, %[d0], %[kp0]\n\t"
+        "v_cndmask_b32_e64 %[t1], 0, %[d0], %[kn0]\n\t"
+        "v_add_f32_e32 %[ps0], %[ps0], %[t0]\n\t"
+        "v_add_f32_e32 %[ns0], %[ns0], %[t1]\n\t"
+        "v_cndmask_b32_e64 %[t0], 0, %[d1], %[kp1]\n\t"
+        "v_cndmask_b32_e64 %[t1], 0, %[d1], %[kn1]\n\t"
+        "v_add_f32_e32 %[ps1], %[ps1], %[t0]\n\t"
+        "v_add_f32_e32 %[ns1], %[ns1], %[t1]\n\t"
+        "v_cndmask_b32_e64 %[t0], 0, %[c16], %[kn0]\n\t"
+        "v_cndmask_b32_e64 %[t1], 0, %[c16], %[kn1]\n\t"
+        "v_addc_co_u32_e64 %[cpn0], %[co], %[cpn0], %[t0], %[kp0]\n\t"
+        "v_addc_co_u32_e64 %[cpn1], %[co], %[cpn1], %[t1], %[kp1]"
+        : [ps0] "+v"(ps0), [ns0] "+v"(ns0), [cpn0] "+v"(cpn0), [ps1] "+v"(ps1), [ns1] "+v"(ns1),
+          [cpn1] "+v"(cpn1), [kp0] "=&s"(kp0), [kn0] "=&s"(kn0), [kp1] "=&s"(kp1), [kn1] "=&s"(kn1),
+          [co] "=&s"(co), [t0] "=&v"(t0), [t1] "=&v"(t1)
+        : [d0] "v"(d0), [d1] "v"(d1), [tau] "v"(tau), [c16] "v"(c16));
 }
 
 // SplitMix64 output function: the value SplitMix64 returns when its state

@@ -9,15 +9,9 @@
 // the scores -- and therefore the plan -- are reproducible bit for bit.
 // The base block is re-read per expert from L2 (it stays resident: 8-16 KiB
 // per workgroup), so HBM sees it once.
+#include <algorithm>
 #include <cmath>
 
-// The catalog kernel keeps two copies of each window bin (the merge kernel
-// that trims in place keeps four): a wave's histogram row is then 4 KiB, the
-// workgroup's LDS 24 KiB and its registers fit five waves per SIMD.  More
-// waves in flight pay for the extra same-address atomics: on the headline
-// family the pass took 2.45-2.50 ms against 2.69 ms with four copies at four
-// waves (one copy at five waves: 2.59 ms; six waves spill).
-#define MP_TIES_NC 2
 #include "device_common.h"
 #include "mp_internal.h"
 #include "ties_select.h"
@@ -62,10 +56,7 @@ __device__ inline float block_sumsq(const uint4* __restrict__ b, const uint4* __
             }
         }
     }
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1)
-        p = p + __shfl_xor(p, s);
-    return p;
+    return wave_xor_sum(p);
 }
 
 template <int DT, bool DELTA>
@@ -89,25 +80,168 @@ __global__ __launch_bounds__(256) void k_index(const void* __restrict__ base, Ex
     }
 }
 
+// The smallest magnitude pattern of a block of n elements whose lane holds
+// the deltas of chunks lane, lane + 64, ... in d (padding left out): the
+// threshold that keeps everything.
+template <int R, int V>
+__device__ inline uint32_t smallest_mag(const float (&d)[R * V], uint32_t n, int lane)
+{
+    uint32_t mn = 0x7fffffffu;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool in = (uint32_t)(r * 64 + lane) * (uint32_t)V < n;
+#pragma unroll
+        for (int q = 0; q < V; ++q)
+            mn = min(mn, in ? mag_bits(d[r * V + q]) : 0x7fffffffu);
+    }
+    return ~wave_max_u32(~mn);
+}
+
+// Waves per SIMD of the catalog kernel, by the rows of chunks a lane holds.
+// 64 deltas and the raw rows they come from take 96 to 112 registers: five
+// waves, four for explicit deltas and fp32 (five spill there).
+template <int DT, bool DELTA, int ROWS>
+constexpr int cat_waves()
+{
+    return ROWS >= 16 ? 4 : ROWS >= 8 ? (DT == 1 && DELTA ? 4 : 5) : 8;
+}
+
 // Catalog statistics for TIES: per unit, the sum of squares of k_index
 // (same order, same bits; optional) and the trim threshold, the fp32
 // pattern of the k-th largest |d| of the (expert, block) unit for a keep
 // density (all ones when k = 0: a NaN pattern, which keeps nothing).  The
 // threshold depends on the unit and the density only, never on an access
-// mask, so merges at any budget can reuse it.  The base block is staged in
-// LDS once; wave w takes experts w, w+4, ... of the block: it holds the
-// whole unit's deltas in registers (64 per lane; lane l owns chunks l, l+64,
-// ...) and selects with its own LDS row, so after the staging the workgroup
-// never synchronises.
-#ifndef MP_CAT_WAVES
-#define MP_CAT_WAVES 5
-#endif
-template <int DT, bool DELTA>
-__global__ __launch_bounds__(256, DT == 1 ? MP_CAT_WAVES : 3) void k_index_ties(
+// mask, so merges at any budget can reuse it.
+//
+// One wave, a workgroup of its own, takes the units of one expert in U
+// consecutive blocks; R rows of 64 chunks hold the layout's longest block
+// (R * V deltas per lane).  Bound by HBM from 1024-element bf16 blocks up,
+// below by the fixed work of a unit (clearing and walking its histogram).
+// A wave alone has no barrier and no idle partners at K not a multiple of
+// four, and the rows fit the block instead of being padded to 4096
+// elements.  Against one 256-thread workgroup per 4096-element frame with
+// the base staged in LDS (4 layers of the Qwen2.5-1.5B shape, us): bf16 K = 4
+// blocks of 4096 / 2048 / 1024 / 512: 358 -> 330, 522 -> 308, 964 -> 354,
+// 1836 -> 465; K = 1: 190 -> 126; K = 6: 529 -> 455; fp32 blocks of 2048 /
+// 1024 (K = 6) / 512: 811 -> 594, 2733 -> 870, 3045 -> 727.  All 28 layers,
+// bf16, K = 4: 2480 -> 2200-2420 (6.4-7.0 TB/s).
+// Two blocks per wave hide the loads of a 1 KiB unit (512 bf16 elements: 536
+// -> 465 us); for larger units they cost registers and were slower.
+template <int DT, bool DELTA, int R, int U>
+__global__ __launch_bounds__(64, (cat_waves<DT, DELTA, R * U>())) void k_index_ties(
+    const void* __restrict__ base, ExpertPtrs ex, int K, uint64_t k_magic, uint32_t G, uint32_t per_xcd,
+    const uint64_t* __restrict__ boff, const uint32_t* __restrict__ blen, uint32_t n_full, uint32_t k_full,
+    double density, float gcoef, float* __restrict__ sumsq, uint32_t* __restrict__ tau)
+{
+    constexpr int V = Fmt<DT>::V;
+    constexpr int E = R * V;  // deltas per lane
+    __shared__ uint32_t row[ties::NB];
+    const int lane = threadIdx.x;
+    // id -> (run of U blocks, expert), the expert fastest, a run's experts on
+    // one XCD (x = id mod 8) so that they read its base through one L2.  Each
+    // XCD takes a contiguous range of runs (1887 against 1994 us for the
+    // runs x, x + 8, ... on 28 layers in bf16), except with 16 KiB units,
+    // where the interleaved order is faster (K = 2: 358 against 378 us)
+    const uint32_t pos = blockIdx.x >> 3, xcd = blockIdx.x & 7u;
+    const uint32_t q8 = K > 1 ? (uint32_t)__umul64hi((uint64_t)pos, k_magic) : pos;
+    const uint32_t i = pos - q8 * (uint32_t)K;
+    const uint32_t first = (R >= 16 ? q8 * 8u + xcd : xcd * per_xcd + q8) * (uint32_t)U;  // the run's first block
+    if (first >= G)
+        return;
+    constexpr int RG = R > 8 ? 8 : R;  // rows loaded before the first use (fp32: 16 of each would spill)
+    uint32_t n[U];
+    uint64_t off[U];
+    uint4 xb[U][RG], xe[U][RG];
+    // Loads are buffer loads over the block's byte range: lanes past a short
+    // block's end read zeros without a branch.  The base is cached (the
+    // block's other experts read it too).
+    auto load = [&](int j, int r0) {
+        const uint32_t nbytes = (first + (uint32_t)j < G) ? n[j] / (uint32_t)V * 16u : 0u;
+        if (!DELTA) {  // explicit deltas need no base
+            const __amdgpu_buffer_rsrc_t rb = block_rsrc(chunk_ptr(base, off[j], Fmt<DT>::esize), nbytes);
+#pragma unroll
+            for (int r = 0; r < RG; ++r)
+                xb[j][r] = bld16(rb, (uint32_t)((r0 + r) * 64 + lane) * 16u);
+        }
+        const __amdgpu_buffer_rsrc_t re = block_rsrc(chunk_ptr(ex.p[i], off[j], Fmt<DT>::esize), nbytes);
+#pragma unroll
+        for (int r = 0; r < RG; ++r)
+            xe[j][r] = bld16s(re, (uint32_t)((r0 + r) * 64 + lane) * 16u);
+    };
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const uint32_t g = min(first + (uint32_t)j, G - 1u);
+        off[j] = boff[g];
+        n[j] = blen[g];
+        load(j, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        if (U > 1 && first + (uint32_t)j >= G)
+            break;
+        float d[E];
+        float p = 0.0f;
+#pragma unroll
+        for (int r0 = 0; r0 < R; r0 += RG) {
+            if (r0 > 0) {
+                __builtin_amdgcn_sched_barrier(0);  // the compiler would hoist these loads and spill
+                load(j, r0);
+            }
+#pragma unroll
+            for (int r = 0; r < RG; ++r) {
+                float fb[V], fe[V];
+                if (!DELTA)
+                    Fmt<DT>::unpack(xb[j][r], fb);
+                Fmt<DT>::unpack(xe[j][r], fe);
+#pragma unroll
+                for (int q = 0; q < V; ++q) {
+                    const int e = (r0 + r) * V + q;
+                    d[e] = DELTA ? fe[q] : fe[q] - fb[q];  // padding: 0 - 0
+                    p = fmaf(d[e], d[e], p);  // + 0 on padding, exact
+                }
+            }
+        }
+        p = wave_xor_sum(p);
+        uint32_t k = k_full;
+        if (n[j] != n_full) {
+            const double kk = ceil(density * (double)n[j]);
+            k = (kk >= (double)n[j]) ? n[j] : (uint32_t)kk;
+        }
+        uint32_t th;
+        if (k == 0u) {
+            th = 0xffffffffu;
+        } else if (k == n[j]) {
+            th = smallest_mag<R, V>(d, n[j], lane);
+        } else {
+            // a guess at tau: gcoef times the deltas' root mean square
+            const uint32_t guess = __float_as_uint(gcoef * sqrtf(p / (float)n[j]));
+            th = wave_kth_largest<E>(reinterpret_cast<char*>(row), 0, d, k, lane, guess);
+            if (U > 1)
+                wave_lds_sync();  // the row is the next unit's
+        }
+        if (lane == 0) {
+            const uint32_t u = (first + (uint32_t)j) * (uint32_t)K + i;  // < 2^32 (checked by the host)
+            if (sumsq != nullptr)
+                sumsq[u] = p;
+            tau[u] = th;
+        }
+    }
+}
+
+// fp32 blocks of more than 2048 elements: one 256-thread workgroup per block,
+// the base staged in LDS once and wave w taking experts w, w + 4, ... (each
+// with its own LDS row; no barrier after the staging).  A wave per unit needs
+// 128 registers for 16 rows of base and expert and reads each 16 KiB base
+// block K times from L2: at K = 4 / 8 / 16 it takes 608 / 1141 / 2287 us, this
+// 611 / 1087 / 2059 (4 layers of the Qwen2.5-1.5B shape, medians over three
+// processes).  With K < 4 some of the four waves idle (K = 1 / 2: 341 / 380
+// against 250 / 358 us), and explicit deltas have no base to stage.
+__global__ __launch_bounds__(256, 3) void k_index_ties_staged(
     const void* __restrict__ base, ExpertPtrs ex, int K, const uint64_t* __restrict__ boff,
     const uint32_t* __restrict__ blen, uint32_t n_full, uint32_t k_full, double density, float gcoef,
     float* __restrict__ sumsq, uint32_t* __restrict__ tau)
 {
+    constexpr int DT = 0;
     constexpr int V = Fmt<DT>::V;
     constexpr int R = kTiesMaxBlock / 64 / V;  // chunk rows per lane
     constexpr int E = R * V;                   // deltas per lane
@@ -132,23 +266,22 @@ __global__ __launch_bounds__(256, DT == 1 ? MP_CAT_WAVES : 3) void k_index_ties(
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             float fb[V], fe[V];
-            if (!DELTA)
-                Fmt<DT>::unpack(xb[r * 64 + lane], fb);
+            Fmt<DT>::unpack(xb[r * 64 + lane], fb);
             Fmt<DT>::unpack(xe[r], fe);
 #pragma unroll
             for (int q = 0; q < V; ++q) {
-                d[r * V + q] = DELTA ? fe[q] : fe[q] - fb[q];  // padding: 0 - 0
+                d[r * V + q] = fe[q] - fb[q];  // padding: 0 - 0
                 p = fmaf(d[r * V + q], d[r * V + q], p);  // + 0 on padding, exact
             }
         }
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1)
-            p = p + __shfl_xor(p, s);
+        p = wave_xor_sum(p);
         // a guess at tau: gcoef times the deltas' root mean square
         const uint32_t guess = __float_as_uint(gcoef * sqrtf(p / (float)n));
-        const uint32_t th = (k == 0u) ? 0xffffffffu
-                                      : wave_kth_largest<E>(reinterpret_cast<char*>(&rows[0][0]), wave * ties::NB * 4,
-                                                            d, k, lane, guess);
+        uint32_t th = 0xffffffffu;
+        if (k == n)
+            th = smallest_mag<R, V>(d, n, lane);
+        else if (k != 0u)
+            th = wave_kth_largest<E>(reinterpret_cast<char*>(&rows[0][0]), wave * ties::NB * 4, d, k, lane, guess);
         if (lane == 0) {
             if (sumsq != nullptr)
                 sumsq[g * K + i] = p;
@@ -170,20 +303,16 @@ __global__ __launch_bounds__(256, DT == 1 ? MP_CAT_WAVES : 3) void k_index_ties(
     // and is staged while the expert is still in flight; further experts
     // (K > 4) are read one at a time.
     uint4 xbr[R / 4];
-    if (!DELTA) {  // explicit deltas need no base
-        const __amdgpu_buffer_rsrc_t rb = block_rsrc(chunk_ptr(base, off, Fmt<DT>::esize), nbytes);
+    const __amdgpu_buffer_rsrc_t rb = block_rsrc(chunk_ptr(base, off, Fmt<DT>::esize), nbytes);
 #pragma unroll
-        for (int q = 0; q < R / 4; ++q)
-            xbr[q] = bld16s(rb, (uint32_t)(q * 256 + t) * 16u);
-    }
+    for (int q = 0; q < R / 4; ++q)
+        xbr[q] = bld16s(rb, (uint32_t)(q * 256 + t) * 16u);
     uint4 xf[R];
     load_expert(wave < K ? wave : 0, wave < K ? nbytes : 0u, xf);
-    if (!DELTA) {
 #pragma unroll
-        for (int q = 0; q < R / 4; ++q)
-            xb[q * 256 + t] = xbr[q];  // zeros past the block's end
-        __syncthreads();
-    }
+    for (int q = 0; q < R / 4; ++q)
+        xb[q * 256 + t] = xbr[q];  // zeros past the block's end
+    __syncthreads();
     if (wave < K)
         unit(wave, xf);
     for (int i = wave + 4; i < K; i += 4) {
@@ -226,15 +355,44 @@ hipError_t launch_index_ties(const BlockTable& bt, const void* base, const Exper
     // which values the first histogram pass counts; the thresholds are exact
     // for any data.
     const float gcoef = (float)(0.8 * normal_two_sided_quantile(density));
-    const dim3 grid((unsigned)bt.G), block(256);
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, block, 0, s, base, ex, K, bt.d_off, bt.d_len, n_full, k_full, density, gcoef,
-                           sumsq, tau);
+    // pos / K = mulhi(pos, floor(2^64 / K) + 1) for pos < 2^32, K > 1
+    const uint64_t magic = K > 1 ? ~(uint64_t)0 / (uint64_t)K + 1u : 0u;
+    auto go = [&](auto kern, int64_t U) {
+        // a launch has fewer than 2^32 threads: very many units take several
+        const int64_t most = ((int64_t)1 << 25) / K * U;
+        for (int64_t g0 = 0; g0 < bt.G; g0 += most) {
+            const int64_t G = std::min(most, bt.G - g0), per_xcd = ((G + U - 1) / U + 7) / 8;
+            hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd * K)), dim3(64), 0, s, base, ex, K, magic, (uint32_t)G,
+                               (uint32_t)per_xcd, bt.d_off + g0, bt.d_len + g0, n_full, k_full, density, gcoef,
+                               sumsq != nullptr ? sumsq + g0 * K : nullptr, tau + g0 * K);
+        }
     };
-    if (bt.dtype == 0)
-        delta ? go(k_index_ties<0, true>) : go(k_index_ties<0, false>);
-    else
-        delta ? go(k_index_ties<1, true>) : go(k_index_ties<1, false>);
+#define MP_CAT(DTV, RV, UV)                                                                                            \
+    (delta ? go(k_index_ties<DTV, true, RV, UV>, UV) : go(k_index_ties<DTV, false, RV, UV>, UV))
+    // rows of 64 chunks per unit from the layout's longest block
+    if (bt.dtype == 0) {
+        if (bt.max_len <= 512)
+            MP_CAT(0, 2, 1);
+        else if (bt.max_len <= 1024)
+            MP_CAT(0, 4, 1);
+        else if (bt.max_len <= 2048)
+            MP_CAT(0, 8, 1);
+        else if (delta || K < 4)
+            MP_CAT(0, 16, 1);
+        else
+            hipLaunchKernelGGL(k_index_ties_staged, dim3((unsigned)bt.G), dim3(256), 0, s, base, ex, K, bt.d_off, bt.d_len, n_full,
+                               k_full, density, gcoef, sumsq, tau);
+    } else {
+        if (bt.max_len <= 512)
+            MP_CAT(1, 1, 2);
+        else if (bt.max_len <= 1024)
+            MP_CAT(1, 2, 1);
+        else if (bt.max_len <= 2048)
+            MP_CAT(1, 4, 1);
+        else
+            MP_CAT(1, 8, 1);
+    }
+#undef MP_CAT
     return hipGetLastError();
 }
 

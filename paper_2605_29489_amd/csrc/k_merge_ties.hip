@@ -7,7 +7,6 @@
 // way, and halving the histogram rows (33 to 17 KiB per workgroup) took the
 // merges on the Qwen2.5-1.5B-shaped family at B = 25/50/100% from 1.90 /
 // 2.71 / 4.03 ms to 1.82 / 2.61 / 3.97 ms.  A fifth wave spills the deltas.
-#define MP_TIES_NC 2
 #include "device_common.h"
 #include "merge_src.h"
 #include "mp_internal.h"
@@ -147,7 +146,7 @@ __device__ inline uint32_t block_radix_select(TiesSmem& sm, int j, const float (
         }
         __syncthreads();
         if (wave == 0) {
-            const Cut c = wave_find_from_top<1>(h, (1 << wd) - 1, r, lane);
+            const Cut c = wave_find_from_top(h, (1 << wd) - 1, r, lane);
             if (lane == 0) {
                 sm.st[j][1] = c.bin;
                 sm.st[j][2] = c.rank;
@@ -215,11 +214,12 @@ __device__ inline void ties_deltas(TiesSmem& sm, const uint4 (&raw)[ties::GS][CP
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
                     d[j][q * V + v] = fmaf(-bsub, x0[q * V + v], x[v]);  // x - x0 or the delta; padding 0
-                    ss = fmaf(d[j][q * V + v], d[j][q * V + v], ss);
+                    if (q == 0)  // a part of the block is enough for the guess
+                        ss = fmaf(d[j][q * V + v], d[j][q * V + v], ss);
                 }
 #pragma unroll
                 for (int v = 0; v < V; v += 2)  // pairs: one three-way maximum each
-                    mx = fmaxf(mx, fmaxf(fabsf(d[j][q * V + v]), fabsf(d[j][q * V + v + 1])));
+                    mx = max3_abs(mx, d[j][q * V + v], d[j][q * V + v + 1]);
             }
             const uint32_t w = wave_max_u32(__float_as_uint(mx));
             ss = wave_sum_f32(ss);
@@ -236,7 +236,7 @@ __device__ inline void ties_deltas(TiesSmem& sm, const uint4 (&raw)[ties::GS][CP
 // patterns) and returns the largest |d| pattern of the group's slots.  Every
 // thread of the workgroup calls it.
 template <int E>
-__device__ inline uint32_t ties_select_group(TiesSmem& sm, uint32_t n, uint32_t k, int ns, float gcoef,
+__device__ inline uint32_t ties_select_group(TiesSmem& sm, uint32_t n, uint32_t n_guess, uint32_t k, int ns, float gcoef,
                                              const float (&d)[ties::GS][E], uint32_t (&tau)[ties::GS])
 {
     using namespace ties;
@@ -261,7 +261,7 @@ __device__ inline uint32_t ties_select_group(TiesSmem& sm, uint32_t n, uint32_t 
                 const uint32_t wfloor = window_floor(wb);
                 // the guess only decides which values the first pass counts
                 // (any value, NaN included, leaves tau exact)
-                const float gf = gcoef * __builtin_amdgcn_sqrtf(ss * __builtin_amdgcn_rcpf((float)n));
+                const float gf = gcoef * __builtin_amdgcn_sqrtf(ss * __builtin_amdgcn_rcpf((float)min(n, n_guess)));
                 const uint32_t guess = (gcoef > 0.0f) ? __float_as_uint(gf) : 0u;
                 flo[j] = (guess > wfloor) ? (guess >> KS) << KS : wfloor;
                 if (t == 0)
@@ -278,7 +278,7 @@ __device__ inline uint32_t ties_select_group(TiesSmem& sm, uint32_t n, uint32_t 
     // ---- C: one wave per expert finds the bin of the k-th largest
     // wave j (all lanes): the state of slot j from a walk of its histogram
     auto walk = [&](int j, uint32_t bm, bool partial) {
-        const Cut c = wave_find_from_top<NC>(sm.h[j], NBIN - 1, k, lane);
+        const Cut c = wave_find_window(sm.h[j], k, lane);
         const int wb = window_base(bm);
         uint32_t state = DONE, v1 = 1u, v2 = 0u;  // v1: tau, or the bucket key to refine
         if (!c.found) {
@@ -427,7 +427,7 @@ __device__ inline uint32_t ties_trim_group(TiesSmem& sm, const Src& src, int64_t
     ties_load_group<DT, CPT>(src, b, off, n, gm, rank0, raw, ctr);
     const int ns = __popc(gm);
     ties_deltas<DT, CPT>(sm, raw, ns, x0, d, bsub);
-    return ties_select_group<CPT * Fmt<DT>::V>(sm, n, k, ns, gcoef, d, tau);
+    return ties_select_group<CPT * Fmt<DT>::V>(sm, n, ties::NT * Fmt<DT>::V, k, ns, gcoef, d, tau);
 }
 
 // Keep test and the running signed masses of element e over NS slots, with
@@ -647,7 +647,7 @@ __global__ __launch_bounds__(ties::NT, MULTI ? ties::NT / 128 : MP_TIES_WAVES) v
         uint32_t top = 0u;
         if (ns != 0) {
             ties_deltas<DT, CPT>(sm, raw, ns, x0, d, bsub);
-            top = ties_select_group<E>(sm, n, k, ns, gcoef, d, tau);
+            top = ties_select_group<E>(sm, n, NT * V, k, ns, gcoef, d, tau);
         }
         const bool big = top >= 0x7e000000u;  // some |d| >= 2^125: masses may overflow
         switch (ns) {

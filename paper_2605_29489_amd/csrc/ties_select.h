@@ -14,114 +14,117 @@
 
 #include "device_common.h"
 
-#ifndef MP_TIES_MB
-#define MP_TIES_MB 7
-#endif
-#ifndef MP_TIES_NC
-#define MP_TIES_NC 4
-#endif
-#ifndef MP_TIES_ASM
-#define MP_TIES_ASM 1
-#endif
-
 namespace mp {
 
 namespace ties {
-constexpr int MB = MP_TIES_MB;  // mantissa bits in a window key
-constexpr int NC = MP_TIES_NC;  // copies of each window bin (lanes spread over them)
+constexpr int MB = 7;           // mantissa bits in a window key
+constexpr int NC = 2;           // copies of each window bin (lanes spread over them)
 constexpr int KS = 23 - MB;     // pattern bits below a key
 constexpr int NBIN = 4 << MB;   // window bins: four binades
-constexpr int NB = NBIN * NC;    // words per histogram row
-static_assert(NBIN * NC == NB, "a histogram row holds every copy of every bin");
-static_assert(NC == 1 || NC == 2 || NC == 4 || NC == 8 || NC == 16, "bins are 16-byte aligned or fill one");
-constexpr int LG = (NC == 1) ? 2 : (NC == 2) ? 3 : (NC == 4) ? 4 : (NC == 8) ? 5 : 6;  // log2(4 NC)
+constexpr int NB = NBIN * NC;   // words per histogram row
+constexpr int LG = 3;           // log2 of a bin's bytes (4 NC)
+static_assert((4 * NC) == (1 << LG), "a bin's bytes");
 enum : uint32_t { DONE = 0u, LIST = 1u, RADIX = 2u };
 }  // namespace ties
 
 
 struct Cut {
     uint32_t found, bin, rank, count, aux;  // wave-uniform
+    uint32_t total;                         // elements counted in the whole histogram (window walks)
 };
 
-// Wave-level, all lanes: walk histogram bins downward from bin `top` and
-// find the bin where the count from the top first reaches k.  A bin is NC
-// consecutive words; counts are the low 16 bits of the word sums and aux
-// returns the bin's high-half sum.  rank = k minus the count above the bin.
-// Each round reads 1 KB: 16 consecutive bytes per lane (conflict-free), and
-// prefix-sums the lane totals across the wave with DPP.
-template <int NC>
+// Wave-level, all lanes: the bin of the window histogram h (NBIN bins of NC
+// = 2 words) where the count from the top first reaches k.  A bin's count is
+// the low 16 bits of its words' sum, aux the high half's.  rank = k minus the
+// count above the bin.  The whole row (at most 65,535 elements) is read at
+// once, 16 consecutive bytes per lane and read (conflict-free), and the four
+// quarter rows' lane sums are prefix-summed two to a register, so the walk
+// costs one LDS latency and one chain of seven adds wherever the cut lies;
+// quarter after quarter it was up to four of each, on the critical path of
+// every unit.
+__device__ inline Cut wave_find_window(const uint32_t* __restrict__ h, uint32_t k, int lane)
+{
+    using namespace ties;
+    static_assert(NC == 2 && NB == 4 * 256, "four reads of 64 lanes x 4 words cover the row");
+    uint32_t hi[4], lo[4], s[4];  // the lane's two bins of each quarter (hi above lo), their counts
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint4 raw = *reinterpret_cast<const uint4*>(h + NB - 4 - 4 * (j * 64 + lane));
+        hi[j] = raw.z + raw.w;
+        lo[j] = raw.x + raw.y;
+        s[j] = (hi[j] + lo[j]) & 0xffffu;
+    }
+    const uint32_t i01 = wave_incl_sum(s[0] | (s[1] << 16)), i23 = wave_incl_sum(s[2] | (s[3] << 16));
+    const uint32_t t01 = (uint32_t)__builtin_amdgcn_readlane((int)i01, 63);
+    const uint32_t t23 = (uint32_t)__builtin_amdgcn_readlane((int)i23, 63);
+    const uint32_t c0 = t01 & 0xffffu, c1 = c0 + (t01 >> 16), c2 = c1 + (t23 & 0xffffu), c3 = c2 + (t23 >> 16);
+    Cut r{0u, 0u, 0u, 0u, 0u, c3};
+    if (k > c3)
+        return r;
+    // the quarter holding the cut (wave-uniform), and the lane's bins there
+    uint32_t above, incl, sj, hj, lj, q;
+    if (k <= c1) {
+        const bool f = k <= c0;
+        q = f ? 0u : 1u;
+        above = f ? 0u : c0;
+        incl = f ? (i01 & 0xffffu) : (i01 >> 16);
+        sj = f ? s[0] : s[1];
+        hj = f ? hi[0] : hi[1];
+        lj = f ? lo[0] : lo[1];
+    } else {
+        const bool f = k <= c2;
+        q = f ? 2u : 3u;
+        above = f ? c1 : c2;
+        incl = f ? (i23 & 0xffffu) : (i23 >> 16);
+        sj = f ? s[2] : s[3];
+        hj = f ? hi[2] : hi[3];
+        lj = f ? lo[2] : lo[3];
+    }
+    const uint32_t before = above + incl - sj;
+    const unsigned long long bal = __ballot(before < k && k <= before + sj);
+    const int src = __ffsll((long long)bal) - 1;  // exactly one lane
+    const uint32_t hb = (uint32_t)__builtin_amdgcn_readlane((int)hj, src);
+    const uint32_t lb = (uint32_t)__builtin_amdgcn_readlane((int)lj, src);
+    const uint32_t bf = (uint32_t)__builtin_amdgcn_readlane((int)before, src);
+    const uint32_t hc = hb & 0xffffu;
+    const bool up = bf + hc >= k;  // the cut lies in the lane's upper bin
+    const uint32_t w = up ? hb : lb;
+    r.found = 1u;
+    r.bin = (uint32_t)(NBIN - 1) - 2u * (q * 64u + (uint32_t)src) - (up ? 0u : 1u);
+    r.rank = k - bf - (up ? 0u : hc);
+    r.count = w & 0xffffu;
+    r.aux = w >> 16;
+    return r;
+}
+
+// Wave-level, all lanes: as above over one-word bins (a radix digit's
+// counters), walking downward from bin `top` in rounds of 256.
 __device__ inline Cut wave_find_from_top(const uint32_t* __restrict__ h, int top, uint32_t k, int lane)
 {
-    if (NC >= 4) {  // one bin per lane per round
-        Cut r{0u, 0u, 0u, 0u, 0u};
-        uint32_t above = 0;
-        for (int hb = top; hb >= 0; hb -= 64) {
-            const int bin = hb - lane;
-            uint32_t w = 0u;
-            if (bin >= 0) {
-                const uint4* p = reinterpret_cast<const uint4*>(h + bin * NC);
-#pragma unroll
-                for (int u = 0; u < NC / 4; ++u) {
-                    const uint4 raw = p[u];
-                    w += raw.x + raw.y + raw.z + raw.w;
-                }
-            }
-            const uint32_t s = w & 0xffffu;
-            const uint32_t incl = wave_incl_sum(s);
-            const uint32_t before = above + incl - s;
-            const bool hit = before < k && k <= above + incl;
-            const unsigned long long bal = __ballot(hit);
-            if (bal) {
-                const int src = __ffsll((long long)bal) - 1;
-                r.found = 1u;
-                r.bin = (uint32_t)__builtin_amdgcn_readlane(bin, src);
-                r.rank = (uint32_t)__builtin_amdgcn_readlane((int)(k - before), src);
-                r.count = (uint32_t)__builtin_amdgcn_readlane((int)s, src);
-                r.aux = (uint32_t)__builtin_amdgcn_readlane((int)(w >> 16), src);
-                return r;
-            }
-            above += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        }
-        return r;
-    }
-    constexpr int BPL = NC >= 4 ? 1 : 4 / NC;  // bins per lane per round
-    Cut r{0u, 0u, 0u, 0u, 0u};
-    const int topw = top * NC + NC - 1;  // highest word
+    Cut r{0u, 0u, 0u, 0u, 0u, 0u};
     uint32_t above = 0;
-    for (int hi = topw | 3; hi >= 0; hi -= 256) {
+    for (int hi = top | 3; hi >= 0; hi -= 256) {
         const int g4 = hi - 4 * lane - 3;  // multiple of 4: the lane's words are g4 .. g4+3
         uint4 raw = make_uint4(0u, 0u, 0u, 0u);
         if (g4 >= 0)
             raw = *reinterpret_cast<const uint4*>(h + g4);
-        uint32_t bw[BPL];  // bin sums, highest bin first
-        if (NC == 1) {
-            bw[0] = raw.w; bw[BPL > 1 ? 1 : 0] = raw.z; bw[BPL > 2 ? 2 : 0] = raw.y; bw[BPL > 3 ? 3 : 0] = raw.x;
-        } else if (NC == 2) {
-            bw[0] = raw.z + raw.w; bw[BPL > 1 ? 1 : 0] = raw.x + raw.y;
-        } else {
-            bw[0] = raw.x + raw.y + raw.z + raw.w;
-        }
-        uint32_t s = 0u;
-#pragma unroll
-        for (int q = 0; q < BPL; ++q)
-            s += bw[q] & 0xffffu;
+        const uint32_t bw[4] = {raw.w, raw.z, raw.y, raw.x};  // highest bin first
+        const uint32_t s = raw.x + raw.y + raw.z + raw.w;
         const uint32_t incl = wave_incl_sum(s);
         const uint32_t before = above + incl - s;  // count in the bins above this lane's
         const bool hit = before < k && k <= above + incl;
         const unsigned long long bal = __ballot(hit);
         if (bal) {
-            uint32_t c = before, bin = 0u, cnt = 0u, aux = 0u;
+            uint32_t c = before, bin = 0u, cnt = 0u;
             bool got = false;
 #pragma unroll
-            for (int q = 0; q < BPL; ++q) {
-                const uint32_t cq = bw[q] & 0xffffu;
-                if (!got && (c + cq >= k || q == BPL - 1)) {
+            for (int q = 0; q < 4; ++q) {
+                if (!got && (c + bw[q] >= k || q == 3)) {
                     got = true;
-                    bin = (uint32_t)(g4 / NC + BPL - 1 - q);
-                    cnt = cq;
-                    aux = bw[q] >> 16;
+                    bin = (uint32_t)(g4 + 3 - q);
+                    cnt = bw[q];
                 } else if (!got) {
-                    c += cq;
+                    c += bw[q];
                 }
             }
             const int src = __ffsll((long long)bal) - 1;
@@ -129,7 +132,6 @@ __device__ inline Cut wave_find_from_top(const uint32_t* __restrict__ h, int top
             r.bin = (uint32_t)__builtin_amdgcn_readlane((int)bin, src);
             r.rank = (uint32_t)__builtin_amdgcn_readlane((int)(k - c), src);
             r.count = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
-            r.aux = (uint32_t)__builtin_amdgcn_readlane((int)aux, src);
             return r;
         }
         above += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
@@ -203,7 +205,6 @@ __device__ inline void window_add(char* base, uint32_t bits, uint32_t floor_bits
     const bool in = MAG ? bits >= floor_bits : fabsf(__uint_as_float(bits)) >= __uint_as_float(floor_bits);
     // the address and increment are formed in every lane (one instruction
     // each either way), so inc flows from element to element unmerged
-#if MP_TIES_ASM
     static_assert(KS == 16, "the low bits are the low half-word");
     uint32_t key, boff;
     asm("v_bfe_u32 %0, %1, %2, %3" : "=v"(key) : "v"(bits), "i"(KS), "i"(31 - KS));
@@ -211,10 +212,6 @@ __device__ inline void window_add(char* base, uint32_t bits, uint32_t floor_bits
     // high half-word of inc = min(low half-word of bits, 1); low half-word kept
     asm("v_min_u32_sdwa %0, %1, 1 dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:WORD_0 src1_sel:DWORD"
         : "+v"(inc) : "v"(bits));
-#else
-    const uint32_t boff = (__builtin_amdgcn_ubfe(bits, KS, 31 - KS) << LG) + koff;
-    inc = (min(bits & ((1u << KS) - 1u), 1u) << 16) + 1u;
-#endif
     if (in)
         atomicAdd(reinterpret_cast<uint32_t*>(base + boff), inc);
 }
@@ -306,13 +303,57 @@ __device__ inline uint32_t wave_kth_largest(char* base, int row_off, const float
         for (int e = 0; e < E; ++e)
             window_add<false>(base, __float_as_uint(d[e]), flo, koff, inc);
         wave_lds_sync();
-        c = wave_find_from_top<NC>(h, NBIN - 1, k, lane);
+        c = wave_find_window(h, k, lane);
         if (c.found || flo == wfloor)
             break;
         flo = wfloor;  // below the guess: count the whole window
         wave_lds_sync();
     }
-    if (c.found) {  // else the k-th largest lies below the window
+    if (!c.found) {
+        // The k-th largest lies below the window (high densities, deltas that
+        // mostly round to zero): windows further down, each anchored at the
+        // largest magnitude below the last one.  Every step goes down at
+        // least four binades and stops at zero.  A NaN is in no window: units
+        // that hold one go to the radix select, where it ranks above infinity.
+        bool nan = false;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            nan |= mag_bits(d[e]) > 0x7f800000u;
+        uint32_t r = k - c.total, below = wfloor;
+#pragma unroll 1
+        while (!__any(nan)) {
+            uint32_t mx = 0u;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const uint32_t mg = mag_bits(d[e]);
+                mx = max(mx, mg < below ? mg : 0u);
+            }
+            mx = wave_max_u32(mx);
+            if (mx == 0u)
+                return 0u;  // only zeros are left
+            const uint32_t ko = window_koff(mx, lane, &wb) + (uint32_t)row_off;
+            const uint32_t fl = window_floor(wb);
+            wave_lds_sync();
+#pragma unroll
+            for (int q = 0; q < NB / 256; ++q)
+                *reinterpret_cast<uint4*>(&h[4 * (q * 64 + lane)]) = make_uint4(0u, 0u, 0u, 0u);
+            wave_lds_sync();
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const uint32_t mg = mag_bits(d[e]);
+                if (mg >= fl && mg < below)
+                    atomicAdd(reinterpret_cast<uint32_t*>(base + ((mg >> KS) << LG) + ko),
+                              (mg & ((1u << KS) - 1u)) != 0u ? 0x10001u : 1u);
+            }
+            wave_lds_sync();
+            c = wave_find_window(h, r, lane);
+            if (c.found)
+                break;
+            r -= c.total;
+            below = fl;
+        }
+    }
+    if (c.found) {
         if (c.aux < c.rank)
             return (uint32_t)(wb + (int)c.bin) << KS;  // the rank-th largest of the bin is its floor
         // list the bin's values, then fix their low bits one at a time
@@ -360,7 +401,7 @@ __device__ inline uint32_t wave_kth_largest(char* base, int row_off, const float
                 atomicAdd(&h[(mg >> sh) & ((1u << wd) - 1u)], 1u);
         }
         wave_lds_sync();
-        const Cut c = wave_find_from_top<1>(h, (1 << wd) - 1, r, lane);
+        const Cut c = wave_find_from_top(h, (1 << wd) - 1, r, lane);
         pref = (pref << wd) | c.bin;
         r = c.rank;
     }
