@@ -74,6 +74,8 @@ struct DeviceWs {
     uint32_t* tt_hist = nullptr;               // tensor-scope TIES: digit histograms per (expert, tensor)
     uint4* tt_state = nullptr;                 //   and the select state per pair (+ the error word)
     int64_t tt_pairs = 0;
+    uint32_t* tt_list = nullptr;               //   and the lists of the one-pass route
+    uint64_t tt_list_words = 0;
     uint32_t* h_tt_err = nullptr;              // pinned copy of the error word
 };
 
@@ -132,6 +134,7 @@ void free_ws(int dev, DeviceWs& w)
     (void)ws_free_r(w.cov);
     (void)ws_free_r(w.tt_hist);
     (void)ws_free_r(w.tt_state);
+    (void)ws_free_r(w.tt_list);
     (void)ws_host_free_r(w.h_tt_err);
     (void)hipSetDevice(cur);
 }
@@ -238,6 +241,12 @@ int get_table(const mp_layout* L, int esize, BlockTable** out)
         a = z;
     }
     bt->n_chunks = (int64_t)chunks.size();
+    uint64_t most = 0;
+    for (int32_t t = 0; t < L->n_tensors; ++t)
+        most = std::max<uint64_t>(most, (uint64_t)L->numel[t]);
+    const uint64_t words = ties_tensor_list_words((uint64_t)L->n_tensors, (uint64_t)bt->P);
+    if (L->block_elems <= kTiesMaxBlock && words < (1ull << 32) && most < (1ull << 31))
+        bt->tt_words = words;
     // the tensor-level plan's table
     std::vector<uint32_t> tlen((size_t)L->n_tensors), tg0((size_t)L->n_tensors + 1, 0);
     std::set<uint32_t> tl;
@@ -604,12 +613,33 @@ int run_merge(const mp_layout* L, const void* base, const void* const* experts, 
 }  // namespace
 
 namespace {
+void ws_give(void* p, bool host);
+
+// Gives back the lists of tensor-scope TIES, which no call needs to succeed
+// and no kernel uses between calls (each call on them synchronises).
+bool drop_optional()
+{
+    bool any = false;
+    for (auto& kv : g_ws) {
+        DeviceWs& w = *kv.second;
+        any |= w.tt_list != nullptr;
+        ws_give(w.tt_list, false);
+        w.tt_list = nullptr;
+        w.tt_list_words = 0;
+    }
+    return any;
+}
+
 hipError_t ws_take(void** p, size_t bytes, bool host)
 {
     *p = nullptr;
-    if (g_ws_limit != 0 && g_ws_held + bytes > g_ws_limit)
+    if (g_ws_limit != 0 && g_ws_held + bytes > g_ws_limit && !(drop_optional() && g_ws_held + bytes <= g_ws_limit))
         return hipErrorOutOfMemory;
-    const hipError_t e = host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
+    hipError_t e = host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
+    if (e != hipSuccess && drop_optional()) {
+        (void)hipGetLastError();
+        e = host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
+    }
     if (e != hipSuccess) {
         *p = nullptr;
         return e;
@@ -790,10 +820,25 @@ int mp_ties_tensor_thresholds(const mp_layout* layout, const void* base, const v
         ws.tt_state = nullptr;
         ws.tt_pairs = 0;
         if ((e = ws_malloc((void**)&ws.tt_hist, sizeof(uint32_t) * 2048 * (size_t)pairs)) != hipSuccess ||
-            (e = ws_malloc((void**)&ws.tt_state, sizeof(uint4) * (size_t)(pairs + 1))) != hipSuccess)
+            (e = ws_malloc((void**)&ws.tt_state, sizeof(uint4) * (size_t)(3 * pairs + 1))) != hipSuccess)
             return fail(MP_E_NOMEM, "tensor-scope TIES buffers: %s", hipGetErrorString(e));
         ws.tt_pairs = pairs;
     }
+    // lists for the route that reads the blocks once; without room for them
+    // (the workspace limit, a full device) the radix route needs none
+    const uint64_t need = (uint64_t)K * bt.tt_words;
+    if (need > ws.tt_list_words) {
+        (void)ws_free_r(ws.tt_list);
+        ws.tt_list = nullptr;
+        ws.tt_list_words = 0;
+        if (ws_malloc((void**)&ws.tt_list, sizeof(uint32_t) * (size_t)need) == hipSuccess) {
+            ws.tt_list_words = need;
+        } else {
+            ws.tt_list = nullptr;
+            (void)hipGetLastError();
+        }
+    }
+    uint32_t* const list = (need != 0u && need <= ws.tt_list_words) ? ws.tt_list : nullptr;
     // The scratch is shared by every call on this device: the call returns
     // only once its kernels are done (under the library lock), so a call on
     // another stream never finds it in use, and the error word is read here.
@@ -802,7 +847,8 @@ int mp_ties_tensor_thresholds(const mp_layout* layout, const void* base, const v
         return MP_OK;  // no units: nothing to select
     const char* hook = std::getenv("MP_FAULT_TENSOR_NO_CUT");
     const bool force = hook != nullptr && hook[0] == '1';
-    if ((e = launch_ties_tensor(bt, base, c.ex, K, mask, density, tau, ws.tt_hist, ws.tt_state, s, delta, force)) !=
+    if ((e = launch_ties_tensor(bt, base, c.ex, K, mask, density, tau, ws.tt_hist, ws.tt_state, list, s,
+                                delta, force)) !=
         hipSuccess)
         return hip_fail(e, "tensor-scope thresholds launch");
     if ((e = hipMemcpyAsync(ws.h_tt_err, ws.tt_state + pairs, sizeof(uint32_t), hipMemcpyDeviceToHost, s)) !=

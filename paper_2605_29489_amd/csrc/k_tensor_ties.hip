@@ -4,8 +4,30 @@
 // This is the per-tensor variant of Appendix A.1's trim; merges then use
 // the per-unit threshold kernel with each unit taking its tensor's value.
 //
-// An exact MSD radix select on the 31-bit magnitude patterns, three digit
-// passes (bits 30..20, 19..9, 8..0) over the selected blocks:
+// Two exact routes.  The bracket route reads the selected blocks once, after
+// a sample of about a sixteenth of them:
+//   k_tt_sample   (twice) histograms a slice of every selected block, first
+//                 of bits 30..20, then of the range that the first kept;
+//   k_tt_bracket  (twice) one wave per (expert, tensor) pair turns the sample
+//                 histogram into a bracket [lo, hi) of patterns around the
+//                 k-th largest, five standard deviations of the sample's rank
+//                 to either side;
+//   k_tt_scan     the full pass: counts the elements at or above hi, counts
+//                 the bracket's elements in 256 bins, and lists those of them
+//                 that do not equal their bin's floor (coarse bf16 deltas repeat
+//                 a few floors millions of times; those need no listing);
+//   k_tt_pick     one workgroup per pair: the bin that holds the k-th largest;
+//                 it is the bin's floor, or one of the listed elements.
+// Nothing depends on the sample being right: a pair whose k-th largest lies
+// outside its bracket, or whose list overflows, is left to the second route.
+// The full pass is bound by memory (base and selected experts once, 1.4 ms of
+// the 1.5B-parameter case against 4.5 ms for three digit passes).
+//
+// The radix route is an exact MSD select on the 31-bit magnitude patterns,
+// three digit passes (bits 30..20, 19..9, 8..0) over the selected blocks.  It
+// takes whole layouts with blocks over 4096 elements or without room for the
+// lists, and the pairs that the first route left (its kernels return at once
+// when there are none):
 //   k_tt_hist     one workgroup per (run of <= 16 consecutive blocks of one
 //                 tensor, expert): LDS histogram of the digit of the
 //                 elements that match the prefix fixed so far, nonzero bins
@@ -19,11 +41,15 @@
 //                 fewer than k selected elements give 0 (the k-th largest
 //                 is a completed zero);
 //   k_tt_expand   tau[g*K + i] = the pair's threshold for every unit.
-// State per pair (uint4): {prefix, remaining rank, done, tau}.
+// State per pair (uint4): {prefix, remaining rank, done, tau}; the entry after
+// the pairs' holds {error, pairs left by the first route, 0, 0}.  The bracket
+// route adds per pair {lo, hi - lo, bin shift, sampled elements above hi} and
+// {selected elements, elements above hi, listed, 0}.
 #include <cmath>
 
 #include "device_common.h"
 #include "mp_internal.h"
+#include "ties_select.h"
 
 namespace mp {
 
@@ -45,27 +71,27 @@ constexpr int kTH = 256, kCop = 2;
 __host__ __device__ inline int tt_shift(int pass) { return pass == 0 ? 20 : (pass == 1 ? 9 : 0); }
 __host__ __device__ inline int tt_width(int pass) { return pass == 2 ? 9 : 11; }
 
-__global__ __launch_bounds__(kTT) void k_tt_zero(uint32_t* __restrict__ p, int64_t n)
+__global__ __launch_bounds__(kTT) void k_tt_zero(uint32_t* __restrict__ p, int64_t n,
+                                                 const uint32_t* __restrict__ left = nullptr)
 {
+    if (left != nullptr && *left == 0u)
+        return;
     for (int64_t q = (int64_t)blockIdx.x * kTT + threadIdx.x; q < n; q += (int64_t)gridDim.x * kTT)
         p[q] = 0u;
 }
 
 template <int DT, bool DELTA, int kTH, int kCopies>
-__global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, ExpertPtrs ex, int K,
+__device__ inline void tt_hist_run(const void* __restrict__ base, ExpertPtrs ex, int K,
                                                   const uint4* __restrict__ chunks,
                                                   const uint64_t* __restrict__ boff,
                                                   const uint32_t* __restrict__ blen,
                                                   const uint32_t* __restrict__ mask,
                                                   const uint4* __restrict__ state, int T, int pass,
-                                                  uint32_t* __restrict__ hist, uint32_t n_pairs, uint32_t per_xcd)
+                                                  uint32_t* __restrict__ hist, uint32_t n_pairs, uint32_t pr)
 {
     constexpr int V = Fmt<DT>::V;
     __shared__ __align__(16) uint32_t h[kDigBins * kCopies];  // h[bin * kCopies + copy]
     static_assert(kCopies == 1 || kCopies == 2 || kCopies == 4, "a bin's copies are one LDS read");
-    // workgroup id -> (run, expert): XCD x = id mod 8 takes pairs
-    // x*per_xcd .. in order
-    const uint32_t pr = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (pr >= n_pairs)
         return;
     const uint4 ch = chunks[pr / (uint32_t)K];
@@ -140,11 +166,33 @@ __global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, 
     }
 }
 
+// Workgroup id -> (run, expert): XCD x = id mod 8 takes pairs x*per_xcd ..
+// in order, every gridDim.x / 8-th of them (grid: a multiple of 8).  `left`
+// (null: none) is the count of pairs that the bracket route left.
+template <int DT, bool DELTA, int kTH, int kCopies>
+__global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, ExpertPtrs ex, int K,
+                                                 const uint4* __restrict__ chunks, const uint64_t* __restrict__ boff,
+                                                 const uint32_t* __restrict__ blen, const uint32_t* __restrict__ mask,
+                                                 const uint4* __restrict__ state, int T, int pass,
+                                                 uint32_t* __restrict__ hist, uint32_t n_pairs, uint32_t per_xcd,
+                                                 const uint32_t* __restrict__ left)
+{
+    if (left != nullptr && *left == 0u)
+        return;
+    for (uint32_t j = blockIdx.x >> 3; j < per_xcd; j += gridDim.x >> 3) {
+        __syncthreads();  // the previous run's histogram has been read
+        tt_hist_run<DT, DELTA, kTH, kCopies>(base, ex, K, chunks, boff, blen, mask, state, T, pass, hist, n_pairs,
+                                             (blockIdx.x & 7u) * per_xcd + j);
+    }
+}
+
 __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, const uint32_t* __restrict__ hist,
                                                      const uint64_t* __restrict__ tnumel, int K, int T,
                                                      double density, int pass, uint32_t* __restrict__ err,
-                                                     int force_no_cut)
+                                                     int force_no_cut, const uint32_t* __restrict__ left)
 {
+    if (left != nullptr && *left == 0u)
+        return;
     const int lane = threadIdx.x & 63;
     const int64_t q = (int64_t)blockIdx.x * (kTT / 64) + (threadIdx.x >> 6);
     if (q >= (int64_t)K * T)
@@ -222,6 +270,418 @@ __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, c
     }
 }
 
+// ---------------------------------------------------------------- bracket route
+constexpr int kSampleShare = 16;          // the sample: a sixteenth of every block
+constexpr uint32_t kSampleRuns = 8;       // runs per sampling workgroup
+constexpr uint32_t kSmallTensor = 8192u;  // up to here a pair lists every element
+constexpr int kScanBins = 256, kScanCop = 4;
+constexpr uint32_t kScanList = 3584u;  // words of the workgroup's list (with the bins 18 KiB: eight workgroups a CU)
+
+// A pair's list: room for kSmallTensor words (every element of a small tensor)
+// and a 128th of the tensor; brackets typically hold a fraction of that, and a
+// pair that needs more takes the radix route.  first: the tensor's first
+// element in a checkpoint; the tensors before it take at most the words
+// before the offset returned.
+__device__ inline uint64_t tt_list_at(int i, uint32_t lwords, uint32_t t, uint64_t first)
+{
+    return (uint64_t)i * lwords + (uint64_t)t * kSmallTensor + first / 128u;
+}
+__device__ inline uint32_t tt_list_cap(uint64_t numel) { return kSmallTensor + (uint32_t)(numel / 128u); }
+
+// Adds a workgroup's nonzero sample bins to the pair's histogram and clears them.
+__device__ inline void tt_flush_sample(uint32_t* h, uint32_t* __restrict__ out)
+{
+    __syncthreads();
+    for (int q = (int)threadIdx.x; q < kDigBins; q += kTT) {
+        const uint32_t v = h[q];
+        if (v != 0u) {
+            atomicAdd(&out[q], v);
+            h[q] = 0u;
+        }
+    }
+    __syncthreads();
+}
+
+// Sample pass LV (0: bits 30..20 of every sampled element, and the pair's
+// selected elements; 1: the bracket's elements by (pattern - lo) >> shift).
+// One workgroup per expert and kSampleRuns consecutive runs; from block g of
+// a run it takes the (g mod 16)-th slice of segc 16-byte chunks, so the slices
+// visit every part of a tensor's blocks.
+template <int DT, bool DELTA, int LV>
+__global__ __launch_bounds__(kTT) void k_tt_sample(const void* __restrict__ base, ExpertPtrs ex, int K,
+                                                   const uint4* __restrict__ chunks,
+                                                   const uint64_t* __restrict__ boff,
+                                                   const uint32_t* __restrict__ blen,
+                                                   const uint32_t* __restrict__ mask, uint32_t n_runs, int T,
+                                                   uint32_t segc, const uint4* __restrict__ state,
+                                                   const uint4* __restrict__ br, uint32_t* __restrict__ hist,
+                                                   uint4* __restrict__ cnt)
+{
+    constexpr int V = Fmt<DT>::V;
+    __shared__ uint32_t h[kDigBins];
+    const int i = (int)(blockIdx.x % (uint32_t)K);
+    const uint32_t r0 = (blockIdx.x / (uint32_t)K) * kSampleRuns, r1 = min(r0 + kSampleRuns, n_runs);
+    const uint32_t tid = threadIdx.x;
+    for (int q = (int)tid; q < kDigBins; q += kTT)
+        h[q] = 0u;
+    __syncthreads();
+    uint32_t cur = 0xffffffffu;  // the tensor whose counts h holds
+    for (uint32_t r = r0; r < r1; ++r) {
+        const uint4 ch = chunks[r];
+        const size_t pq = (size_t)i * T + ch.z;
+        if (cur != ch.z && cur != 0xffffffffu)
+            tt_flush_sample(h, hist + ((size_t)i * T + cur) * kDigBins);
+        cur = ch.z;
+        uint32_t lo = 0u, width = 0x80000000u, sh = 20u;
+        if (LV == 1) {
+            if (state[pq].z != 0u)
+                continue;
+            const uint4 b = br[pq];
+            lo = b.x;
+            width = b.y;
+            sh = b.z;
+        }
+        const uint32_t nb = ch.y - ch.x;  // at most kChunkBlocks
+        if (LV == 0) {  // the selected elements of the run (one wave)
+            uint32_t n = (tid < nb && ((mask[ch.x + tid] >> i) & 1u)) ? blen[ch.x + tid] : 0u;
+            if (tid < 64u) {
+                n = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(n), 63);
+                if (tid == 0u && n != 0u)
+                    atomicAdd(&cnt[pq].x, n);
+            }
+        }
+        for (uint32_t q = tid; q < nb * segc; q += kTT) {
+            const uint32_t g = ch.x + q / segc, nch = blen[g] / V;
+            uint32_t c = (g % kSampleShare) * segc + q % segc;
+            if (nch <= (g % kSampleShare) * segc)
+                c = q % segc;  // a short block without that slice: its first one
+            if (!((mask[g] >> i) & 1u) || c >= nch)
+                continue;
+            const uint64_t off = boff[g];
+            float fe[V], fb[V];
+            Fmt<DT>::unpack(chunk_ptr(ex.p[i], off, Fmt<DT>::esize)[c], fe);
+            if (!DELTA)
+                Fmt<DT>::unpack(chunk_ptr(base, off, Fmt<DT>::esize)[c], fb);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const uint32_t mg = __float_as_uint(DELTA ? fe[v] : fe[v] - fb[v]) & 0x7fffffffu;
+                if (LV == 0 || mg - lo < width)
+                    atomicAdd(&h[(mg - lo) >> sh], 1u);
+            }
+        }
+    }
+    if (cur != 0xffffffffu)
+        tt_flush_sample(h, hist + ((size_t)i * T + cur) * kDigBins);
+}
+
+// The smallest shift that leaves the patterns [lo, hi) at most `bins` bins
+// (ALIGNED: bins of whole multiples of 2^shift, else counted from lo).
+__device__ inline uint32_t tt_shift_for(uint32_t lo, uint32_t hi, uint32_t bins, bool aligned)
+{
+    uint32_t s = 0u;
+    while ((aligned ? ((hi - 1u) >> s) - (lo >> s) : (hi - 1u - lo) >> s) >= bins)
+        ++s;
+    return s;
+}
+
+// One wave per pair after sample pass LV: narrows the pair's bracket and
+// clears its sample histogram.  Pass 0 also ends the pairs that keep nothing
+// (k = 0: all ones) or whose k-th largest is a completed zero (fewer than k
+// elements selected: 0).
+template <int LV>
+__global__ __launch_bounds__(kTT) void k_tt_bracket(uint4* __restrict__ state, uint4* __restrict__ br,
+                                                    const uint4* __restrict__ cnt, uint32_t* __restrict__ hist,
+                                                    const uint64_t* __restrict__ tnumel, int K, int T, double density)
+{
+    constexpr int per = kDigBins / 64;
+    const int lane = threadIdx.x & 63;
+    const int64_t q = (int64_t)blockIdx.x * (kTT / 64) + (threadIdx.x >> 6);
+    if (q >= (int64_t)K * T)
+        return;
+    const uint64_t n = tnumel[q % T];
+    const double kk = ceil(density * (double)n);
+    const uint64_t k = (kk >= (double)n) ? n : (uint64_t)kk;
+    const uint32_t N = cnt[q].x;
+    uint32_t* h = hist + (size_t)q * kDigBins;
+    uint32_t c[per], mine = 0u;
+#pragma unroll
+    for (int j = 0; j < per; j += 4) {
+        uint4* p = reinterpret_cast<uint4*>(h + lane * per + j);
+        const uint4 v = *p;
+        *p = make_uint4(0u, 0u, 0u, 0u);
+        c[j] = v.x;
+        c[j + 1] = v.y;
+        c[j + 2] = v.z;
+        c[j + 3] = v.w;
+        mine += v.x + v.y + v.z + v.w;
+    }
+    if (state[q].z != 0u)
+        return;
+    if (LV == 0 && (k == 0u || (uint64_t)N < k)) {
+        if (lane == 0)
+            state[q] = make_uint4(0u, 0u, 1u, k == 0u ? 0xffffffffu : 0u);
+        return;
+    }
+    uint4 b = LV == 0 ? make_uint4(0u, 0x80000000u, 20u, 0u) : br[q];
+    const uint32_t incl0 = wave_incl_sum(mine);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl0, 63);
+    const uint32_t above = total - incl0;  // samples in the bins of higher lanes
+    // the sampled elements (level 1 counts only the bracket's; the pair's
+    // sampled total travels in state.y)
+    const uint32_t ns = LV == 0 ? total : state[q].y;
+    uint32_t lo = b.x, hi = b.x + b.y, sab = b.w;  // hi: 2^31 at most
+    if (N > kSmallTensor && ns >= 64u) {
+        const double f = (double)ns / (double)N, p = (double)k / (double)N;
+        const double rs = (double)k * f, m = 5.0 * sqrt(rs * (1.0 - p)) + 8.0;
+        // ranks counted from the top of the bracket
+        const double rhi = rs - m - (double)b.w, rlo = rs + m - (double)b.w;
+        int bhi = -1, blo = -1;  // the bins that hold them, if any
+        uint32_t ahi = 0u, acc = above;
+#pragma unroll
+        for (int j = per - 1; j >= 0; --j) {
+            const double before = (double)acc, after = (double)(acc + c[j]);
+            if (rhi >= 1.0 && before < rhi && rhi <= after) {
+                bhi = lane * per + j;
+                ahi = acc;
+            }
+            if (rlo >= 1.0 && before < rlo && rlo <= after)
+                blo = lane * per + j;
+            acc += c[j];
+        }
+        const unsigned long long mh = __ballot(bhi >= 0), ml = __ballot(blo >= 0);
+        if (mh != 0ull) {  // otherwise the bracket keeps its top
+            const int src = __ffsll((long long)mh) - 1;
+            hi = min(hi, b.x + (((uint32_t)__shfl(bhi, src) + 1u) << b.z));
+            sab += __shfl(ahi, src);
+        }
+        if (ml != 0ull)  // otherwise it keeps its bottom
+            lo = b.x + ((uint32_t)__shfl(blo, __ffsll((long long)ml) - 1) << b.z);
+    }
+    if (lane == 0) {
+        const uint32_t s = LV == 0 ? tt_shift_for(lo, hi, kDigBins, false) : tt_shift_for(lo, hi, kScanBins, true);
+        br[q] = make_uint4(lo, hi - lo, s, sab);
+        if (LV == 0)
+            state[q].y = ns;
+    }
+}
+
+// The full pass.  One workgroup per (run, expert) in k_tt_hist's order.  Per
+// element two compares and a subtraction; the bracket's elements add to the
+// bins (four copies) and, off their bin's floor, to the workgroup's list,
+// which is appended to the pair's at the end (entries past the LDS list go
+// there directly; past the pair's room they are only counted, and the pair is
+// left to the radix route).
+template <int DT, bool DELTA>
+__global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, ExpertPtrs ex, int K,
+                                                 const uint4* __restrict__ chunks, const uint64_t* __restrict__ boff,
+                                                 const uint32_t* __restrict__ blen, const uint32_t* __restrict__ mask,
+                                                 const uint4* __restrict__ state, const uint4* __restrict__ br, int T,
+                                                 uint32_t* __restrict__ hist, uint4* __restrict__ cnt,
+                                                 uint32_t* __restrict__ list, const uint32_t* __restrict__ g0,
+                                                 const uint64_t* __restrict__ tnumel, uint32_t lwords,
+                                                 uint32_t n_pairs, uint32_t per_xcd)
+{
+    constexpr int V = Fmt<DT>::V;
+    __shared__ __align__(16) uint32_t h[kScanBins * kScanCop];
+    __shared__ uint32_t lst[kScanList];
+    __shared__ uint32_t s_n, s_at, s_above;
+    const uint32_t pr = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+    if (pr >= n_pairs)
+        return;
+    const uint4 ch = chunks[pr / (uint32_t)K];
+    const int i = (int)(pr % (uint32_t)K);
+    const size_t pq = (size_t)i * T + ch.z;
+    if (state[pq].z != 0u)
+        return;
+    const int tid = threadIdx.x;
+    static_assert(kChunkBlocks <= kTT, "a thread per block of a run");
+    if (!__syncthreads_or(tid < (int)(ch.y - ch.x) && ((mask[ch.x + (uint32_t)tid] >> i) & 1u)))
+        return;
+    const uint4 b = br[pq];
+    const uint32_t lo = b.x, width = b.y, sh = b.z, b0 = lo >> sh, hi = lo + width;
+    const uint32_t low = (1u << sh) - 1u;
+    uint32_t* const glist = list + tt_list_at(i, lwords, ch.z, boff[g0[ch.z]]);
+    const uint32_t cap = tt_list_cap(tnumel[ch.z]);
+    for (int q = tid; q < kScanBins * kScanCop; q += kTT)
+        h[q] = 0u;
+    if (tid == 0) {
+        s_n = 0u;
+        s_above = 0u;
+    }
+    __syncthreads();
+    const uint32_t cp = (uint32_t)(tid % kScanCop);
+    uint32_t above = 0u;
+    for (uint32_t g = ch.x; g < ch.y; ++g) {
+        if (!((mask[g] >> i) & 1u))
+            continue;
+        const uint64_t off = boff[g];
+        const uint32_t nch = blen[g] / V;
+        const uint4* pe = chunk_ptr(ex.p[i], off, Fmt<DT>::esize);
+        const uint4* pb = chunk_ptr(base, off, Fmt<DT>::esize);
+        for (uint32_t c0 = tid; c0 < nch; c0 += 2 * kTT) {
+            uint4 re[2], rb[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t c = c0 + (uint32_t)(u * kTT);
+                re[u] = c < nch ? ld16s(pe + c) : make_uint4(0u, 0u, 0u, 0u);
+                rb[u] = (!DELTA && c < nch) ? pb[c] : make_uint4(0u, 0u, 0u, 0u);  // cached: the run's other experts read it too
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (c0 + (uint32_t)(u * kTT) >= nch)
+                    continue;
+                float fe[V], fb[V];
+                Fmt<DT>::unpack(re[u], fe);
+                if (!DELTA)
+                    Fmt<DT>::unpack(rb[u], fb);
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const uint32_t mg = __float_as_uint(DELTA ? fe[v] : fe[v] - fb[v]) & 0x7fffffffu;
+                    above += mg >= hi ? 1u : 0u;
+                    if (mg - lo < width) {
+                        atomicAdd(&h[((mg >> sh) - b0) * kScanCop + cp], 1u);
+                        if ((mg & low) != 0u) {
+                            const uint32_t at = atomicAdd(&s_n, 1u);
+                            if (at < kScanList) {
+                                lst[at] = mg;
+                            } else {
+                                const uint32_t to = atomicAdd(&cnt[pq].z, 1u);
+                                if (to < cap)
+                                    glist[to] = mg;
+                            }
+                        }
+                    }
+                }
+            }
+        }
+    }
+    above = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(above), 63);
+    if ((tid & 63) == 0)
+        atomicAdd(&s_above, above);
+    __syncthreads();
+    const uint32_t n = min(s_n, kScanList);
+    if (tid == 0) {
+        s_at = n != 0u ? atomicAdd(&cnt[pq].z, n) : 0u;
+        if (s_above != 0u)
+            atomicAdd(&cnt[pq].y, s_above);
+    }
+    uint32_t* out = hist + pq * kDigBins;
+    for (int q = tid; q < kScanBins; q += kTT) {
+        const uint4 w = reinterpret_cast<const uint4*>(h)[q];
+        const uint32_t v = w.x + w.y + w.z + w.w;
+        if (v != 0u)
+            atomicAdd(&out[q], v);
+    }
+    __syncthreads();
+    const uint32_t at = s_at;
+    for (uint32_t q = (uint32_t)tid; q < n; q += kTT)
+        if (at + q < cap)
+            glist[at + q] = lst[q];
+}
+
+constexpr int kPick = 1024;
+
+// One workgroup per pair after the full pass (see the top of the file).  The
+// list is read once for patterns whose bin leaves at most 11 bits open, and
+// once more per further 11 bits; four independent loads a thread hide the
+// latency that bounds it.
+__global__ __launch_bounds__(kPick) void k_tt_pick(uint4* __restrict__ state, const uint4* __restrict__ br,
+                                                   const uint4* __restrict__ cnt, const uint32_t* __restrict__ hist,
+                                                   const uint32_t* __restrict__ list,
+                                                   const uint32_t* __restrict__ g0,
+                                                   const uint64_t* __restrict__ boff, uint32_t lwords,
+                                                   const uint64_t* __restrict__ tnumel, int T, double density,
+                                                   uint32_t* __restrict__ left)
+{
+    __shared__ __align__(16) uint32_t h[kDigBins];
+    __shared__ uint32_t s_bin, s_rank, s_cnt, s_ok;
+    const size_t q = blockIdx.x;
+    if (state[q].z != 0u)
+        return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int t = (int)(q % (size_t)T);
+    const uint64_t n = tnumel[t];
+    const double kk = ceil(density * (double)n);
+    const uint32_t k = (uint32_t)((kk >= (double)n) ? n : (uint64_t)kk);
+    const uint4 b = br[q], ct = cnt[q];
+    const uint32_t nl = ct.z;
+    const uint32_t* __restrict__ L = list + tt_list_at((int)(q / (size_t)T), lwords, (uint32_t)t, boff[g0[t]]);
+    if (tid < kScanBins)
+        h[tid] = hist[q * kDigBins + (size_t)tid];
+    __syncthreads();
+    if (tid < 64) {
+        Cut c{0u, 0u, 0u, 0u, 0u, 0u};
+        if (k > ct.y && nl <= tt_list_cap(n))
+            c = wave_find_from_top(h, kScanBins - 1, k - ct.y, lane);
+        if (tid == 0) {
+            s_ok = c.found;
+            s_bin = c.bin;
+            s_rank = c.rank;
+            s_cnt = c.count;
+        }
+    }
+    __syncthreads();
+    if (s_ok == 0u) {  // outside the bracket, or the list overflowed
+        if (tid == 0)
+            atomicAdd(left, 1u);
+        return;
+    }
+    uint32_t sb = b.z, pref = (b.x >> b.z) + s_bin, rank = s_rank;
+    bool first = true;
+    while (sb != 0u) {
+        const uint32_t wd = min(sb, 11u), up = sb;
+        sb -= wd;
+        __syncthreads();
+        for (int x = tid; x < kDigBins; x += kPick)
+            h[x] = 0u;
+        if (tid == 0)
+            s_cnt = 0u;
+        __syncthreads();
+        const uint32_t dm = (1u << wd) - 1u;
+        uint32_t mine = 0u;
+        for (uint32_t a = (uint32_t)tid; a < nl; a += 4u * kPick) {
+            uint32_t m[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                m[u] = a + (uint32_t)(u * kPick) < nl ? L[a + (uint32_t)(u * kPick)] : 0xffffffffu;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if ((m[u] >> up) == pref) {  // the filler's top bit is set in no prefix
+                    ++mine;
+                    atomicAdd(&h[(m[u] >> sb) & dm], 1u);
+                }
+            }
+        }
+        if (mine != 0u)
+            atomicAdd(&s_cnt, mine);
+        __syncthreads();
+        if (first && s_cnt < rank) {  // the bin's rank-th largest is its floor
+            pref <<= up;
+            sb = 0u;
+            break;
+        }
+        first = false;
+        if (tid < 64) {
+            const Cut c = wave_find_from_top(h, (int)dm, rank, lane);
+            if (tid == 0) {
+                s_ok = c.found;
+                s_bin = c.bin;
+                s_rank = c.rank;
+            }
+        }
+        __syncthreads();
+        if (s_ok == 0u) {  // cannot happen: the list holds the rank-th largest
+            if (tid == 0)
+                atomicAdd(left, 1u);
+            return;
+        }
+        pref = (pref << wd) | s_bin;
+        rank = s_rank;
+    }
+    if (tid == 0)
+        state[q] = make_uint4(pref, 0u, 1u, pref);
+}
+
 __global__ __launch_bounds__(kTT) void k_tt_expand(const uint4* __restrict__ state,
                                                     const uint32_t* __restrict__ tensor, int64_t G, int K, int T,
                                                     uint32_t* __restrict__ tau)
@@ -236,27 +696,75 @@ __global__ __launch_bounds__(kTT) void k_tt_expand(const uint4* __restrict__ sta
 
 }  // namespace
 
+// Words of one expert's lists over n_tensors tensors of elems elements.
+uint64_t ties_tensor_list_words(uint64_t n_tensors, uint64_t elems)
+{
+    return n_tensors * kSmallTensor + elems / 128u + 1u;
+}
+
 hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const ExpertPtrs& ex, int K,
                               const uint32_t* mask, double density, uint32_t* tau, uint32_t* hist, uint4* state,
-                              hipStream_t s, bool delta, bool force_no_cut)
+                              uint32_t* list, hipStream_t s, bool delta, bool force_no_cut)
 {
     if (bt.G == 0)
         return hipSuccess;
     const int T = (int)bt.n_tensors;
     const int64_t pairs = (int64_t)K * T;
     const int64_t nh = pairs * kDigBins;
-    // the state words and, after them, the error word start at zero
+    // the state words, after them the error and left-over words, and the
+    // bracket route's counters start at zero
+    uint4 *br = state + 2 * pairs + 1, *cnt = state + pairs + 1;
     uint32_t* err = reinterpret_cast<uint32_t*>(state + pairs);
-    hipLaunchKernelGGL(k_tt_zero, dim3((unsigned)std::min<int64_t>((pairs * 4 + 4 + kTT - 1) / kTT, 1024)), dim3(kTT),
-                       0, s, reinterpret_cast<uint32_t*>(state), pairs * 4 + 4);
+    uint32_t* left = err + 1;
+    const bool bracket = list != nullptr && !force_no_cut;
+    const int64_t nz = (2 * pairs + 1) * 4;
+    hipLaunchKernelGGL(k_tt_zero, dim3((unsigned)std::min<int64_t>((nz + kTT - 1) / kTT, 1024)), dim3(kTT), 0, s,
+                       reinterpret_cast<uint32_t*>(state), nz, nullptr);
     const uint32_t n_pairs = (uint32_t)(bt.n_chunks * K), per_xcd = (n_pairs + 7u) / 8u;
     const dim3 hgrid(8u * per_xcd);
+    const dim3 zgrid((unsigned)std::min<int64_t>((nh + kTT - 1) / kTT, 2048));
+    const dim3 pgrid((unsigned)((pairs + 3) / 4));
+    if (bracket) {
+        hipLaunchKernelGGL(k_tt_zero, zgrid, dim3(kTT), 0, s, hist, nh, nullptr);
+        const uint32_t n_runs = (uint32_t)bt.n_chunks;
+        const dim3 sgrid((n_runs + kSampleRuns - 1) / kSampleRuns * (uint32_t)K);
+        const uint32_t v = bt.dtype == 0 ? 4u : 8u;
+        const uint32_t segc = std::max<uint32_t>(1u, (uint32_t)bt.block_elems / v / kSampleShare);
+        const uint32_t lwords = (uint32_t)bt.tt_words;
+        auto sample = [&](auto kern) {
+            hipLaunchKernelGGL(kern, sgrid, dim3(kTT), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask,
+                               n_runs, T, segc, state, br, hist, cnt);
+        };
+        auto scan = [&](auto kern) {
+            hipLaunchKernelGGL(kern, hgrid, dim3(kTT), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask, state,
+                               br, T, hist, cnt, list, bt.d_g0, bt.d_tnumel, lwords, n_pairs, per_xcd);
+        };
+        if (bt.dtype == 0)
+            delta ? sample(k_tt_sample<0, true, 0>) : sample(k_tt_sample<0, false, 0>);
+        else
+            delta ? sample(k_tt_sample<1, true, 0>) : sample(k_tt_sample<1, false, 0>);
+        hipLaunchKernelGGL(k_tt_bracket<0>, pgrid, dim3(kTT), 0, s, state, br, cnt, hist, bt.d_tnumel, K, T, density);
+        if (bt.dtype == 0)
+            delta ? sample(k_tt_sample<0, true, 1>) : sample(k_tt_sample<0, false, 1>);
+        else
+            delta ? sample(k_tt_sample<1, true, 1>) : sample(k_tt_sample<1, false, 1>);
+        hipLaunchKernelGGL(k_tt_bracket<1>, pgrid, dim3(kTT), 0, s, state, br, cnt, hist, bt.d_tnumel, K, T, density);
+        if (bt.dtype == 0)
+            delta ? scan(k_tt_scan<0, true>) : scan(k_tt_scan<0, false>);
+        else
+            delta ? scan(k_tt_scan<1, true>) : scan(k_tt_scan<1, false>);
+        hipLaunchKernelGGL(k_tt_pick, dim3((unsigned)pairs), dim3(kPick), 0, s, state, br, cnt, hist, list,
+                           bt.d_g0, bt.d_off, lwords, bt.d_tnumel, T, density, left);
+    }
+    // the radix passes: over everything, or over the pairs the bracket route
+    // left (a grid that fills the chip twice, so that empty passes end soon)
+    const uint32_t* go_left = bracket ? left : nullptr;
+    const dim3 rgrid(bracket ? std::min(8u * per_xcd, 2048u) : 8u * per_xcd);
     for (int pass = 0; pass < 3; ++pass) {
-        hipLaunchKernelGGL(k_tt_zero, dim3((unsigned)std::min<int64_t>((nh + kTT - 1) / kTT, 2048)), dim3(kTT), 0, s,
-                           hist, nh);
+        hipLaunchKernelGGL(k_tt_zero, zgrid, dim3(kTT), 0, s, hist, nh, go_left);
         auto go = [&](auto kern, int nth) {
-            hipLaunchKernelGGL(kern, hgrid, dim3(nth), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask, state,
-                               T, pass, hist, n_pairs, per_xcd);
+            hipLaunchKernelGGL(kern, rgrid, dim3(nth), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask, state,
+                               T, pass, hist, n_pairs, per_xcd, go_left);
         };
         if (pass == 0) {
             if (bt.dtype == 0)
@@ -269,8 +777,8 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
             else
                 delta ? go(k_tt_hist<1, true, kTH, kCop>, kTH) : go(k_tt_hist<1, false, kTH, kCop>, kTH);
         }
-        hipLaunchKernelGGL(k_tt_resolve, dim3((unsigned)((pairs + 3) / 4)), dim3(kTT), 0, s, state, hist,
-                           bt.d_tnumel, K, T, density, pass, err, force_no_cut ? 1 : 0);
+        hipLaunchKernelGGL(k_tt_resolve, pgrid, dim3(kTT), 0, s, state, hist, bt.d_tnumel, K, T, density, pass, err,
+                           force_no_cut ? 1 : 0, go_left);
     }
     hipLaunchKernelGGL(k_tt_expand, dim3((unsigned)((bt.G * K + kTT - 1) / kTT)), dim3(kTT), 0, s, state,
                        bt.d_tensor, bt.G, K, T, tau);

@@ -52,6 +52,8 @@ struct BlockTable {
     int64_t n_chunks = 0;
     uint4* d_chunk = nullptr;
     uint64_t* d_tnumel = nullptr;  // elements per tensor [n_tensors]
+    // words of tensor-scope TIES's lists of one expert (0: the layout takes the radix route)
+    uint64_t tt_words = 0;
     // the tensor-level plan (no block catalog): elements per tensor as u32
     // (valid when every tensor has fewer than 2^32), their distinct values,
     // and the first block of every tensor [n_tensors + 1]
@@ -127,13 +129,16 @@ hipError_t launch_plan(const BlockTable& bt, PlanScratch& ps, int K, const float
 
 // TIES thresholds at tensor scope (k_tensor_ties.hip): per unit (g, i) the
 // k-th largest |d| of tensor(g)'s zero-completed masked deltas of expert i.
-// hist: device uint32[K * n_tensors * 2048], state: device uint4[K * n_tensors
-// + 1]; the word after the pairs' states is set to nonzero if a selection
-// found no cut (an internal error).  force_no_cut: a test hook that sends
+// hist: device uint32[K * n_tensors * 2048], state: device uint4[3 * K *
+// n_tensors + 1]; the word after the first K * n_tensors entries is set to
+// nonzero if a selection found no cut (an internal error).  list: K *
+// bt.tt_words device words for the route that reads the blocks once, or null
+// for the radix route.  force_no_cut: a test hook that sends
 // the first pair down that error path (the kernels still finish normally).
 hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const ExpertPtrs& ex, int K,
                               const uint32_t* mask, double density, uint32_t* tau, uint32_t* hist, uint4* state,
-                              hipStream_t s, bool delta, bool force_no_cut);
+                              uint32_t* list, hipStream_t s, bool delta, bool force_no_cut);
+uint64_t ties_tensor_list_words(uint64_t n_tensors, uint64_t elems);
 
 // ---------------------------------------------------------------- LoRA source (k_lora.hip)
 constexpr int kMaxLoraRank = 64;

@@ -1,0 +1,77 @@
+"""Tensor-scope TIES thresholds on the device against the CPU oracle, bit for
+bit, where the one-pass route can go wrong: tensor sizes around its list-all
+limit and its slices, repeated values, samples that mislead, lists that
+overflow, blocks too long for it, and a workspace without room for its lists."""
+
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import to_dev
+from tests.test_gpu_parity import _say, mp  # noqa: F401  (mp: the module fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(mp, dtype, be, numel, base, exps, mask, density, delta=False):  # noqa: F811
+    import torch
+    L = mp.Layout(numel, be, mp.MP_F32 if dtype == "f32" else mp.MP_BF16)
+    blocks = oracle.Blocks(numel, be)
+    K = len(exps)
+    tau = torch.full((blocks.G * K,), -1, dtype=torch.int32, device="cuda")
+    m = torch.from_numpy(mask.view(np.int32)).to("cuda")
+    mp.mp_ties_tensor_thresholds(L, to_dev(base, dtype), [to_dev(e, dtype) for e in exps], m, density, tau, delta=delta)
+    want = oracle.expand_tensor_thresholds(
+        blocks, oracle.ties_tensor_thresholds(blocks, dtype, base, exps, mask, density, delta=delta))
+    assert np.array_equal(tau.cpu().numpy().view(np.uint32), want), f"{dtype} be={be} density={density}"
+
+
+def _family(dtype, numel, be, seed):
+    """Six experts: normal, a few repeated values, mostly zero, all equal,
+    large only in the first sixteenth of every 16 blocks (the sampled slices see
+    far too many), and magnitudes that share their top 16 bits."""
+    P = sum(numel)
+    rng = np.random.default_rng(seed)
+    sign = rng.choice([-1.0, 1.0], P)
+    pos = np.arange(P)
+    seen = (pos % be) // max(1, be // 16) == (pos // be) % 16
+    deltas = [rng.normal(0.0, 1e-3, P), rng.choice([0.5, 1.0, 1.5], P) * 2.0 ** -10 * sign,
+              np.where(rng.random(P) < 0.05, rng.normal(0.0, 1e-3, P), 0.0), np.full(P, 2.0 ** -9),
+              np.where(seen, 1.0, 1e-3) * rng.normal(0.0, 1.0, P),
+              1e-3 * (1.0 + rng.integers(0, 1 << 14, P) * 2.0 ** -23) * sign]
+    deltas = [d.astype(np.float32) for d in deltas]
+    if dtype == "f32":  # a zero base keeps the fp32 patterns
+        return np.zeros(P, np.float32), deltas
+    base = oracle.round_bf16(rng.normal(0.0, 0.02, P).astype(np.float32))
+    x0 = (base.astype(np.uint32) << 16).view(np.float32)
+    return base, [oracle.round_bf16(x0 + d) for d in deltas]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("be", [64, 520, 4096, 8192])
+def test_tensor_thresholds_edges(mp, dtype, be):  # noqa: F811
+    numel = [8, 8184, 8192, 8200, 17 * be + 8, 300_000, 16 * be, 40 * be - 8]
+    base, exps = _family(dtype, numel, be, seed=be)
+    K, G = len(exps), oracle.Blocks(numel, be).G
+    rng = np.random.default_rng(be)
+    some = (rng.integers(0, 1 << K, G) & 0x3f).astype(np.uint32)
+    for mask in (some, np.full(G, (1 << K) - 1, np.uint32), np.zeros(G, np.uint32)):
+        for density in (0.0, 1e-6, 0.01, 0.2, 0.5, 0.9, 1.0):
+            _say(f"case {dtype} block {be} density {density}")
+            _check(mp, dtype, be, numel, base, exps, mask, density)
+    _check(mp, dtype, be, numel, base, exps, some, 0.2, delta=True)
+
+
+def test_tensor_thresholds_without_lists(mp):  # noqa: F811
+    """A workspace limit that leaves no room for the lists: the same thresholds."""
+    be, numel = 4096, [300_000, 8192]
+    base, exps = _family("bf16", numel, be, seed=1)
+    mask = np.full(oracle.Blocks(numel, be).G, 63, np.uint32)
+    _check(mp, "bf16", be, numel, base, exps, mask, 0.2)
+    held = mp.mp_workspace_bytes()
+    try:
+        mp.mp_set_workspace_limit(held)
+        _check(mp, "bf16", be, numel[::-1], base, exps, mask, 0.2)  # its table takes the lists' place
+    finally:
+        mp.mp_set_workspace_limit(0)
+    _check(mp, "bf16", be, numel, base, exps, mask, 0.3)
