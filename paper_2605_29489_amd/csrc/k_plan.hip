@@ -9,21 +9,26 @@
 //
 // So no full sort is needed:
 //   round r:  find the cut key of the current candidate set by a
-//             cost-weighted MSD radix select (8 digit passes of 8 bits;
-//             each pass builds a cost histogram of the candidates that match
-//             the resolved key prefix, in LDS, then one wave scans it);
+//             cost-weighted MSD radix select (each pass builds a cost
+//             histogram of the candidates that match the resolved key prefix
+//             and finds the bin where the running cost passes the budget);
 //             select every candidate below the cut; the candidates above the
-//             cut that are cheaper than c_p form the next round's set (a
-//             compact uid list), with the remaining budget.
+//             cut that still fit what is left form the next round's set.
 //   A round whose candidates all fit selects them all and ends the plan.
 // Each round strictly lowers the cost bound, so the number of rounds is at
 // most the number of distinct block lengths of the layout.
 //
-// Round 0 (all units) runs as one launch per digit pass over the whole
-// device; the later rounds, whose candidate lists are short, run together
-// in one single-workgroup launch.  All control state lives on the device
-// (PlanCtl); the host enqueues a fixed kernel sequence and kernels that are
-// no longer needed return at once.
+// Up to kOneMax units the whole plan is one single-workgroup launch
+// (k_plan_one): keys and costs stay in registers.  Above that, round 0 (all
+// units) runs over the whole device: digits of 11 bits, three passes for the
+// score and one or two for the uid, then one pass that marks the mask; the
+// later rounds, whose candidate lists are short (units of short blocks only),
+// run together in k_plan_one, which also closes the digest and the stats.  All
+// control state lives on the device (PlanCtl); the host enqueues a fixed kernel
+// sequence and kernels that are no longer needed return at once.  What bounds
+// it is launches and dependent passes, not bytes: at 1.5M units, eight 8-bit
+// passes of one thread per block took 8.5 us each, the later rounds (reloading
+// their list in each pass) 30 us and fourteen launches in all 143 us.
 #include "device_common.h"
 #include "mp_internal.h"
 
@@ -31,18 +36,18 @@ namespace mp {
 
 // Workgroups of the round-0 kernels (at most).  Each workgroup ends a pass
 // with device-scope atomic adds into the shared histogram, which serialize
-// per address; 512 workgroups measured fastest (2048: the atomics dominate
-// the first digit pass; 256: no faster).
+// per address.
 constexpr int kPlanGrid = 512;
+constexpr int kHistGrid = 256, kHistT = 512;  // the digit passes: one workgroup per CU
+constexpr int kPlanBins = 2048;               // 11-bit digits
 
 struct PlanCtl {
     unsigned long long brem[9];       // remaining budget before resolving digit d
     unsigned long long prefix[9];     // key prefix with digits < d resolved
-    unsigned long long hist[3][256];  // rotating cost histograms of digit passes
+    unsigned long long hist[3][kPlanBins];  // rotating cost histograms of digit passes
     unsigned long long total0;        // candidate cost of the round (all-fit case)
     unsigned long long sel_cost;
     unsigned long long sel_count;
-    unsigned long long digest_acc;
     unsigned long long stats[7];      // budget, cost, full, n_sel, n_units, digest, error
     unsigned int all_fit;
     unsigned int done;
@@ -136,18 +141,10 @@ __device__ inline void resolve_digit(const unsigned long long* h, unsigned long 
     *total_out = total;
 }
 
-struct CandSrc {
-    // round 0: implicit (all units, one thread per block handling its K units)
-    // later rounds: explicit list of uids
-    const uint32_t* list;  // null in round 0
-    const unsigned int* list_n;
-    unsigned int cap;
-};
-
-__global__ __launch_bounds__(kT) void k_plan_init(PlanCtl* ctl, unsigned long long budget)
+__global__ __launch_bounds__(1024) void k_plan_init(PlanCtl* ctl, unsigned long long budget)
 {
     const int t = threadIdx.x;
-    for (int q = t; q < 3 * 256; q += kT)
+    for (int q = t; q < 3 * kPlanBins; q += 1024)
         (&ctl->hist[0][0])[q] = 0ull;
     if (t == 0) {
         ctl->brem[0] = budget;
@@ -155,7 +152,6 @@ __global__ __launch_bounds__(kT) void k_plan_init(PlanCtl* ctl, unsigned long lo
         ctl->total0 = 0ull;
         ctl->sel_cost = 0ull;
         ctl->sel_count = 0ull;
-        ctl->digest_acc = 0ull;
         ctl->all_fit = 0u;
         ctl->done = 0u;
         ctl->list_n[0] = 0u;
@@ -164,178 +160,260 @@ __global__ __launch_bounds__(kT) void k_plan_init(PlanCtl* ctl, unsigned long lo
     }
 }
 
-// Digit pass d of the current round: resolve digit d-1 (every workgroup does
-// it redundantly from the previous histogram; workgroup 0 publishes it), then
-// histogram digit d of the candidates matching the resolved prefix.
-__global__ __launch_bounds__(kT) void k_plan_hist(PlanCtl* ctl, int d, const float* __restrict__ sumsq,
-                                                  Coeffs w, uint32_t flags, int K,
-                                                  const uint32_t* __restrict__ blen, uint32_t esize, int64_t G,
-                                                  CandSrc src)
+// Exclusive prefix sum of x over the NT threads of a workgroup, and the
+// total.  All threads call it; sw holds NT / 64 words.
+template <int NT>
+__device__ inline unsigned long long block_excl_sum(unsigned long long x, unsigned long long* sw,
+                                                    unsigned long long* total)
 {
-    __shared__ unsigned long long lh[256];
-    __shared__ unsigned long long s_prefix;
-    __shared__ int s_stop;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned long long incl = x;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long y = __shfl_up(incl, (unsigned)off);
+        if (lane >= off)
+            incl += y;
+    }
+    __syncthreads();  // sw is free
+    if (lane == 63)
+        sw[wave] = incl;
+    __syncthreads();
+    unsigned long long before = 0ull, all = 0ull;
+#pragma unroll
+    for (int v = 0; v < NT / 64; ++v) {
+        const unsigned long long y = sw[v];
+        before += v < wave ? y : 0ull;
+        all += y;
+    }
+    *total = all;
+    return before + incl - x;
+}
+
+// Resolution of one digit by a kHistT-thread workgroup: h[kPlanBins] holds
+// the cost of the matching candidates per digit value.  found: some v is the
+// smallest with sum_{v' <= v} h[v'] > brem; below is the cost under it, total
+// the whole histogram's.  Results through LDS; ends with a barrier.
+struct Digit {
+    unsigned long long below, total;
+    int v;  // -1: the total fits
+};
+__device__ inline void block_resolve(const unsigned long long* __restrict__ h, unsigned long long brem,
+                                     unsigned long long* sw, Digit* out)
+{
+    constexpr int per = kPlanBins / kHistT;
+    const int t = threadIdx.x;
+    unsigned long long c[per], run = 0ull;
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+        c[q] = h[t * per + q];
+        run += c[q];
+    }
+    unsigned long long total;
+    unsigned long long at = block_excl_sum<kHistT>(run, sw, &total);
+    if (t == 0) {
+        out->total = total;
+        if (total <= brem)
+            out->v = -1;
+    }
+    if (at <= brem && at + run > brem) {  // exactly one thread, if the total does not fit
+        int v = t * per;
+#pragma unroll
+        for (int q = 0; q < per - 1; ++q) {
+            if (v == t * per + q && at + c[q] <= brem) {
+                at += c[q];
+                ++v;
+            }
+        }
+        out->v = v;
+        out->below = at;
+    }
+    __syncthreads();
+}
+
+// Digit pass d of round 0 (key bits sh .. sh + wd - 1; the pass before took
+// those from psh up): resolve the pass before (every workgroup does it
+// redundantly from its histogram; workgroup 0 publishes it), then histogram
+// this digit of the units matching the resolved prefix.  One thread per unit,
+// four units' loads in flight.
+__global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int sh, int wd, int psh,
+                                                      const float* __restrict__ sumsq, Coeffs w, uint32_t flags,
+                                                      int K, const uint32_t* __restrict__ blen, uint32_t esize,
+                                                      int64_t G)
+{
+    __shared__ unsigned long long lh[kPlanBins];
+    __shared__ unsigned long long sw[kHistT / 64];
+    __shared__ Digit dg;
+    __shared__ float s_w[kMaxK];
     if (ctl->done || ctl->all_fit)
         return;
     const int t = threadIdx.x;
-    const int lane = t & 63;
-    if (t < 64) {
-        unsigned long long prefix = 0ull, brem = ctl->brem[0];
-        int stop = 0;
-        if (d > 0) {
-            int v;
-            unsigned long long below, total;
-            resolve_digit(ctl->hist[(d - 1) % 3], ctl->brem[d - 1], lane, &v, &below, &total);
-            if (v < 0) {  // digit 0: every candidate fits; later digits: cannot happen
-                stop = 1;
-                if (blockIdx.x == 0 && lane == 0) {
-                    if (d == 1) {
-                        ctl->total0 = total;
-                        ctl->all_fit = 1u;
-                    } else {
-                        ctl->error = 3u;
-                    }
-                }
-            } else {
-                prefix = ctl->prefix[d - 1] | ((unsigned long long)v << (56 - 8 * (d - 1)));
-                brem = ctl->brem[d - 1] - below;
-                if (blockIdx.x == 0 && lane == 0) {
-                    ctl->prefix[d] = prefix;
-                    ctl->brem[d] = brem;
+    if (t < K)
+        s_w[t] = w.v[t];
+#pragma unroll
+    for (int q = 0; q < kPlanBins / kHistT; ++q)
+        lh[q * kHistT + t] = 0ull;
+    unsigned long long prefix = 0ull;
+    if (d > 0) {
+        const unsigned long long brem = ctl->brem[d - 1];
+        block_resolve(ctl->hist[(d - 1) % 3], brem, sw, &dg);
+        if (dg.v < 0) {  // digit 0: every candidate fits; later digits: cannot happen
+            if (blockIdx.x == 0 && t == 0) {
+                if (d == 1) {
+                    ctl->total0 = dg.total;
+                    ctl->all_fit = 1u;
+                } else {
+                    ctl->error = 3u;
                 }
             }
+            return;
         }
-        if (lane == 0) {
-            s_prefix = prefix;
-            s_stop = stop;
-        }
-    }
-    if (blockIdx.x == 0) {
-        unsigned long long* hn = ctl->hist[(d + 1) % 3];
-        for (int q = t; q < 256; q += kT)
-            hn[q] = 0ull;
-    }
-    lh[t] = 0ull;
-    __syncthreads();
-    if (s_stop)
-        return;
-    const unsigned long long prefix = s_prefix;
-    const int hi_shift = 64 - 8 * d;  // bits above the digit (d > 0)
-    const int dg_shift = 56 - 8 * d;
-    if (src.list == nullptr) {
-        for (int64_t g = (int64_t)blockIdx.x * kT + t; g < G; g += (int64_t)gridDim.x * kT) {
-            const unsigned long long c = (unsigned long long)blen[g] * esize;
-            for (int i = 0; i < K; ++i) {
-                const uint32_t uid = (uint32_t)(g * K + i);
-                const float S = plan_stat(sumsq, uid);
-                if (plan_skips(S, c, flags))
-                    continue;
-                const unsigned long long key = unit_key(S, w.v[i], uid, c, flags);
-                if (d == 0 || ((key ^ prefix) >> hi_shift) == 0)
-                    atomicAdd(&lh[(key >> dg_shift) & 255u], c);
+        prefix = ctl->prefix[d - 1] | ((unsigned long long)dg.v << psh);
+        if (blockIdx.x == 0) {
+            if (t == 0) {
+                ctl->prefix[d] = prefix;
+                ctl->brem[d] = brem - dg.below;
             }
+            unsigned long long* hn = ctl->hist[(d + 1) % 3];
+            for (int q = t; q < kPlanBins; q += kHistT)
+                hn[q] = 0ull;
         }
     } else {
-        // listed units are candidates already
-        const unsigned int n = min(*src.list_n, src.cap);
-        for (unsigned int q = blockIdx.x * kT + t; q < n; q += gridDim.x * kT) {
-            const uint32_t uid = src.list[q];
-            const uint32_t g = uid / (uint32_t)K, i = uid % (uint32_t)K;
-            const unsigned long long c = (unsigned long long)blen[g] * esize;
-            const unsigned long long key = unit_key(plan_stat(sumsq, uid), w.v[i], uid, c, flags);
-            if (d == 0 || ((key ^ prefix) >> hi_shift) == 0)
-                atomicAdd(&lh[(key >> dg_shift) & 255u], c);
+        __syncthreads();
+    }
+    const int64_t n = G * K, step = (int64_t)gridDim.x * kHistT;
+    const unsigned long long dm = (1ull << wd) - 1ull;
+    for (int64_t u0 = (int64_t)blockIdx.x * kHistT + t; u0 < n; u0 += 4 * step) {
+        float S[4];
+        uint32_t len[4], ex[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t u = u0 + q * step;
+            const uint32_t uid = (uint32_t)(u < n ? u : 0);
+            const uint32_t g = uid / (uint32_t)K;
+            ex[q] = uid - g * (uint32_t)K;
+            S[q] = plan_stat(sumsq, uid);
+            len[q] = blen[g];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t u = u0 + q * step;
+            const unsigned long long c = (unsigned long long)len[q] * esize;
+            if (u >= n || plan_skips(S[q], c, flags))
+                continue;
+            const unsigned long long key = unit_key(S[q], s_w[ex[q]], (uint32_t)u, c, flags);
+            if (d == 0 || ((key ^ prefix) >> (sh + wd)) == 0)
+                atomicAdd(&lh[(key >> sh) & dm], c);
         }
     }
     __syncthreads();
-    if (lh[t])
-        atomicAdd(&ctl->hist[d % 3][t], lh[t]);
+    unsigned long long* out = ctl->hist[d % 3];
+#pragma unroll
+    for (int q = 0; q < kPlanBins / kHistT; ++q) {
+        const unsigned long long v = lh[q * kHistT + t];
+        if (v)
+            atomicAdd(&out[q * kHistT + t], v);
+    }
 }
 
-// After digit pass 7: resolve the last digit (the cut key p), select the
-// candidates below it, and collect the next round's candidates (above p,
-// cheaper than c_p).  In the all-fit case select every candidate.
-__global__ __launch_bounds__(kT) void k_plan_mark(PlanCtl* ctl, const float* __restrict__ sumsq, Coeffs w,
-                                                  uint32_t flags, int K, const uint32_t* __restrict__ blen,
-                                                  uint32_t esize, int64_t G, CandSrc src,
-                                                  uint32_t* __restrict__ mask, uint32_t* __restrict__ next,
-                                                  unsigned int* __restrict__ next_n, unsigned int next_cap)
+// After the last digit pass d (key bits from sh up): resolve its digit; the
+// cut key p is among the at most 2^open uids (kMarkUids at most) that share all
+// bits above (open = sh, or fewer where the uids need no more), found by a prefix sum of their costs in uid order.  Then mark:
+// select the candidates below the cut and list the next round's (above p, and
+// not dearer than what is left).  In the all-fit case select every candidate.
+// Per workgroup: the selected cost and count, and the mask's digest terms.
+constexpr int kMarkBits = 12, kMarkUids = 1 << kMarkBits;
+__global__ __launch_bounds__(kHistT) void k_plan_mark(PlanCtl* ctl, int d, int sh, int open, const float* __restrict__ sumsq,
+                                                      Coeffs w, uint32_t flags, int K,
+                                                      const uint32_t* __restrict__ blen, uint32_t esize, int64_t G,
+                                                      uint32_t* __restrict__ mask, uint32_t* __restrict__ next,
+                                                      unsigned int* __restrict__ next_n, unsigned int next_cap)
 {
-    __shared__ unsigned long long s_keyp, s_cp;
-    __shared__ int s_all;
-    __shared__ unsigned long long s_cost[4], s_cnt[4];
-    if (ctl->done)
-        return;
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6;
-    if (t < 64) {
-        int all = (int)ctl->all_fit;
-        unsigned long long keyp = 0ull, cp = 0ull;
-        if (!all) {
-            int v;
-            unsigned long long below, total;
-            resolve_digit(ctl->hist[7 % 3], ctl->brem[7], lane, &v, &below, &total);
-            keyp = ctl->prefix[7] | (unsigned long long)(unsigned)(v < 0 ? 0 : v);
-            const uint32_t gp = (uint32_t)keyp / (uint32_t)K;
-            if (v < 0 || (int64_t)gp >= G) {  // cannot happen: the cut is a real unit
-                if (lane == 0)
-                    ctl->error = 1u;
-                keyp = 0ull;  // select nothing more this round
-                cp = 0ull;
-            } else {
-                cp = (unsigned long long)blen[gp] * esize;
-            }
-            if (blockIdx.x == 0 && lane == 0) {
-                ctl->prefix[8] = keyp;
-                ctl->brem[8] = ctl->brem[7] - below;
-            }
+    __shared__ unsigned long long sw[kHistT / 64];
+    __shared__ Digit dg;
+    __shared__ unsigned long long s_keyp, s_rem;
+    __shared__ unsigned long long s_sum[3][kHistT / 64];
+    __shared__ float s_w[kMaxK];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (t < K)
+        s_w[t] = w.v[t];
+    const bool all = ctl->all_fit != 0u;
+    unsigned long long keyp = 0ull, rem = 0ull;
+    bool ok = true;
+    if (!all) {
+        if (t == 0) {
+            s_keyp = ~0ull;
+            s_rem = 0ull;
         }
-        if (lane == 0) {
-            s_keyp = keyp;
-            s_cp = cp;
-            s_all = all;
-        }
-    }
-    __syncthreads();
-    const unsigned long long keyp = s_keyp, cp = s_cp;
-    const int all = s_all;
-    unsigned long long my_cost = 0ull, my_cnt = 0ull;
-    if (src.list == nullptr) {
-        for (int64_t g = (int64_t)blockIdx.x * kT + t; g < G; g += (int64_t)gridDim.x * kT) {
-            const unsigned long long c = (unsigned long long)blen[g] * esize;
-            uint32_t word = 0u;
-            for (int i = 0; i < K; ++i) {
-                const uint32_t uid = (uint32_t)(g * K + i);
-                const float S = plan_stat(sumsq, uid);
-                if (plan_skips(S, c, flags))
-                    continue;
-                const unsigned long long key = unit_key(S, w.v[i], uid, c, flags);
-                if (all || key < keyp) {
-                    word |= 1u << i;
-                    my_cost += c;
-                    my_cnt += 1;
-                } else if (key > keyp && c < cp) {
-                    const unsigned int slot = atomicAdd(next_n, 1u);
-                    if (slot < next_cap)
-                        next[slot] = uid;
-                    else
-                        ctl->error = 2u;
+        block_resolve(ctl->hist[d % 3], ctl->brem[d], sw, &dg);
+        ok = dg.v >= 0;
+        if (ok) {
+            const unsigned long long pre = ctl->prefix[d] | ((unsigned long long)dg.v << sh);
+            const unsigned long long left = ctl->brem[d] - dg.below;
+            constexpr int per = kMarkUids / kHistT;
+            unsigned long long c[per], run = 0ull;
+            const int64_t n = G * K;
+            const int m = 1 << open, per_t = (m + kHistT - 1) / kHistT;
+#pragma unroll
+            for (int q = 0; q < per; ++q) {
+                c[q] = 0ull;
+                const int j = t * per_t + q;
+                const int64_t u = (int64_t)(uint32_t)pre + j;
+                if (q < per_t && j < m && u < n) {
+                    const uint32_t g = (uint32_t)u / (uint32_t)K;
+                    const unsigned long long cc = (unsigned long long)blen[g] * esize;
+                    const float S = plan_stat(sumsq, (uint32_t)u);
+                    if (!plan_skips(S, cc, flags) &&
+                        unit_key(S, s_w[(uint32_t)u - g * (uint32_t)K], (uint32_t)u, cc, flags) == pre + (unsigned)j)
+                        c[q] = cc;
+                }
+                run += c[q];
+            }
+            unsigned long long total;
+            unsigned long long at = block_excl_sum<kHistT>(run, sw, &total);
+            if (at <= left && at + run > left) {  // exactly one thread
+                bool found = false;
+#pragma unroll
+                for (int q = 0; q < per; ++q) {
+                    if (!found && at + c[q] > left) {
+                        found = true;
+                        s_keyp = pre + (unsigned)(t * per_t + q);
+                        s_rem = left - at;
+                    }
+                    at += found ? 0ull : c[q];
                 }
             }
-            mask[g] = word;
+        }
+        __syncthreads();
+        keyp = s_keyp;
+        rem = s_rem;
+        if (keyp == ~0ull)
+            ok = false;  // cannot happen: the cut is a real unit (a full uid with a NaN-free score is not all ones)
+        if (!ok)
+            keyp = 0ull;  // select nothing
+        if (blockIdx.x == 0 && t == 0) {
+            if (!ok)
+                ctl->error = 1u;
+            ctl->prefix[8] = keyp;
+            ctl->brem[8] = rem;
         }
     } else {
-        const unsigned int n = min(*src.list_n, src.cap);
-        for (unsigned int q = blockIdx.x * kT + t; q < n; q += gridDim.x * kT) {
-            const uint32_t uid = src.list[q];
-            const uint32_t g = uid / (uint32_t)K, i = uid % (uint32_t)K;
-            const unsigned long long c = (unsigned long long)blen[g] * esize;
-            const unsigned long long key = unit_key(plan_stat(sumsq, uid), w.v[i], uid, c, flags);
+        __syncthreads();
+    }
+    unsigned long long my_cost = 0ull, my_cnt = 0ull, my_dig = 0ull;
+    for (int64_t g = (int64_t)blockIdx.x * kHistT + t; g < G; g += (int64_t)gridDim.x * kHistT) {
+        const unsigned long long c = (unsigned long long)blen[g] * esize;
+        uint32_t word = 0u;
+        for (int i = 0; i < K; ++i) {
+            const uint32_t uid = (uint32_t)(g * K + i);
+            const float S = plan_stat(sumsq, uid);
+            if (plan_skips(S, c, flags))
+                continue;
+            const unsigned long long key = unit_key(S, s_w[i], uid, c, flags);
             if (all || key < keyp) {
-                atomicOr(&mask[g], 1u << i);
+                word |= 1u << i;
                 my_cost += c;
                 my_cnt += 1;
-            } else if (key > keyp && c < cp) {
+            } else if (key > keyp && c <= rem) {
                 const unsigned int slot = atomicAdd(next_n, 1u);
                 if (slot < next_cap)
                     next[slot] = uid;
@@ -343,20 +421,27 @@ __global__ __launch_bounds__(kT) void k_plan_mark(PlanCtl* ctl, const float* __r
                     ctl->error = 2u;
             }
         }
+        mask[g] = word;
+        my_dig += mix64(((unsigned long long)g << 32) | word);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         my_cost += __shfl_xor(my_cost, off);
         my_cnt += __shfl_xor(my_cnt, off);
+        my_dig += __shfl_xor(my_dig, off);
     }
     if (lane == 0) {
-        s_cost[wave] = my_cost;
-        s_cnt[wave] = my_cnt;
+        s_sum[0][wave] = my_cost;
+        s_sum[1][wave] = my_cnt;
+        s_sum[2][wave] = my_dig;
     }
     __syncthreads();
-    if (t == 0) {
-        ctl->part[0][blockIdx.x] = s_cost[0] + s_cost[1] + s_cost[2] + s_cost[3];
-        ctl->part[1][blockIdx.x] = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    if (t < 3) {
+        unsigned long long v = 0ull;
+#pragma unroll
+        for (int q = 0; q < kHistT / 64; ++q)
+            v += s_sum[t][q];
+        ctl->part[t][blockIdx.x] = v;
     }
 }
 
@@ -382,7 +467,7 @@ __device__ inline unsigned long long block_sum_parts(const PlanCtl* ctl, int row
     return s[0] + s[1] + s[2] + s[3];
 }
 
-// Close round r: carry the remaining budget, reset the digit state, and
+// Close round 0: carry the remaining budget and
 // finish the plan when everything fit or no cheaper candidate is left.
 __global__ __launch_bounds__(kT) void k_plan_advance(PlanCtl* ctl, int next_list, int reuse_list, int n_part)
 {
@@ -392,8 +477,6 @@ __global__ __launch_bounds__(kT) void k_plan_advance(PlanCtl* ctl, int next_list
         return;
     const unsigned long long cs = block_sum_parts(ctl, 0, n_part);
     const unsigned long long cn = block_sum_parts(ctl, 1, n_part);
-    for (int q = t; q < 3 * 256; q += kT)
-        (&ctl->hist[0][0])[q] = 0ull;
     if (t != 0)
         return;
     ctl->sel_cost += cs;
@@ -554,6 +637,187 @@ __global__ __launch_bounds__(kT) void k_plan_rest(PlanCtl* ctl, const float* __r
     }
 }
 
+// The plan's rounds in one workgroup with keys and costs in registers (at most
+// kOneMax candidates).  ALL: every unit, from the start (mask and digest from
+// LDS words).  Otherwise the rounds after round 0 over the list that
+// k_plan_mark left; they change the digest word by word.  Per round: drop the
+// candidates dearer than what is left (they can never be taken), take all if
+// they fit, else find the cut digit by digit, stopping as soon as a single
+// candidate matches, take what lies below it and go on with what lies above.
+// Both write the stats: with tensor_level only the selection goes to ctl (the
+// stats are closed over the expanded mask).
+constexpr int kOneT = 1024, kOnePer = 8, kOneMax = kOneT * kOnePer;
+
+template <bool ALL>
+__global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* __restrict__ sumsq, Coeffs w,
+                                                    uint32_t flags, int K, const uint32_t* __restrict__ blen,
+                                                    uint32_t esize, int64_t G, const uint32_t* __restrict__ list,
+                                                    const unsigned int* __restrict__ list_n, unsigned int cap,
+                                                    uint32_t* __restrict__ mask, int n_part,
+                                                    unsigned long long budget, unsigned long long full,
+                                                    unsigned long long n_units, bool tensor_level,
+                                                    unsigned long long* __restrict__ stats)
+{
+    __shared__ unsigned long long lh[256];
+    __shared__ unsigned long long sw[kOneT / 64];
+    __shared__ unsigned long long s_below, s_total, s_key;
+    __shared__ int s_v;
+    __shared__ float s_w[kMaxK];
+    __shared__ uint32_t s_mask[ALL ? kOneMax : 1];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    unsigned long long rem = budget, err = 0ull, cost = 0ull, cnt = 0ull, dig = 0ull;  // this thread's, summed at the end
+    bool rounds = true;
+    uint32_t n;
+    if (ALL) {
+        n = (uint32_t)(G * K);
+        for (int64_t g = t; g < G; g += kOneT)
+            s_mask[g] = 0u;
+    } else {
+        for (int q = t; q < n_part; q += kOneT) {
+            cost += ctl->part[0][q];
+            cnt += ctl->part[1][q];
+            dig += ctl->part[2][q];
+        }
+        const bool all = ctl->all_fit != 0u;
+        err = ctl->error;
+        rem = ctl->brem[8];
+        n = min(*list_n, cap);
+        rounds = !all && err == 0ull && n <= (uint32_t)kOneMax;
+    }
+    if (t < K)
+        s_w[t] = w.v[t];
+    __syncthreads();
+    unsigned long long key[kOnePer], c[kOnePer];
+    uint32_t alive = 0u;
+#pragma unroll
+    for (int q = 0; q < kOnePer; ++q) {
+        const uint32_t j = (uint32_t)(q * kOneT + t);
+        key[q] = 0ull;
+        c[q] = 0ull;
+        if (rounds && j < n) {
+            const uint32_t uid = ALL ? j : list[j];
+            const uint32_t g = uid / (uint32_t)K;
+            const float S = plan_stat(sumsq, uid);
+            c[q] = (unsigned long long)blen[g] * esize;
+            key[q] = unit_key(S, s_w[uid - g * (uint32_t)K], uid, c[q], flags);
+            if (!ALL || !plan_skips(S, c[q], flags))  // listed units are candidates already
+                alive |= 1u << q;
+        }
+    }
+    auto take = [&](int q) {
+        const uint32_t uid = (uint32_t)key[q], g = uid / (uint32_t)K, bit = 1u << (uid - g * (uint32_t)K);
+        cost += c[q];
+        cnt += 1ull;
+        if (ALL) {
+            atomicOr(&s_mask[g], bit);
+        } else {
+            const uint32_t old = atomicOr(&mask[g], bit);
+            dig += mix64(((unsigned long long)g << 32) | (old | bit)) - mix64(((unsigned long long)g << 32) | old);
+        }
+    };
+    for (;;) {
+        unsigned long long mine = 0ull, total;
+#pragma unroll
+        for (int q = 0; q < kOnePer; ++q) {
+            if (((alive >> q) & 1u) && c[q] > rem)
+                alive &= ~(1u << q);
+            mine += ((alive >> q) & 1u) ? c[q] : 0ull;
+        }
+        (void)block_excl_sum<kOneT>(mine, sw, &total);
+        if (total <= rem) {  // everything fits (or nothing is left)
+#pragma unroll
+            for (int q = 0; q < kOnePer; ++q)
+                if ((alive >> q) & 1u)
+                    take(q);
+            break;
+        }
+        unsigned long long prefix = 0ull, brem = rem;
+        bool bad = false;
+        uint32_t match = alive;  // candidates that match the prefix
+        for (int d = 0; d < 8; ++d) {
+            __syncthreads();
+            if (t < 256)
+                lh[t] = 0ull;
+            __syncthreads();
+            const int sh = 56 - 8 * d;
+#pragma unroll
+            for (int q = 0; q < kOnePer; ++q)
+                if ((match >> q) & 1u)
+                    atomicAdd(&lh[(key[q] >> sh) & 255u], c[q]);
+            __syncthreads();
+            if (wave == 0) {
+                int v;
+                unsigned long long below, tot;
+                resolve_digit(lh, brem, lane, &v, &below, &tot);
+                if (lane == 0) {
+                    s_v = v;
+                    s_below = below;
+                }
+            }
+            __syncthreads();
+            if (s_v < 0) {  // cannot happen: the total passes the budget
+                bad = true;
+                break;
+            }
+            brem -= s_below;
+            prefix |= (unsigned long long)s_v << sh;
+#pragma unroll
+            for (int q = 0; q < kOnePer; ++q)
+                if (((match >> q) & 1u) && ((key[q] ^ prefix) >> sh) != 0ull)
+                    match &= ~(1u << q);
+            if (__syncthreads_or(__popc(match) > 1) == 0 && __syncthreads_count(match != 0u) == 1) {
+                // one candidate is left: it is the cut
+#pragma unroll
+                for (int q = 0; q < kOnePer; ++q)
+                    if ((match >> q) & 1u)
+                        s_key = key[q];
+                __syncthreads();
+                prefix = s_key;
+                break;
+            }
+        }
+        if (bad) {
+            err = 3ull;
+            break;
+        }
+#pragma unroll
+        for (int q = 0; q < kOnePer; ++q) {
+            if (((alive >> q) & 1u) && key[q] <= prefix) {
+                if (key[q] < prefix)
+                    take(q);
+                alive &= ~(1u << q);
+            }
+        }
+        rem = brem;
+    }
+    __syncthreads();
+    if (ALL) {
+        for (int64_t g = t; g < G; g += kOneT) {
+            const uint32_t m = s_mask[g];
+            mask[g] = m;
+            dig += mix64(((unsigned long long)g << 32) | m);
+        }
+    }
+    unsigned long long tc, tn, td;
+    (void)block_excl_sum<kOneT>(cost, sw, &tc);
+    (void)block_excl_sum<kOneT>(cnt, sw, &tn);
+    (void)block_excl_sum<kOneT>(dig, sw, &td);
+    if (t != 0)
+        return;
+    if (tensor_level) {
+        ctl->sel_cost = tc;
+        ctl->error = (unsigned int)err;
+        return;
+    }
+    stats[0] = budget;
+    stats[1] = tc;
+    stats[2] = full;
+    stats[3] = tn;
+    stats[4] = n_units;
+    stats[5] = mix64(td ^ tc);
+    stats[6] = err;
+}
+
 __global__ __launch_bounds__(kT) void k_plan_digest(PlanCtl* ctl, const uint32_t* __restrict__ mask, int64_t G)
 {
     __shared__ unsigned long long s[4];
@@ -572,66 +836,111 @@ __global__ __launch_bounds__(kT) void k_plan_digest(PlanCtl* ctl, const uint32_t
 }
 
 __global__ __launch_bounds__(kT) void k_plan_final(PlanCtl* ctl, unsigned long long budget, unsigned long long full,
-                                                   unsigned long long n_units, int n_part)
+                                                   unsigned long long n_units, int n_part,
+                                                  unsigned long long* __restrict__ stats)
 {
     // takes in the digest terms of k_plan_digest's n_part workgroups
     const unsigned long long dg = block_sum_parts(ctl, 2, n_part);
     if (threadIdx.x != 0)
         return;
-    ctl->digest_acc += dg;
-    ctl->stats[0] = budget;
-    ctl->stats[1] = ctl->sel_cost;
-    ctl->stats[2] = full;
-    ctl->stats[3] = ctl->sel_count;
-    ctl->stats[4] = n_units;
-    ctl->stats[5] = mix64(ctl->digest_acc ^ ctl->sel_cost);
-    ctl->stats[6] = ctl->error;
+    stats[0] = budget;
+    stats[1] = ctl->sel_cost;
+    stats[2] = full;
+    stats[3] = ctl->sel_count;
+    stats[4] = n_units;
+    stats[5] = mix64(dg ^ ctl->sel_cost);
+    stats[6] = ctl->error;
 }
 
 }  // namespace
 
 namespace {
 
-// The plan's kernel sequence over G blocks with lengths blen[G] (elements),
-// control block ctl and two candidate lists of cap uids each; `rounds`
-// bounds the number of rounds (the distinct block lengths, or any larger
-// number: the later rounds stop once the plan is done).
-// Algorithm 1's selection over G "blocks" with lengths blen[G] (elements):
-// control block ctl, two candidate lists of cap uids each; `rounds` bounds
-// the number of rounds (the distinct lengths, or any larger number: the
-// later rounds stop once the plan is done).  Writes mask[G] and the
-// selected cost into ctl; stats come from one of the finals below.
-void enqueue_select(PlanCtl* ctl, uint32_t* list0, uint32_t* list1, unsigned cap, const uint32_t* blen,
-                    uint32_t es, int64_t G, int rounds, int K, const float* sumsq, const Coeffs& w,
-                    uint32_t flags, uint64_t budget, uint32_t* mask, hipStream_t s)
+// What a plan runs on: control block ctl, two candidate lists of cap uids each,
+// G "blocks" with lengths blen[G] (elements); `rounds` bounds the number of
+// rounds (the distinct lengths, or any larger number: the later rounds stop
+// once the plan is done).
+struct PlanIn {
+    PlanCtl* ctl;
+    uint32_t *list0, *list1;
+    unsigned cap;
+    const uint32_t* blen;
+    uint32_t es;
+    int64_t G;
+    int rounds, K;
+    const float* sumsq;
+    Coeffs w;
+    uint32_t flags;
+    uint64_t budget, full;
+    uint32_t* mask;
+};
+
+// Algorithm 1's selection; returns whether the stats are closed (written to
+// `stats`, device-visible; never at tensor level).  Otherwise mask[G] is
+// written, the selected cost is in ctl, and one of the finals below closes.
+bool enqueue_select(const PlanIn& p, bool tensor_level, unsigned long long* stats, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_plan_init, dim3(1), dim3(kT), 0, s, ctl, (unsigned long long)budget);
-    if (G > 0) {
-        const int64_t want = (G + kT - 1) / kT;
-        const unsigned grid0 = (unsigned)std::min<int64_t>(want, kPlanGrid);
-        // round 0 over every unit; its candidates for round 1 go to list1
-        const CandSrc src{nullptr, nullptr, 0u};
-        for (int d = 0; d < 8; ++d)
-            hipLaunchKernelGGL(k_plan_hist, dim3(grid0), dim3(kT), 0, s, ctl, d, sumsq, w, flags, K, blen, es, G,
-                               src);
-        hipLaunchKernelGGL(k_plan_mark, dim3(grid0), dim3(kT), 0, s, ctl, sumsq, w, flags, K, blen, es, G, src,
-                           mask, list1, &ctl->list_n[1], cap);
-        hipLaunchKernelGGL(k_plan_advance, dim3(1), dim3(kT), 0, s, ctl, 1, 0, (int)grid0);
-        if (rounds > 1)
-            hipLaunchKernelGGL(k_plan_rest, dim3(1), dim3(kT), 0, s, ctl, sumsq, w, flags, K, blen, es, G, list0,
-                               list1, cap, mask, 1, rounds);
+    PlanCtl* ctl = p.ctl;
+    const int64_t n = p.G * p.K;
+    const unsigned long long budget = p.budget, full = p.full;
+    if (n <= kOneMax) {
+        hipLaunchKernelGGL(k_plan_one<true>, dim3(1), dim3(kOneT), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen,
+                           p.es, p.G, nullptr, nullptr, 0u, p.mask, 0, budget, full, (unsigned long long)n,
+                           tensor_level, stats);
+        return !tensor_level;
     }
+    hipLaunchKernelGGL(k_plan_init, dim3(1), dim3(1024), 0, s, ctl, budget);
+    // round 0 over every unit; its candidates for round 1 go to list1.  The
+    // score's digits, then the uid's until at most kMarkBits are open
+    const unsigned hgrid = (unsigned)std::min<int64_t>((n + kHistT - 1) / kHistT, kHistGrid);
+    int bits = 0;
+    while (bits < 32 && (n - 1) >> bits)
+        ++bits;
+    int d = 0, psh = 0;
+    auto pass = [&](int sh, int wd) {
+        hipLaunchKernelGGL(k_plan_hist, dim3(hgrid), dim3(kHistT), 0, s, ctl, d, sh, wd, psh, p.sumsq, p.w, p.flags,
+                           p.K, p.blen, p.es, p.G);
+        psh = sh;
+        ++d;
+    };
+    pass(53, 11);
+    pass(42, 11);
+    pass(32, 10);
+    for (int open = bits; open > kMarkBits;) {
+        const int wd = std::min(open, 11);
+        open -= wd;
+        pass(open, wd);
+    }
+    // the uid bits above `bits` are zero in every key; with few units the
+    // whole uid is left to the marking pass
+    const int open = psh == 32 ? bits : psh;
+    const unsigned mgrid = (unsigned)std::min<int64_t>((p.G + kHistT - 1) / kHistT, kPlanGrid);
+    hipLaunchKernelGGL(k_plan_mark, dim3(mgrid), dim3(kHistT), 0, s, ctl, d - 1, psh, open, p.sumsq, p.w, p.flags, p.K,
+                       p.blen, p.es, p.G, p.mask, p.list1, &ctl->list_n[1], p.cap);
+    if (!tensor_level && p.cap <= (unsigned)kOneMax) {
+        hipLaunchKernelGGL(k_plan_one<false>, dim3(1), dim3(kOneT), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen,
+                           p.es, p.G, p.list1, &ctl->list_n[1], p.cap, p.mask, (int)mgrid, budget, full,
+                           (unsigned long long)n, false, stats);
+        return true;
+    }
+    // longer lists: reloaded in each pass
+    hipLaunchKernelGGL(k_plan_advance, dim3(1), dim3(kT), 0, s, ctl, 1, 0, (int)mgrid);
+    if (p.rounds > 1)
+        hipLaunchKernelGGL(k_plan_rest, dim3(1), dim3(kT), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen, p.es, p.G,
+                           p.list0, p.list1, p.cap, p.mask, 1, p.rounds);
+    return false;
 }
 
-// Stats of a block-level plan: digest over mask[G], the units selected.
-hipError_t enqueue_block_final(PlanCtl* ctl, const uint32_t* mask, int64_t G, int K, uint64_t budget,
-                               uint64_t full_bytes, hipStream_t s)
+// Block-level plan: the selection, then (where it has not closed them) the
+// stats over mask[G], left in `stats`.
+hipError_t enqueue_block_plan(const PlanIn& p, unsigned long long* stats, hipStream_t s)
 {
-    const int n_digest = G > 0 ? (int)std::min<int64_t>((G + kT - 1) / kT, kPlanGrid) : 0;
-    if (G > 0)
-        hipLaunchKernelGGL(k_plan_digest, dim3((unsigned)n_digest), dim3(kT), 0, s, ctl, mask, G);
-    hipLaunchKernelGGL(k_plan_final, dim3(1), dim3(kT), 0, s, ctl, (unsigned long long)budget,
-                       (unsigned long long)full_bytes, (unsigned long long)(G * K), n_digest);
+    if (!enqueue_select(p, false, stats, s)) {
+        const int n_digest = (int)std::min<int64_t>((p.G + kT - 1) / kT, kPlanGrid);
+        hipLaunchKernelGGL(k_plan_digest, dim3((unsigned)n_digest), dim3(kT), 0, s, p.ctl, p.mask, p.G);
+        hipLaunchKernelGGL(k_plan_final, dim3(1), dim3(kT), 0, s, p.ctl, (unsigned long long)p.budget,
+                           (unsigned long long)p.full, (unsigned long long)(p.G * p.K), n_digest, stats);
+    }
     return hipGetLastError();
 }
 
@@ -677,31 +986,32 @@ __global__ __launch_bounds__(kT) void k_plan_expand(PlanCtl* ctl, const uint32_t
 
 __global__ __launch_bounds__(kT) void k_plan_final_tensors(PlanCtl* ctl, unsigned long long budget,
                                                            unsigned long long full, unsigned long long n_units,
-                                                           int n_part)
+                                                           int n_part, unsigned long long* __restrict__ stats)
 {
     const unsigned long long cn = block_sum_parts(ctl, 1, n_part);
     const unsigned long long dg = block_sum_parts(ctl, 2, n_part);
     if (threadIdx.x != 0)
         return;
-    ctl->stats[0] = budget;
-    ctl->stats[1] = ctl->sel_cost;
-    ctl->stats[2] = full;
-    ctl->stats[3] = cn;
-    ctl->stats[4] = n_units;
-    ctl->stats[5] = mix64(dg ^ ctl->sel_cost);
-    ctl->stats[6] = ctl->error;
+    stats[0] = budget;
+    stats[1] = ctl->sel_cost;
+    stats[2] = full;
+    stats[3] = cn;
+    stats[4] = n_units;
+    stats[5] = mix64(dg ^ ctl->sel_cost);
+    stats[6] = ctl->error;
 }
 
-// Stats of a tensor-level plan: expand tmask[T] to mask[G], then count and
-// digest the block mask.
-hipError_t enqueue_tensor_final(PlanCtl* ctl, const uint32_t* tmask, const uint32_t* g0, int T, int64_t G, int K,
-                                uint64_t budget, uint64_t full_bytes, uint32_t* mask, hipStream_t s)
+// Tensor-level plan: p's blocks are the n_tensors tensors and p.mask their
+// selection words; expands those to mask[G], counts and digests it.
+hipError_t enqueue_tensor_plan(const PlanIn& p, const uint32_t* g0, int T, int64_t G, uint32_t* mask,
+                               unsigned long long* stats, hipStream_t s)
 {
+    (void)enqueue_select(p, true, stats, s);
     const int n_part = G > 0 ? (int)std::min<int64_t>((G + kT - 1) / kT, kPlanGrid) : 0;
     if (G > 0)
-        hipLaunchKernelGGL(k_plan_expand, dim3((unsigned)n_part), dim3(kT), 0, s, ctl, tmask, g0, T, G, mask);
-    hipLaunchKernelGGL(k_plan_final_tensors, dim3(1), dim3(kT), 0, s, ctl, (unsigned long long)budget,
-                       (unsigned long long)full_bytes, (unsigned long long)(G * K), n_part);
+        hipLaunchKernelGGL(k_plan_expand, dim3((unsigned)n_part), dim3(kT), 0, s, p.ctl, p.mask, g0, T, G, mask);
+    hipLaunchKernelGGL(k_plan_final_tensors, dim3(1), dim3(kT), 0, s, p.ctl, (unsigned long long)p.budget,
+                       (unsigned long long)p.full, (unsigned long long)(G * p.K), n_part, stats);
     return hipGetLastError();
 }
 
@@ -711,23 +1021,24 @@ hipError_t launch_plan(const BlockTable& bt, PlanScratch& ps, int K, const float
                        const Coeffs& w, uint32_t flags, uint64_t budget, uint64_t full_bytes, uint32_t* mask,
                        hipStream_t s)
 {
-    PlanCtl* ctl = ps.ctl;
-    const uint32_t es = (uint32_t)bt.esize;
-    hipError_t e;
-    if (sumsq != nullptr) {
-        enqueue_select(ctl, ps.list[0], ps.list[1], (unsigned)ps.list_cap, bt.d_len, es, bt.G, bt.n_distinct_len, K,
-                       sumsq, w, flags, budget, mask, s);
-        e = enqueue_block_final(ctl, mask, bt.G, K, budget, full_bytes, s);
-    } else {
-        // no block catalog: the tensor-level plan, each tensor one unit per expert
-        const int64_t T = bt.n_tensors;
-        enqueue_select(ctl, ps.list[0], ps.list[1], (unsigned)ps.list_cap, bt.d_tlen, es, T, bt.n_distinct_tlen, K,
-                       nullptr, w, flags, budget, ps.tmask, s);
-        e = enqueue_tensor_final(ctl, ps.tmask, bt.d_g0, (int)T, bt.G, K, budget, full_bytes, mask, s);
-    }
+    // the stats go straight to the pinned words the caller reads after its
+    // synchronisation: no copy behind the last kernel
+    unsigned long long* stats = nullptr;
+    hipError_t e = hipHostGetDevicePointer((void**)&stats, ps.h_stats, 0);
     if (e != hipSuccess)
         return e;
-    return hipMemcpyAsync(ps.h_stats, ctl->stats, sizeof(ctl->stats), hipMemcpyDeviceToHost, s);
+    const int64_t per_k = std::max<int64_t>(sumsq != nullptr ? bt.n_short : bt.n_tensors, 1);
+    const unsigned cap = (unsigned)std::min<int64_t>(ps.list_cap, per_k * K);  // what this layout can list
+    PlanIn p{ps.ctl, ps.list[0], ps.list[1], cap, bt.d_len, (uint32_t)bt.esize, bt.G,
+             bt.n_distinct_len, K, sumsq, w, flags, budget, full_bytes, mask};
+    if (sumsq != nullptr)
+        return enqueue_block_plan(p, stats, s);
+    // no block catalog: the tensor-level plan, each tensor one unit per expert
+    p.blen = bt.d_tlen;
+    p.G = bt.n_tensors;
+    p.rounds = bt.n_distinct_tlen;
+    p.mask = ps.tmask;
+    return enqueue_tensor_plan(p, bt.d_g0, (int)bt.n_tensors, bt.G, mask, stats, s);
 }
 
 // ---------------------------------------------------------------- plan without allocation
@@ -739,7 +1050,8 @@ hipError_t launch_plan(const BlockTable& bt, PlanScratch& ps, int K, const float
 // and each call rebuilds everything it reads from it.
 namespace {
 
-constexpr size_t kStaticPlanBytes = size_t(16) << 20;
+// 16 MiB of layout-dependent parts and the control block beyond its first 18,688 bytes
+constexpr size_t kStaticPlanBytes = (size_t(16) << 20) + ((sizeof(PlanCtl) + 255) & ~size_t(255)) - 18688;
 
 static __device__ __align__(256) unsigned char scratch[kStaticPlanBytes];
 
@@ -890,17 +1202,18 @@ hipError_t launch_plan_static(void* ws, const int64_t* numel, int32_t n_tensors,
             hipLaunchKernelGGL(k_static_blen, dim3((unsigned)((G + kT - 1) / kT)), dim3(kT), 0, s, d_numel, g0,
                                (int)n_tensors, block_elems, G, blen);
     }
+    // n_short + 1 bounds the distinct block lengths, hence the rounds
+    PlanIn in{ctl, list0, list1, (unsigned)cap, blen, es, G, (int)std::min<int64_t>(n_short + 1, 1 << 30), K, sumsq, w,
+              flags, budget, full_bytes, mask};
     if (sumsq != nullptr) {
-        // n_short + 1 bounds the distinct block lengths, hence the rounds
-        enqueue_select(ctl, list0, list1, (unsigned)cap, blen, es, G, (int)std::min<int64_t>(n_short + 1, 1 << 30), K,
-                       sumsq, w, flags, budget, mask, s);
-        e = enqueue_block_final(ctl, mask, G, K, budget, full_bytes, s);
+        e = enqueue_block_plan(in, ctl->stats, s);
     } else {
         // tensor-level plan; the number of tensors bounds its rounds
-        const int64_t T = G > 0 ? n_tensors : 0;
-        enqueue_select(ctl, list0, list1, (unsigned)cap, tlen, es, T, (int)std::max<int64_t>(T, 1), K, nullptr, w,
-                       flags, budget, tmask, s);
-        e = enqueue_tensor_final(ctl, tmask, g0, (int)n_tensors, G, K, budget, full_bytes, mask, s);
+        in.blen = tlen;
+        in.G = G > 0 ? n_tensors : 0;
+        in.rounds = (int)std::max<int64_t>(in.G, 1);
+        in.mask = tmask;
+        e = enqueue_tensor_plan(in, g0, (int)n_tensors, G, mask, ctl->stats, s);
     }
     if (e != hipSuccess)
         return e;
