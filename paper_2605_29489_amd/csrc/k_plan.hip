@@ -646,10 +646,12 @@ __global__ __launch_bounds__(kT) void k_plan_rest(PlanCtl* ctl, const float* __r
 // candidate matches, take what lies below it and go on with what lies above.
 // Both write the stats: with tensor_level only the selection goes to ctl (the
 // stats are closed over the expanded mask).
-constexpr int kOneT = 1024, kOnePer = 8, kOneMax = kOneT * kOnePer;
+constexpr int kOneMax = 8192;
 
-template <bool ALL>
-__global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* __restrict__ sumsq, Coeffs w,
+// NT threads of PER candidates each.  A round is a chain of barriers, cheaper
+// the fewer waves there are: lists up to 1024 take four waves.
+template <bool ALL, int NT, int PER>
+__global__ __launch_bounds__(NT) void k_plan_one(PlanCtl* ctl, const float* __restrict__ sumsq, Coeffs w,
                                                     uint32_t flags, int K, const uint32_t* __restrict__ blen,
                                                     uint32_t esize, int64_t G, const uint32_t* __restrict__ list,
                                                     const unsigned int* __restrict__ list_n, unsigned int cap,
@@ -659,21 +661,21 @@ __global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* _
                                                     unsigned long long* __restrict__ stats)
 {
     __shared__ unsigned long long lh[256];
-    __shared__ unsigned long long sw[kOneT / 64];
+    __shared__ unsigned long long sw[NT / 64];
     __shared__ unsigned long long s_below, s_total, s_key;
     __shared__ int s_v;
     __shared__ float s_w[kMaxK];
-    __shared__ uint32_t s_mask[ALL ? kOneMax : 1];
+    __shared__ uint32_t s_mask[ALL ? NT * PER : 1];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     unsigned long long rem = budget, err = 0ull, cost = 0ull, cnt = 0ull, dig = 0ull;  // this thread's, summed at the end
     bool rounds = true;
     uint32_t n;
     if (ALL) {
         n = (uint32_t)(G * K);
-        for (int64_t g = t; g < G; g += kOneT)
+        for (int64_t g = t; g < G; g += NT)
             s_mask[g] = 0u;
     } else {
-        for (int q = t; q < n_part; q += kOneT) {
+        for (int q = t; q < n_part; q += NT) {
             cost += ctl->part[0][q];
             cnt += ctl->part[1][q];
             dig += ctl->part[2][q];
@@ -682,16 +684,16 @@ __global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* _
         err = ctl->error;
         rem = ctl->brem[8];
         n = min(*list_n, cap);
-        rounds = !all && err == 0ull && n <= (uint32_t)kOneMax;
+        rounds = !all && err == 0ull && n <= (uint32_t)(NT * PER);
     }
     if (t < K)
         s_w[t] = w.v[t];
     __syncthreads();
-    unsigned long long key[kOnePer], c[kOnePer];
+    unsigned long long key[PER], c[PER];
     uint32_t alive = 0u;
 #pragma unroll
-    for (int q = 0; q < kOnePer; ++q) {
-        const uint32_t j = (uint32_t)(q * kOneT + t);
+    for (int q = 0; q < PER; ++q) {
+        const uint32_t j = (uint32_t)(q * NT + t);
         key[q] = 0ull;
         c[q] = 0ull;
         if (rounds && j < n) {
@@ -718,15 +720,15 @@ __global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* _
     for (;;) {
         unsigned long long mine = 0ull, total;
 #pragma unroll
-        for (int q = 0; q < kOnePer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             if (((alive >> q) & 1u) && c[q] > rem)
                 alive &= ~(1u << q);
             mine += ((alive >> q) & 1u) ? c[q] : 0ull;
         }
-        (void)block_excl_sum<kOneT>(mine, sw, &total);
+        (void)block_excl_sum<NT>(mine, sw, &total);
         if (total <= rem) {  // everything fits (or nothing is left)
 #pragma unroll
-            for (int q = 0; q < kOnePer; ++q)
+            for (int q = 0; q < PER; ++q)
                 if ((alive >> q) & 1u)
                     take(q);
             break;
@@ -741,7 +743,7 @@ __global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* _
             __syncthreads();
             const int sh = 56 - 8 * d;
 #pragma unroll
-            for (int q = 0; q < kOnePer; ++q)
+            for (int q = 0; q < PER; ++q)
                 if ((match >> q) & 1u)
                     atomicAdd(&lh[(key[q] >> sh) & 255u], c[q]);
             __syncthreads();
@@ -762,13 +764,13 @@ __global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* _
             brem -= s_below;
             prefix |= (unsigned long long)s_v << sh;
 #pragma unroll
-            for (int q = 0; q < kOnePer; ++q)
+            for (int q = 0; q < PER; ++q)
                 if (((match >> q) & 1u) && ((key[q] ^ prefix) >> sh) != 0ull)
                     match &= ~(1u << q);
             if (__syncthreads_or(__popc(match) > 1) == 0 && __syncthreads_count(match != 0u) == 1) {
                 // one candidate is left: it is the cut
 #pragma unroll
-                for (int q = 0; q < kOnePer; ++q)
+                for (int q = 0; q < PER; ++q)
                     if ((match >> q) & 1u)
                         s_key = key[q];
                 __syncthreads();
@@ -781,7 +783,7 @@ __global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* _
             break;
         }
 #pragma unroll
-        for (int q = 0; q < kOnePer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             if (((alive >> q) & 1u) && key[q] <= prefix) {
                 if (key[q] < prefix)
                     take(q);
@@ -792,16 +794,16 @@ __global__ __launch_bounds__(kOneT) void k_plan_one(PlanCtl* ctl, const float* _
     }
     __syncthreads();
     if (ALL) {
-        for (int64_t g = t; g < G; g += kOneT) {
+        for (int64_t g = t; g < G; g += NT) {
             const uint32_t m = s_mask[g];
             mask[g] = m;
             dig += mix64(((unsigned long long)g << 32) | m);
         }
     }
     unsigned long long tc, tn, td;
-    (void)block_excl_sum<kOneT>(cost, sw, &tc);
-    (void)block_excl_sum<kOneT>(cnt, sw, &tn);
-    (void)block_excl_sum<kOneT>(dig, sw, &td);
+    (void)block_excl_sum<NT>(cost, sw, &tc);
+    (void)block_excl_sum<NT>(cnt, sw, &tn);
+    (void)block_excl_sum<NT>(dig, sw, &td);
     if (t != 0)
         return;
     if (tensor_level) {
@@ -884,9 +886,12 @@ bool enqueue_select(const PlanIn& p, bool tensor_level, unsigned long long* stat
     const int64_t n = p.G * p.K;
     const unsigned long long budget = p.budget, full = p.full;
     if (n <= kOneMax) {
-        hipLaunchKernelGGL(k_plan_one<true>, dim3(1), dim3(kOneT), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen,
-                           p.es, p.G, nullptr, nullptr, 0u, p.mask, 0, budget, full, (unsigned long long)n,
-                           tensor_level, stats);
+        auto one = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen, p.es, p.G,
+                               nullptr, nullptr, 0u, p.mask, 0, budget, full, (unsigned long long)n, tensor_level,
+                               stats);
+        };
+        n <= 4096 ? one(k_plan_one<true, 1024, 4>) : one(k_plan_one<true, 1024, 8>);
         return !tensor_level;
     }
     hipLaunchKernelGGL(k_plan_init, dim3(1), dim3(1024), 0, s, ctl, budget);
@@ -918,9 +923,12 @@ bool enqueue_select(const PlanIn& p, bool tensor_level, unsigned long long* stat
     hipLaunchKernelGGL(k_plan_mark, dim3(mgrid), dim3(kHistT), 0, s, ctl, d - 1, psh, open, p.sumsq, p.w, p.flags, p.K,
                        p.blen, p.es, p.G, p.mask, p.list1, &ctl->list_n[1], p.cap);
     if (!tensor_level && p.cap <= (unsigned)kOneMax) {
-        hipLaunchKernelGGL(k_plan_one<false>, dim3(1), dim3(kOneT), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen,
-                           p.es, p.G, p.list1, &ctl->list_n[1], p.cap, p.mask, (int)mgrid, budget, full,
-                           (unsigned long long)n, false, stats);
+        auto one = [&](auto kern, int nt) {
+            hipLaunchKernelGGL(kern, dim3(1), dim3(nt), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen, p.es, p.G,
+                               p.list1, &ctl->list_n[1], p.cap, p.mask, (int)mgrid, budget, full,
+                               (unsigned long long)n, false, stats);
+        };
+        p.cap <= 1024u ? one(k_plan_one<false, 256, 4>, 256) : one(k_plan_one<false, 1024, 8>, 1024);
         return true;
     }
     // longer lists: reloaded in each pass
@@ -1050,8 +1058,12 @@ hipError_t launch_plan(const BlockTable& bt, PlanScratch& ps, int K, const float
 // and each call rebuilds everything it reads from it.
 namespace {
 
-// 16 MiB of layout-dependent parts and the control block beyond its first 18,688 bytes
-constexpr size_t kStaticPlanBytes = (size_t(16) << 20) + ((sizeof(PlanCtl) + 255) & ~size_t(255)) - 18688;
+// The limit that layouts are held to, with kCtlCounted bytes of it for the
+// control block; what the block takes beyond those is added to the array.
+constexpr size_t kStaticPlanLimit = size_t(16) << 20, kCtlCounted = 18688;
+constexpr size_t kCtlBytes = (sizeof(PlanCtl) + 255) & ~size_t(255);
+static_assert(kCtlBytes >= kCtlCounted, "the control block's counted part");
+constexpr size_t kStaticPlanBytes = kStaticPlanLimit + kCtlBytes - kCtlCounted;
 
 static __device__ __align__(256) unsigned char scratch[kStaticPlanBytes];
 
@@ -1144,10 +1156,10 @@ StaticParts static_parts(int64_t n_tensors, int64_t G, int K)
 int64_t static_plan_bytes(int64_t n_tensors, int64_t G, int64_t n_short, int K)
 {
     const StaticParts a = static_parts(n_tensors, G, K);
-    return (int64_t)(a.ctl + a.numel + a.g0 + a.tlen + a.tmask + a.blen + 2 * a.list);
+    return (int64_t)(kCtlCounted + a.numel + a.g0 + a.tlen + a.tmask + a.blen + 2 * a.list);
 }
 
-int64_t static_plan_limit() { return (int64_t)kStaticPlanBytes; }
+int64_t static_plan_limit() { return (int64_t)kStaticPlanLimit; }
 
 hipError_t static_plan_scratch(void** ptr)
 {
