@@ -76,7 +76,7 @@ struct DeviceWs {
     int64_t tt_pairs = 0;
     uint32_t* tt_list = nullptr;               //   and the lists of the one-pass route
     uint64_t tt_list_words = 0;
-    uint32_t* h_tt_err = nullptr;              // pinned copy of the error word
+    uint32_t* h_tt_err = nullptr;              // pinned copy of the error word and the left-over count
 };
 
 std::mutex g_mu;
@@ -303,7 +303,7 @@ int get_ws(DeviceWs** out)
         (e = ws_host_malloc((void**)&w->plan.h_stats, sizeof(uint64_t) * 8)) != hipSuccess ||
         (e = ws_malloc((void**)&w->counters, sizeof(unsigned long long) * 256)) != hipSuccess ||
         (e = ws_host_malloc((void**)&w->h_counters, sizeof(unsigned long long) * 256)) != hipSuccess ||
-        (e = ws_host_malloc((void**)&w->h_tt_err, sizeof(uint32_t))) != hipSuccess) {
+        (e = ws_host_malloc((void**)&w->h_tt_err, 2 * sizeof(uint32_t))) != hipSuccess) {
         free_ws(dev, *w);
         return fail(MP_E_NOMEM, "workspace allocation failed: %s", hipGetErrorString(e));
     }
@@ -847,15 +847,19 @@ int mp_ties_tensor_thresholds(const mp_layout* layout, const void* base, const v
         return MP_OK;  // no units: nothing to select
     const char* hook = std::getenv("MP_FAULT_TENSOR_NO_CUT");
     const bool force = hook != nullptr && hook[0] == '1';
-    if ((e = launch_ties_tensor(bt, base, c.ex, K, mask, density, tau, ws.tt_hist, ws.tt_state, list, s,
-                                delta, force)) !=
-        hipSuccess)
-        return hip_fail(e, "tensor-scope thresholds launch");
-    if ((e = hipMemcpyAsync(ws.h_tt_err, ws.tt_state + pairs, sizeof(uint32_t), hipMemcpyDeviceToHost, s)) !=
-        hipSuccess)
-        return hip_fail(e, "tensor-scope error word readback");
-    if ((e = hipStreamSynchronize(s)) != hipSuccess)
-        return hip_fail(e, "hipStreamSynchronize");
+    TensorTies route = list != nullptr && !force ? TensorTies::Bracket : TensorTies::Radix;
+    for (bool again = true; again;) {
+        if ((e = launch_ties_tensor(bt, base, c.ex, K, mask, density, tau, ws.tt_hist, ws.tt_state, list, route, s,
+                                    delta, force)) != hipSuccess)
+            return hip_fail(e, "tensor-scope thresholds launch");
+        if ((e = hipMemcpyAsync(ws.h_tt_err, ws.tt_state + pairs, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s)) !=
+            hipSuccess)
+            return hip_fail(e, "tensor-scope error word readback");
+        if ((e = hipStreamSynchronize(s)) != hipSuccess)
+            return hip_fail(e, "hipStreamSynchronize");
+        again = route == TensorTies::Bracket && ws.h_tt_err[1] != 0u;  // pairs left to the radix passes
+        route = TensorTies::Left;
+    }
     if (*ws.h_tt_err != 0u)
         return fail(MP_E_HIP, "tensor-scope threshold kernels reported an internal error (no cut found)");
     return MP_OK;

@@ -5,7 +5,7 @@
 // the per-unit threshold kernel with each unit taking its tensor's value.
 //
 // Two exact routes.  The bracket route reads the selected blocks once, after
-// a sample of about a sixteenth of them:
+// a sample of about a 32nd of them:
 //   k_tt_sample   (twice) histograms a slice of every selected block, first
 //                 of bits 30..20, then of the range that the first kept;
 //   k_tt_bracket  (twice) one wave per (expert, tensor) pair turns the sample
@@ -20,14 +20,14 @@
 //                 it is the bin's floor, or one of the listed elements.
 // Nothing depends on the sample being right: a pair whose k-th largest lies
 // outside its bracket, or whose list overflows, is left to the second route.
-// The full pass is bound by memory (base and selected experts once, 1.4 ms of
+// The full pass is bound by memory (base and selected experts once, 1.46 ms of
 // the 1.5B-parameter case against 4.5 ms for three digit passes).
 //
 // The radix route is an exact MSD select on the 31-bit magnitude patterns,
 // three digit passes (bits 30..20, 19..9, 8..0) over the selected blocks.  It
 // takes whole layouts with blocks over 4096 elements or without room for the
-// lists, and the pairs that the first route left (its kernels return at once
-// when there are none):
+// lists, and the pairs that the first route left (the host, which waits for the
+// call anyway, sees their number and launches it only then):
 //   k_tt_hist     one workgroup per (run of <= 16 consecutive blocks of one
 //                 tensor, expert): LDS histogram of the digit of the
 //                 elements that match the prefix fixed so far, nonzero bins
@@ -71,27 +71,27 @@ constexpr int kTH = 256, kCop = 2;
 __host__ __device__ inline int tt_shift(int pass) { return pass == 0 ? 20 : (pass == 1 ? 9 : 0); }
 __host__ __device__ inline int tt_width(int pass) { return pass == 2 ? 9 : 11; }
 
-__global__ __launch_bounds__(kTT) void k_tt_zero(uint32_t* __restrict__ p, int64_t n,
-                                                 const uint32_t* __restrict__ left = nullptr)
+__global__ __launch_bounds__(kTT) void k_tt_zero(uint32_t* __restrict__ p, int64_t n)
 {
-    if (left != nullptr && *left == 0u)
-        return;
     for (int64_t q = (int64_t)blockIdx.x * kTT + threadIdx.x; q < n; q += (int64_t)gridDim.x * kTT)
         p[q] = 0u;
 }
 
 template <int DT, bool DELTA, int kTH, int kCopies>
-__device__ inline void tt_hist_run(const void* __restrict__ base, ExpertPtrs ex, int K,
+__global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, ExpertPtrs ex, int K,
                                                   const uint4* __restrict__ chunks,
                                                   const uint64_t* __restrict__ boff,
                                                   const uint32_t* __restrict__ blen,
                                                   const uint32_t* __restrict__ mask,
                                                   const uint4* __restrict__ state, int T, int pass,
-                                                  uint32_t* __restrict__ hist, uint32_t n_pairs, uint32_t pr)
+                                                  uint32_t* __restrict__ hist, uint32_t n_pairs, uint32_t per_xcd)
 {
     constexpr int V = Fmt<DT>::V;
     __shared__ __align__(16) uint32_t h[kDigBins * kCopies];  // h[bin * kCopies + copy]
     static_assert(kCopies == 1 || kCopies == 2 || kCopies == 4, "a bin's copies are one LDS read");
+    // workgroup id -> (run, expert): XCD x = id mod 8 takes pairs
+    // x*per_xcd .. in order
+    const uint32_t pr = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (pr >= n_pairs)
         return;
     const uint4 ch = chunks[pr / (uint32_t)K];
@@ -166,33 +166,11 @@ __device__ inline void tt_hist_run(const void* __restrict__ base, ExpertPtrs ex,
     }
 }
 
-// Workgroup id -> (run, expert): XCD x = id mod 8 takes pairs x*per_xcd ..
-// in order, every gridDim.x / 8-th of them (grid: a multiple of 8).  `left`
-// (null: none) is the count of pairs that the bracket route left.
-template <int DT, bool DELTA, int kTH, int kCopies>
-__global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, ExpertPtrs ex, int K,
-                                                 const uint4* __restrict__ chunks, const uint64_t* __restrict__ boff,
-                                                 const uint32_t* __restrict__ blen, const uint32_t* __restrict__ mask,
-                                                 const uint4* __restrict__ state, int T, int pass,
-                                                 uint32_t* __restrict__ hist, uint32_t n_pairs, uint32_t per_xcd,
-                                                 const uint32_t* __restrict__ left)
-{
-    if (left != nullptr && *left == 0u)
-        return;
-    for (uint32_t j = blockIdx.x >> 3; j < per_xcd; j += gridDim.x >> 3) {
-        __syncthreads();  // the previous run's histogram has been read
-        tt_hist_run<DT, DELTA, kTH, kCopies>(base, ex, K, chunks, boff, blen, mask, state, T, pass, hist, n_pairs,
-                                             (blockIdx.x & 7u) * per_xcd + j);
-    }
-}
-
 __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, const uint32_t* __restrict__ hist,
                                                      const uint64_t* __restrict__ tnumel, int K, int T,
                                                      double density, int pass, uint32_t* __restrict__ err,
-                                                     int force_no_cut, const uint32_t* __restrict__ left)
+                                                     int force_no_cut)
 {
-    if (left != nullptr && *left == 0u)
-        return;
     const int lane = threadIdx.x & 63;
     const int64_t q = (int64_t)blockIdx.x * (kTT / 64) + (threadIdx.x >> 6);
     if (q >= (int64_t)K * T)
@@ -271,7 +249,7 @@ __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, c
 }
 
 // ---------------------------------------------------------------- bracket route
-constexpr int kSampleShare = 16;          // the sample: a sixteenth of every block
+constexpr int kSampleShare = 32;          // the sample: a 32nd of every block
 constexpr uint32_t kSampleRuns = 8;       // runs per sampling workgroup
 constexpr uint32_t kSmallTensor = 8192u;  // up to here a pair lists every element
 constexpr int kScanBins = 256, kScanCop = 4;
@@ -305,8 +283,8 @@ __device__ inline void tt_flush_sample(uint32_t* h, uint32_t* __restrict__ out)
 // Sample pass LV (0: bits 30..20 of every sampled element, and the pair's
 // selected elements; 1: the bracket's elements by (pattern - lo) >> shift).
 // One workgroup per expert and kSampleRuns consecutive runs; from block g of
-// a run it takes the (g mod 16)-th slice of segc 16-byte chunks, so the slices
-// visit every part of a tensor's blocks.
+// a run it takes the (g mod kSampleShare)-th slice of segc 16-byte chunks, so the
+// slices visit every part of a tensor's blocks.
 template <int DT, bool DELTA, int LV>
 __global__ __launch_bounds__(kTT) void k_tt_sample(const void* __restrict__ base, ExpertPtrs ex, int K,
                                                    const uint4* __restrict__ chunks,
@@ -319,54 +297,80 @@ __global__ __launch_bounds__(kTT) void k_tt_sample(const void* __restrict__ base
 {
     constexpr int V = Fmt<DT>::V;
     __shared__ uint32_t h[kDigBins];
-    const int i = (int)(blockIdx.x % (uint32_t)K);
-    const uint32_t r0 = (blockIdx.x / (uint32_t)K) * kSampleRuns, r1 = min(r0 + kSampleRuns, n_runs);
+    // the K experts of a group of runs on one XCD (id mod 8), one after another
+    const uint32_t pos = blockIdx.x >> 3;
+    const int i = (int)(pos % (uint32_t)K);
+    const uint32_t r0 = (pos / (uint32_t)K * 8u + (blockIdx.x & 7u)) * kSampleRuns, r1 = min(r0 + kSampleRuns, n_runs);
+    if (r0 >= n_runs)
+        return;
     const uint32_t tid = threadIdx.x;
     for (int q = (int)tid; q < kDigBins; q += kTT)
         h[q] = 0u;
     __syncthreads();
+    // (run, share of its slices) pairs in order, kAhead of them loaded at once:
+    // one at a time the pass was a chain of latencies
+    constexpr uint32_t kAhead = 4u;
+    const uint32_t nq = ((uint32_t)kChunkBlocks * segc + kTT - 1u) / kTT, steps = (r1 - r0) * nq;
     uint32_t cur = 0xffffffffu;  // the tensor whose counts h holds
-    for (uint32_t r = r0; r < r1; ++r) {
-        const uint4 ch = chunks[r];
-        const size_t pq = (size_t)i * T + ch.z;
-        if (cur != ch.z && cur != 0xffffffffu)
-            tt_flush_sample(h, hist + ((size_t)i * T + cur) * kDigBins);
-        cur = ch.z;
-        uint32_t lo = 0u, width = 0x80000000u, sh = 20u;
-        if (LV == 1) {
-            if (state[pq].z != 0u)
-                continue;
-            const uint4 b = br[pq];
-            lo = b.x;
-            width = b.y;
-            sh = b.z;
-        }
-        const uint32_t nb = ch.y - ch.x;  // at most kChunkBlocks
-        if (LV == 0) {  // the selected elements of the run (one wave)
-            uint32_t n = (tid < nb && ((mask[ch.x + tid] >> i) & 1u)) ? blen[ch.x + tid] : 0u;
-            if (tid < 64u) {
-                n = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(n), 63);
-                if (tid == 0u && n != 0u)
-                    atomicAdd(&cnt[pq].x, n);
-            }
-        }
-        for (uint32_t q = tid; q < nb * segc; q += kTT) {
-            const uint32_t g = ch.x + q / segc, nch = blen[g] / V;
+    for (uint32_t x0 = 0u; x0 < steps; x0 += kAhead) {
+        uint4 ch[kAhead], re[kAhead], rb[kAhead];
+        uint32_t n[kAhead];
+        bool in[kAhead];
+#pragma unroll
+        for (uint32_t a = 0u; a < kAhead; ++a) {
+            const uint32_t x = min(x0 + a, steps - 1u);
+            ch[a] = chunks[r0 + x / nq];
+            const uint32_t q = x % nq * kTT + tid, nb = ch[a].y - ch[a].x;  // at most kChunkBlocks
+            const uint32_t g = min(ch[a].x + q / segc, ch[a].y - 1u), nch = blen[g] / V;
             uint32_t c = (g % kSampleShare) * segc + q % segc;
             if (nch <= (g % kSampleShare) * segc)
                 c = q % segc;  // a short block without that slice: its first one
-            if (!((mask[g] >> i) & 1u) || c >= nch)
-                continue;
+            in[a] = x0 + a < steps && q < nb * segc && ((mask[g] >> i) & 1u) && c < nch;
             const uint64_t off = boff[g];
-            float fe[V], fb[V];
-            Fmt<DT>::unpack(chunk_ptr(ex.p[i], off, Fmt<DT>::esize)[c], fe);
-            if (!DELTA)
-                Fmt<DT>::unpack(chunk_ptr(base, off, Fmt<DT>::esize)[c], fb);
+            re[a] = rb[a] = make_uint4(0u, 0u, 0u, 0u);
+            if (in[a]) {
+                re[a] = chunk_ptr(ex.p[i], off, Fmt<DT>::esize)[c];
+                if (!DELTA)
+                    rb[a] = chunk_ptr(base, off, Fmt<DT>::esize)[c];
+            }
+            if (LV == 0)  // the run's selected elements, counted with its first share
+                n[a] = x0 + a < steps && x % nq == 0u && tid < nb && ((mask[ch[a].x + tid] >> i) & 1u)
+                           ? blen[ch[a].x + tid]
+                           : 0u;
+        }
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const uint32_t mg = __float_as_uint(DELTA ? fe[v] : fe[v] - fb[v]) & 0x7fffffffu;
-                if (LV == 0 || mg - lo < width)
-                    atomicAdd(&h[(mg - lo) >> sh], 1u);
+        for (uint32_t a = 0u; a < kAhead; ++a) {
+            if (x0 + a >= steps)
+                break;
+            const size_t pq = (size_t)i * T + ch[a].z;
+            if (cur != ch[a].z && cur != 0xffffffffu)
+                tt_flush_sample(h, hist + ((size_t)i * T + cur) * kDigBins);
+            cur = ch[a].z;
+            if (LV == 0 && tid < 64u) {
+                const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(n[a]), 63);
+                if (tid == 0u && sum != 0u)
+                    atomicAdd(&cnt[pq].x, sum);
+            }
+            uint32_t lo = 0u, width = 0x80000000u, sh = 20u;
+            if (LV == 1) {
+                if (state[pq].z != 0u)
+                    continue;
+                const uint4 b = br[pq];
+                lo = b.x;
+                width = b.y;
+                sh = b.z;
+            }
+            if (in[a]) {
+                float fe[V], fb[V];
+                Fmt<DT>::unpack(re[a], fe);
+                if (!DELTA)
+                    Fmt<DT>::unpack(rb[a], fb);
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const uint32_t mg = __float_as_uint(DELTA ? fe[v] : fe[v] - fb[v]) & 0x7fffffffu;
+                    if (LV == 0 || mg - lo < width)
+                        atomicAdd(&h[(mg - lo) >> sh], 1u);
+                }
             }
         }
     }
@@ -704,7 +708,7 @@ uint64_t ties_tensor_list_words(uint64_t n_tensors, uint64_t elems)
 
 hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const ExpertPtrs& ex, int K,
                               const uint32_t* mask, double density, uint32_t* tau, uint32_t* hist, uint4* state,
-                              uint32_t* list, hipStream_t s, bool delta, bool force_no_cut)
+                              uint32_t* list, TensorTies route, hipStream_t s, bool delta, bool force_no_cut)
 {
     if (bt.G == 0)
         return hipSuccess;
@@ -716,18 +720,18 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
     uint4 *br = state + 2 * pairs + 1, *cnt = state + pairs + 1;
     uint32_t* err = reinterpret_cast<uint32_t*>(state + pairs);
     uint32_t* left = err + 1;
-    const bool bracket = list != nullptr && !force_no_cut;
     const int64_t nz = (2 * pairs + 1) * 4;
-    hipLaunchKernelGGL(k_tt_zero, dim3((unsigned)std::min<int64_t>((nz + kTT - 1) / kTT, 1024)), dim3(kTT), 0, s,
-                       reinterpret_cast<uint32_t*>(state), nz, nullptr);
+    if (route != TensorTies::Left)
+        hipLaunchKernelGGL(k_tt_zero, dim3((unsigned)std::min<int64_t>((nz + kTT - 1) / kTT, 1024)), dim3(kTT), 0, s,
+                           reinterpret_cast<uint32_t*>(state), nz);
     const uint32_t n_pairs = (uint32_t)(bt.n_chunks * K), per_xcd = (n_pairs + 7u) / 8u;
     const dim3 hgrid(8u * per_xcd);
     const dim3 zgrid((unsigned)std::min<int64_t>((nh + kTT - 1) / kTT, 2048));
     const dim3 pgrid((unsigned)((pairs + 3) / 4));
-    if (bracket) {
-        hipLaunchKernelGGL(k_tt_zero, zgrid, dim3(kTT), 0, s, hist, nh, nullptr);
+    if (route == TensorTies::Bracket) {
+        hipLaunchKernelGGL(k_tt_zero, zgrid, dim3(kTT), 0, s, hist, nh);
         const uint32_t n_runs = (uint32_t)bt.n_chunks;
-        const dim3 sgrid((n_runs + kSampleRuns - 1) / kSampleRuns * (uint32_t)K);
+        const dim3 sgrid(((n_runs + kSampleRuns - 1) / kSampleRuns + 7u) / 8u * 8u * (uint32_t)K);
         const uint32_t v = bt.dtype == 0 ? 4u : 8u;
         const uint32_t segc = std::max<uint32_t>(1u, (uint32_t)bt.block_elems / v / kSampleShare);
         const uint32_t lwords = (uint32_t)bt.tt_words;
@@ -756,15 +760,12 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
         hipLaunchKernelGGL(k_tt_pick, dim3((unsigned)pairs), dim3(kPick), 0, s, state, br, cnt, hist, list,
                            bt.d_g0, bt.d_off, lwords, bt.d_tnumel, T, density, left);
     }
-    // the radix passes: over everything, or over the pairs the bracket route
-    // left (a grid that fills the chip twice, so that empty passes end soon)
-    const uint32_t* go_left = bracket ? left : nullptr;
-    const dim3 rgrid(bracket ? std::min(8u * per_xcd, 2048u) : 8u * per_xcd);
-    for (int pass = 0; pass < 3; ++pass) {
-        hipLaunchKernelGGL(k_tt_zero, zgrid, dim3(kTT), 0, s, hist, nh, go_left);
+    // the radix passes: over everything, or over the pairs the bracket route left
+    for (int pass = 0; pass < 3 && route != TensorTies::Bracket; ++pass) {
+        hipLaunchKernelGGL(k_tt_zero, zgrid, dim3(kTT), 0, s, hist, nh);
         auto go = [&](auto kern, int nth) {
-            hipLaunchKernelGGL(kern, rgrid, dim3(nth), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask, state,
-                               T, pass, hist, n_pairs, per_xcd, go_left);
+            hipLaunchKernelGGL(kern, hgrid, dim3(nth), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask, state,
+                               T, pass, hist, n_pairs, per_xcd);
         };
         if (pass == 0) {
             if (bt.dtype == 0)
@@ -778,7 +779,7 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
                 delta ? go(k_tt_hist<1, true, kTH, kCop>, kTH) : go(k_tt_hist<1, false, kTH, kCop>, kTH);
         }
         hipLaunchKernelGGL(k_tt_resolve, pgrid, dim3(kTT), 0, s, state, hist, bt.d_tnumel, K, T, density, pass, err,
-                           force_no_cut ? 1 : 0, go_left);
+                           force_no_cut ? 1 : 0);
     }
     hipLaunchKernelGGL(k_tt_expand, dim3((unsigned)((bt.G * K + kTT - 1) / kTT)), dim3(kTT), 0, s, state,
                        bt.d_tensor, bt.G, K, T, tau);

@@ -131,13 +131,15 @@ hipError_t launch_plan(const BlockTable& bt, PlanScratch& ps, int K, const float
 // k-th largest |d| of tensor(g)'s zero-completed masked deltas of expert i.
 // hist: device uint32[K * n_tensors * 2048], state: device uint4[3 * K *
 // n_tensors + 1]; the word after the first K * n_tensors entries is set to
-// nonzero if a selection found no cut (an internal error).  list: K *
-// bt.tt_words device words for the route that reads the blocks once, or null
-// for the radix route.  force_no_cut: a test hook that sends
+// nonzero if a selection found no cut (an internal error).  Route: Bracket reads
+// the blocks once and needs list, K * bt.tt_words device words; the word after
+// the error word then counts the pairs it left, which a second call with Left
+// finishes by the radix passes.  Radix takes every pair by those.  force_no_cut: a test hook that sends
 // the first pair down that error path (the kernels still finish normally).
+enum class TensorTies { Radix, Bracket, Left };
 hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const ExpertPtrs& ex, int K,
                               const uint32_t* mask, double density, uint32_t* tau, uint32_t* hist, uint4* state,
-                              uint32_t* list, hipStream_t s, bool delta, bool force_no_cut);
+                              uint32_t* list, TensorTies route, hipStream_t s, bool delta, bool force_no_cut);
 uint64_t ties_tensor_list_words(uint64_t n_tensors, uint64_t elems);
 
 // ---------------------------------------------------------------- LoRA source (k_lora.hip)

@@ -28,13 +28,13 @@ def _check(mp, dtype, be, numel, base, exps, mask, density, delta=False):  # noq
 
 def _family(dtype, numel, be, seed):
     """Six experts: normal, a few repeated values, mostly zero, all equal,
-    large only in the first sixteenth of every 16 blocks (the sampled slices see
+    large only in the slices that the sample reads (they see
     far too many), and magnitudes that share their top 16 bits."""
     P = sum(numel)
     rng = np.random.default_rng(seed)
     sign = rng.choice([-1.0, 1.0], P)
     pos = np.arange(P)
-    seen = (pos % be) // max(1, be // 16) == (pos // be) % 16
+    seen = (pos % be) // max(1, be // 32) == (pos // be) % 32
     deltas = [rng.normal(0.0, 1e-3, P), rng.choice([0.5, 1.0, 1.5], P) * 2.0 ** -10 * sign,
               np.where(rng.random(P) < 0.05, rng.normal(0.0, 1e-3, P), 0.0), np.full(P, 2.0 ** -9),
               np.where(seen, 1.0, 1e-3) * rng.normal(0.0, 1.0, P),
