@@ -574,6 +574,7 @@ int run_merge(const mp_layout* L, const void* base, const void* const* experts, 
         if ((e = hipGetLastError()) != hipSuccess)
             return hip_fail(e, "counter reset");
     }
+    a.pcie = residency == MP_HOST_PINNED;
     mp_io_stats st{};
     uint64_t staged_bytes = 0;
     if (staged(residency)) {

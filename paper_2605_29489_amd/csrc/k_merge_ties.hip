@@ -1,8 +1,11 @@
 // The TIES merge operator with the trim inside the merge (Appendix A.1:
 // trim, elect signs, average the sign-consistent entries, over the masked
-// deltas), one workgroup per block.
+// deltas), one workgroup per block.  Two forms: k_merge_ties trims up to four
+// experts together with their deltas in the workgroup's registers; k_ties_two,
+// further down, finds the thresholds one wave per expert and then reads the
+// block again to merge it (many experts, short blocks).
 //
-// Two copies of each window bin: registers (about 120 per lane: the K
+// k_merge_ties: two copies of each window bin: registers (about 120 per lane: the K
 // experts' 16 deltas each) hold the kernel at four waves per SIMD either
 // way, and halving the histogram rows (33 to 17 KiB per workgroup) took the
 // merges on the Qwen2.5-1.5B-shaped family at B = 25/50/100% from 1.90 /
@@ -713,6 +716,160 @@ __global__ __launch_bounds__(ties::NT, MULTI ? ties::NT / 128 : MP_TIES_WAVES) v
     }
 }
 
+// ------------------------------------------------------------ select, then merge
+// A workgroup of NW waves per block, for experts in device memory.  First
+// wave w takes the block's selected experts w, w + NW, ...: it holds the unit's deltas
+// (R chunks per lane), finds the trim threshold by itself as the catalog does
+// (no barrier) and leaves it in LDS.  Then all lanes merge: the base and the
+// selected experts are read again, eight elements per lane and pass, each
+// expert folded in as it arrives.  The second read is served by L2 and the
+// last-level cache (a workgroup's blocks are at most a few hundred KiB, and the
+// resident ones together fit), so HBM sees each byte once, and the state
+// carried between groups of experts by k_merge_ties (three registers per
+// element at two waves per SIMD, each group's loads behind the last one's
+// barriers) is not needed.
+template <int DT, int R, int NW, int W, bool DELTA, class Src>
+__global__ __launch_bounds__(64 * NW, W) void k_ties_two(
+    Src src, const void* __restrict__ base, const uint32_t* __restrict__ mask, const uint64_t* __restrict__ boff,
+    const uint32_t* __restrict__ blen, double density, uint32_t n_full, uint32_t k_full, float lambda, uint32_t kmask,
+    void* __restrict__ out, unsigned long long* __restrict__ ctr, float gcoef)
+{
+    constexpr int V = Fmt<DT>::V, ES = Fmt<DT>::esize;
+    constexpr int E = R * V;               // deltas per lane and unit
+    constexpr int RG = R > 8 ? 8 : R;      // rows loaded before the first use (fp32: 16 of each would spill)
+    constexpr int CPT = (DT == 1) ? 1 : 2; // merge: chunks per lane and pass
+    constexpr int EM = CPT * V;
+    __shared__ __align__(16) uint32_t rows[NW][ties::NB];
+    __shared__ uint32_t s_tau[kMaxK];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t b = blockIdx.x;
+    const uint32_t g = uniform_u32(src.block(b));
+    const uint64_t off = boff[g];
+    const uint32_t n = blen[g];
+    uint32_t k = k_full;
+    if (n != n_full) {
+        const double kk = ceil(density * (double)n);
+        k = (kk >= (double)n) ? n : (uint32_t)kk;
+    }
+    const uint32_t m = (k != 0u) ? (mask[g] & kmask) : 0u;  // density 0 keeps nothing: no expert is read
+    const uint32_t nbytes = n / (uint32_t)V * 16u;
+    const __amdgpu_buffer_rsrc_t rb = block_rsrc(chunk_ptr(base, off, ES), nbytes);
+    // ---- thresholds
+    {
+        int r = 0;
+        for (uint32_t mm = m; mm != 0u; mm &= mm - 1u, ++r) {
+            if (r % NW != wave)
+                continue;
+            const int i = __builtin_ctz(mm);
+            if (ctr != nullptr && lane == 0)  // the expert's bytes, counted at their first read
+                atomicAdd(&ctr[(((blockIdx.x * 4u) + (uint32_t)wave) & 7u) << 5 | (uint32_t)i],
+                          (unsigned long long)nbytes);
+            if (k == n) {  // keep every nonzero
+                if (lane == 0)
+                    s_tau[r] = 1u;
+                continue;
+            }
+            const __amdgpu_buffer_rsrc_t re = block_rsrc(src.expert(i, r, b, off, n, ES), nbytes);
+            float d[E];
+            float p = 0.0f;
+#pragma unroll
+            for (int r0 = 0; r0 < R; r0 += RG) {
+                if (r0 > 0)
+                    __builtin_amdgcn_sched_barrier(0);  // the compiler would hoist these loads and spill
+                uint4 xb[RG], xe[RG];
+#pragma unroll
+                for (int q = 0; q < RG; ++q) {
+                    if (!DELTA)
+                        xb[q] = bld16(rb, (uint32_t)((r0 + q) * 64 + lane) * 16u);
+                    xe[q] = bld16(re, (uint32_t)((r0 + q) * 64 + lane) * 16u);
+                }
+#pragma unroll
+                for (int q = 0; q < RG; ++q) {
+                    float fb[V], fe[V];
+                    if (!DELTA)
+                        Fmt<DT>::unpack(xb[q], fb);
+                    Fmt<DT>::unpack(xe[q], fe);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const int e = (r0 + q) * V + v;
+                        d[e] = DELTA ? fe[v] : fe[v] - fb[v];  // padding: 0 - 0
+                        if (r0 == 0 && q == 0)  // a part of the unit is enough for the guess
+                            p = fmaf(d[e], d[e], p);
+                    }
+                }
+            }
+            p = wave_sum_f32(p);
+            // the guess only decides which values the first pass counts
+            const float gf = gcoef * __builtin_amdgcn_sqrtf(p * __builtin_amdgcn_rcpf((float)min(n, 64u * V)));
+            const uint32_t th = wave_kth_largest<E>(reinterpret_cast<char*>(&rows[0][0]), wave * ties::NB * 4, d, k,
+                                                    lane, (gcoef > 0.0f) ? __float_as_uint(gf) : 0u);
+            if (lane == 0)
+                s_tau[r] = max(th, 1u);  // a kept delta is not zero
+            wave_lds_sync();  // the row is the next unit's
+        }
+    }
+    __syncthreads();
+    // ---- merge
+    const __amdgpu_buffer_rsrc_t ro = block_rsrc(static_cast<char*>(out) + off * ES, nbytes);
+    constexpr uint32_t c16 = 0x10000u;
+#pragma unroll 1
+    for (uint32_t c0 = (uint32_t)wave * 64u * CPT; c0 * 16u < nbytes; c0 += 64u * NW * CPT) {
+        uint32_t bo[CPT];
+        uint4 xr[CPT];
+#pragma unroll
+        for (int q = 0; q < CPT; ++q) {
+            bo[q] = (c0 + (uint32_t)(q * 64 + lane)) * 16u;
+            xr[q] = bld16s(rb, bo[q]);
+        }
+        float x0[EM], ps[EM], ns[EM];
+        uint32_t cpn[EM];
+#pragma unroll
+        for (int e = 0; e < EM; ++e) {
+            ps[e] = 0.0f;
+            ns[e] = 0.0f;
+            cpn[e] = 0u;
+        }
+        uint4 nx[CPT];  // the next expert's chunks, in flight
+        uint32_t mm = m;
+        auto fetch = [&](int r) {
+            const __amdgpu_buffer_rsrc_t re = block_rsrc(src.expert(__builtin_ctz(mm), r, b, off, n, ES), nbytes);
+#pragma unroll
+            for (int q = 0; q < CPT; ++q)
+                nx[q] = bld16s(re, bo[q]);
+        };
+        if (mm != 0u)
+            fetch(0);
+#pragma unroll
+        for (int q = 0; q < CPT; ++q)
+            Fmt<DT>::unpack(xr[q], &x0[q * V]);
+        for (int r = 0; mm != 0u; ++r) {
+            float x[EM];
+#pragma unroll
+            for (int q = 0; q < CPT; ++q)
+                Fmt<DT>::unpack(nx[q], &x[q * V]);
+            mm &= mm - 1u;
+            if (mm != 0u)
+                fetch(r + 1);
+            const float tauf = __uint_as_float(uniform_u32(s_tau[r]));
+#pragma unroll
+            for (int e = 0; e < EM; e += 2)
+                ties_fold2(DELTA ? x[e] : x[e] - x0[e], DELTA ? x[e + 1] : x[e + 1] - x0[e + 1], tauf, c16, ps[e],
+                           ns[e], cpn[e], ps[e + 1], ns[e + 1], cpn[e + 1]);
+        }
+        float mean[EM];
+        ties_elect_mean<EM>(ps, ns, cpn, mean, lane);
+#pragma unroll
+        for (int q = 0; q < CPT; ++q) {
+            float y[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                y[v] = fmaf(lambda, mean[q * V + v], x0[q * V + v]);
+            bst16s(ro, bo[q], Fmt<DT>::pack(y));  // dropped past the block's end
+        }
+    }
+}
+
 template <int DT, class Src>
 hipError_t launch_ties_typed(const BlockTable& bt, const MergeArgs& a, const Src& src, const void* base, int K,
                              const uint32_t* mask, int64_t nb, void* out, unsigned long long* ctr, hipStream_t s)
@@ -728,6 +885,46 @@ hipError_t launch_ties_typed(const BlockTable& bt, const MergeArgs& a, const Src
     // the first histogram pass's guess at tau: 0.8 of the rho-tail quantile
     // of a normal with the deltas' RMS, as in the catalog pass
     const float gcoef = (float)(0.8 * normal_two_sided_quantile(a.density));
+    // Select-then-merge for experts in device memory, except at most four
+    // experts on blocks over 2048 elements.  4 layers of the Qwen2.5-1.5B
+    // shape, k_merge_ties -> k_ties_two, us: K = 4, B = 50%, bf16 blocks of 512 /
+    // 1024 / 2048 / 4096: 2222 -> 549, 1206 -> 479, 656 -> 464, 409 (500), fp32:
+    // 2545 -> 833, 1397 -> 733, 807 -> 780, 638 (864); K = 8, B = 25%, bf16: 5817 ->
+    // 563, 2955 -> 481, 1509 -> 472, 835 -> 507, fp32: 6449 -> 891, 3438 -> 781,
+    // 1807 -> 820, 1046 -> 871.  The second read would cross PCIe for pinned experts.
+    if (!a.pcie && (K > ties::GS || bt.max_len <= 2048)) {
+        auto go = [&](auto kern, int nw) {
+            hipLaunchKernelGGL(kern, grid, dim3(64 * nw), 0, s, src, base, mask, bt.d_off, bt.d_len, a.density, n_full,
+                               k_full, a.lambda, kmask, out, ctr, gcoef);
+        };
+        // Rows of 64 chunks per unit from the layout's longest block.  Waves per
+        // workgroup: the fewer, the fewer idle at the barrier; the more, the
+        // less one wave merges alone (bf16 512-element blocks, K = 4: one / two /
+        // four waves 549 / 661 / 907 us; fp32 4096: 1072 / 936 / 864 us)
+#define MP_TWO(RV, NWV, WV)                                                                                            \
+    (a.bsub == 0.0f ? go(k_ties_two<DT, RV, NWV, WV, true, Src>, NWV) : go(k_ties_two<DT, RV, NWV, WV, false, Src>, NWV))
+        if constexpr (DT == 1) {
+            if (bt.max_len <= 512)
+                MP_TWO(1, 1, 6);
+            else if (bt.max_len <= 1024)
+                MP_TWO(2, 1, 6);
+            else if (bt.max_len <= 2048)
+                MP_TWO(4, 2, 6);
+            else
+                MP_TWO(8, 2, 5);
+        } else {
+            if (bt.max_len <= 512)
+                MP_TWO(2, 2, 6);
+            else if (bt.max_len <= 1024)
+                MP_TWO(4, 2, 6);
+            else if (bt.max_len <= 2048)
+                MP_TWO(8, 4, 6);
+            else
+                MP_TWO(16, 4, 4);
+        }
+#undef MP_TWO
+        return hipGetLastError();
+    }
     if (K <= ties::GS)
         hipLaunchKernelGGL((k_merge_ties<DT, false, Src>), grid, dim3(ties::NT), 0, s, src, base, mask, bt.d_off,
                            bt.d_len, a.density, n_full, k_full, a.lambda, kmask, out, ctr, a.bsub, gcoef);

@@ -217,6 +217,7 @@ struct MergeArgs {
     uint32_t seed = 0;
     const uint32_t* tau = nullptr;  // TIES_TAU: per-unit thresholds [G*K]
     float bsub = 1.0f;  // d = x_i - bsub * x_0: 1 for fine-tuned weights, 0 for explicit deltas
+    bool pcie = false;  // the experts are pinned host memory, read over PCIe: every byte once
 };
 
 hipError_t launch_merge(const BlockTable& bt, const MergeArgs& a, const void* base,

@@ -60,3 +60,12 @@ def test_trim_explicit_deltas(mp, dtype):  # noqa: F811
         _say(f"case deltas {dtype} block {be} K {K}")
         _run_all(mp, spec, base, exps, "ties_tau", [0.5], delta=True, density=0.3, lam=1.0)
         _run_all(mp, spec, base, exps, "ties", [0.5], delta=True, density=0.3, lam=1.0)
+
+
+@pytest.mark.parametrize("be,K", [(512, 3), (1024, 6), (4096, 9)])
+def test_in_merge_trim_from_pinned_experts(mp, be, K):  # noqa: F811
+    """Pinned experts keep the form that reads every byte once, also where
+    device experts take the one that reads a block twice."""
+    spec, base, exps = _spread_family(be, "bf16", K, seed=7 * be + K)
+    _say(f"case pinned block {be} K {K}")
+    _run_all(mp, spec, base, exps, "ties", [0.4, 1.0], residency=mp.MP_HOST_PINNED, density=0.2, lam=1.0)
