@@ -235,7 +235,7 @@ int get_table(const mp_layout* L, int esize, BlockTable** out)
     std::vector<uint64_t> tnumel(L->numel, L->numel + L->n_tensors);
     for (int64_t a = 0; a < G;) {
         int64_t z = a + 1;
-        while (z < G && z - a < kChunkBlocks && tens[(size_t)z] == tens[(size_t)a])
+        while (z < G && z - a < run_blocks(L->block_elems) && tens[(size_t)z] == tens[(size_t)a])
             ++z;
         chunks.push_back(make_uint4((uint32_t)a, (uint32_t)z, tens[(size_t)a], 0u));
         a = z;

@@ -28,7 +28,7 @@
 // takes whole layouts with blocks over 4096 elements or without room for the
 // lists, and the pairs that the first route left (the host, which waits for the
 // call anyway, sees their number and launches it only then):
-//   k_tt_hist     one workgroup per (run of <= 16 consecutive blocks of one
+//   k_tt_hist     one workgroup per (run of consecutive blocks of one
 //                 tensor, expert): LDS histogram of the digit of the
 //                 elements that match the prefix fixed so far, nonzero bins
 //                 added to the pair's global histogram.  Each XCD takes a
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, 
         return;
     const int tid = threadIdx.x;
     // nothing to count when the expert has no selected block in the run
-    static_assert(kChunkBlocks <= kTH, "a thread per block of a run");
+    static_assert(kMaxRunBlocks <= kTH, "a thread per block of a run");
     if (!__syncthreads_or(tid < (int)(ch.y - ch.x) && ((mask[ch.x + (uint32_t)tid] >> i) & 1u)))
         return;
     for (int q = tid; q < kDigBins * kCopies / 4; q += kTH)
@@ -291,7 +291,8 @@ __global__ __launch_bounds__(kTT) void k_tt_sample(const void* __restrict__ base
                                                    const uint64_t* __restrict__ boff,
                                                    const uint32_t* __restrict__ blen,
                                                    const uint32_t* __restrict__ mask, uint32_t n_runs, int T,
-                                                   uint32_t segc, const uint4* __restrict__ state,
+                                                   uint32_t run_blocks, uint32_t segc,
+                                                   const uint4* __restrict__ state,
                                                    const uint4* __restrict__ br, uint32_t* __restrict__ hist,
                                                    uint4* __restrict__ cnt)
 {
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(kTT) void k_tt_sample(const void* __restrict__ base
     // (run, share of its slices) pairs in order, kAhead of them loaded at once:
     // one at a time the pass was a chain of latencies
     constexpr uint32_t kAhead = 4u;
-    const uint32_t nq = ((uint32_t)kChunkBlocks * segc + kTT - 1u) / kTT, steps = (r1 - r0) * nq;
+    const uint32_t nq = (run_blocks * segc + kTT - 1u) / kTT, steps = (r1 - r0) * nq;
     uint32_t cur = 0xffffffffu;  // the tensor whose counts h holds
     for (uint32_t x0 = 0u; x0 < steps; x0 += kAhead) {
         uint4 ch[kAhead], re[kAhead], rb[kAhead];
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(kTT) void k_tt_sample(const void* __restrict__ base
         for (uint32_t a = 0u; a < kAhead; ++a) {
             const uint32_t x = min(x0 + a, steps - 1u);
             ch[a] = chunks[r0 + x / nq];
-            const uint32_t q = x % nq * kTT + tid, nb = ch[a].y - ch[a].x;  // at most kChunkBlocks
+            const uint32_t q = x % nq * kTT + tid, nb = ch[a].y - ch[a].x;  // at most run_blocks
             const uint32_t g = min(ch[a].x + q / segc, ch[a].y - 1u), nch = blen[g] / V;
             uint32_t c = (g % kSampleShare) * segc + q % segc;
             if (nch <= (g % kSampleShare) * segc)
@@ -346,9 +347,9 @@ __global__ __launch_bounds__(kTT) void k_tt_sample(const void* __restrict__ base
             if (cur != ch[a].z && cur != 0xffffffffu)
                 tt_flush_sample(h, hist + ((size_t)i * T + cur) * kDigBins);
             cur = ch[a].z;
-            if (LV == 0 && tid < 64u) {
+            if (LV == 0) {
                 const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(n[a]), 63);
-                if (tid == 0u && sum != 0u)
+                if ((tid & 63u) == 0u && sum != 0u)
                     atomicAdd(&cnt[pq].x, sum);
             }
             uint32_t lo = 0u, width = 0x80000000u, sh = 20u;
@@ -482,13 +483,14 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
                                                  const uint4* __restrict__ state, const uint4* __restrict__ br, int T,
                                                  uint32_t* __restrict__ hist, uint4* __restrict__ cnt,
                                                  uint32_t* __restrict__ list, const uint32_t* __restrict__ g0,
-                                                 const uint64_t* __restrict__ tnumel, uint32_t lwords,
+                                                 const uint64_t* __restrict__ tnumel, uint32_t lwords, uint32_t cpb,
                                                  uint32_t n_pairs, uint32_t per_xcd)
 {
     constexpr int V = Fmt<DT>::V;
     __shared__ __align__(16) uint32_t h[kScanBins * kScanCop];
     __shared__ uint32_t lst[kScanList];
     __shared__ uint32_t s_n, s_at, s_above;
+    __shared__ unsigned long long s_sel[kTT / 64];  // the run's selected blocks
     const uint32_t pr = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (pr >= n_pairs)
         return;
@@ -498,8 +500,12 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
     if (state[pq].z != 0u)
         return;
     const int tid = threadIdx.x;
-    static_assert(kChunkBlocks <= kTT, "a thread per block of a run");
-    if (!__syncthreads_or(tid < (int)(ch.y - ch.x) && ((mask[ch.x + (uint32_t)tid] >> i) & 1u)))
+    static_assert(kMaxRunBlocks <= kTT, "a thread per block of a run");
+    const bool selected = tid < (int)(ch.y - ch.x) && ((mask[ch.x + (uint32_t)tid] >> i) & 1u);
+    const unsigned long long sel = __ballot(selected);
+    if ((tid & 63) == 0)
+        s_sel[tid >> 6] = sel;
+    if (!__syncthreads_or(selected))
         return;
     const uint4 b = br[pq];
     const uint32_t lo = b.x, width = b.y, sh = b.z, b0 = lo >> sh, hi = lo + width;
@@ -515,48 +521,75 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
     __syncthreads();
     const uint32_t cp = (uint32_t)(tid % kScanCop);
     uint32_t above = 0u;
-    for (uint32_t g = ch.x; g < ch.y; ++g) {
-        if (!((mask[g] >> i) & 1u))
-            continue;
-        const uint64_t off = boff[g];
-        const uint32_t nch = blen[g] / V;
+    // one chunk's elements
+    auto take = [&](const uint4& e16, const uint4& b16) {
+        float fe[V], fb[V];
+        Fmt<DT>::unpack(e16, fe);
+        if (!DELTA)
+            Fmt<DT>::unpack(b16, fb);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const uint32_t mg = __float_as_uint(DELTA ? fe[v] : fe[v] - fb[v]) & 0x7fffffffu;
+            above += mg >= hi ? 1u : 0u;
+            if (mg - lo < width) {
+                atomicAdd(&h[((mg >> sh) - b0) * kScanCop + cp], 1u);
+                if ((mg & low) != 0u) {
+                    const uint32_t at = atomicAdd(&s_n, 1u);
+                    if (at < kScanList) {
+                        lst[at] = mg;
+                    } else {
+                        const uint32_t to = atomicAdd(&cnt[pq].z, 1u);
+                        if (to < cap)
+                            glist[to] = mg;
+                    }
+                }
+            }
+        }
+    };
+    if (cpb >= 2u * kTT) {  // blocks that give every thread two chunks, one after another
+        for (uint32_t g = ch.x; g < ch.y; ++g) {
+            if (!((mask[g] >> i) & 1u))
+                continue;
+            const uint64_t off = boff[g];
+            const uint32_t nch = blen[g] / V;
+            const uint4* pe = chunk_ptr(ex.p[i], off, Fmt<DT>::esize);
+            const uint4* pb = chunk_ptr(base, off, Fmt<DT>::esize);
+            for (uint32_t c0 = tid; c0 < nch; c0 += 2 * kTT) {
+                uint4 re[2], rb[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const uint32_t c = c0 + (uint32_t)(u * kTT);
+                    re[u] = c < nch ? ld16s(pe + c) : make_uint4(0u, 0u, 0u, 0u);
+                    rb[u] = (!DELTA && c < nch) ? pb[c] : make_uint4(0u, 0u, 0u, 0u);  // cached: the run's other experts read it too
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (c0 + (uint32_t)(u * kTT) < nch)
+                        take(re[u], rb[u]);
+            }
+        }
+    } else {
+        // short blocks: the run is one contiguous range of chunks, shared out
+        // without regard to blocks (one block at a time leaves three quarters
+        // of the threads without a chunk at 512 bf16 elements)
+        const uint64_t off = boff[ch.x];
+        const uint32_t nch = (ch.y - 1u - ch.x) * cpb + blen[ch.y - 1u] / V;
         const uint4* pe = chunk_ptr(ex.p[i], off, Fmt<DT>::esize);
         const uint4* pb = chunk_ptr(base, off, Fmt<DT>::esize);
         for (uint32_t c0 = tid; c0 < nch; c0 += 2 * kTT) {
             uint4 re[2], rb[2];
+            bool in[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const uint32_t c = c0 + (uint32_t)(u * kTT);
-                re[u] = c < nch ? ld16s(pe + c) : make_uint4(0u, 0u, 0u, 0u);
-                rb[u] = (!DELTA && c < nch) ? pb[c] : make_uint4(0u, 0u, 0u, 0u);  // cached: the run's other experts read it too
+                const uint32_t c = c0 + (uint32_t)(u * kTT), j = c / cpb;
+                in[u] = c < nch && ((s_sel[j / 64u % (kTT / 64)] >> (j % 64u)) & 1ull);
+                re[u] = in[u] ? ld16s(pe + c) : make_uint4(0u, 0u, 0u, 0u);
+                rb[u] = (!DELTA && in[u]) ? pb[c] : make_uint4(0u, 0u, 0u, 0u);
             }
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                if (c0 + (uint32_t)(u * kTT) >= nch)
-                    continue;
-                float fe[V], fb[V];
-                Fmt<DT>::unpack(re[u], fe);
-                if (!DELTA)
-                    Fmt<DT>::unpack(rb[u], fb);
-#pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    const uint32_t mg = __float_as_uint(DELTA ? fe[v] : fe[v] - fb[v]) & 0x7fffffffu;
-                    above += mg >= hi ? 1u : 0u;
-                    if (mg - lo < width) {
-                        atomicAdd(&h[((mg >> sh) - b0) * kScanCop + cp], 1u);
-                        if ((mg & low) != 0u) {
-                            const uint32_t at = atomicAdd(&s_n, 1u);
-                            if (at < kScanList) {
-                                lst[at] = mg;
-                            } else {
-                                const uint32_t to = atomicAdd(&cnt[pq].z, 1u);
-                                if (to < cap)
-                                    glist[to] = mg;
-                            }
-                        }
-                    }
-                }
-            }
+            for (int u = 0; u < 2; ++u)
+                if (in[u])
+                    take(re[u], rb[u]);
         }
     }
     above = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(above), 63);
@@ -737,11 +770,12 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
         const uint32_t lwords = (uint32_t)bt.tt_words;
         auto sample = [&](auto kern) {
             hipLaunchKernelGGL(kern, sgrid, dim3(kTT), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask,
-                               n_runs, T, segc, state, br, hist, cnt);
+                               n_runs, T, (uint32_t)run_blocks(bt.block_elems), segc, state, br, hist, cnt);
         };
         auto scan = [&](auto kern) {
             hipLaunchKernelGGL(kern, hgrid, dim3(kTT), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask, state,
-                               br, T, hist, cnt, list, bt.d_g0, bt.d_tnumel, lwords, n_pairs, per_xcd);
+                               br, T, hist, cnt, list, bt.d_g0, bt.d_tnumel, lwords, (uint32_t)bt.block_elems / v, n_pairs,
+                               per_xcd);
         };
         if (bt.dtype == 0)
             delta ? sample(k_tt_sample<0, true, 0>) : sample(k_tt_sample<0, false, 0>);

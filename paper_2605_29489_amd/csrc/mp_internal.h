@@ -48,7 +48,7 @@ struct BlockTable {
     uint32_t* d_len = nullptr;     // elements in the block
     uint32_t* d_tensor = nullptr;  // tensor id
     uint64_t* d_elem0 = nullptr;   // index of the block's first element inside its tensor
-    // runs of at most kChunkBlocks consecutive blocks of one tensor: {g0, g1 (end), tensor, 0}
+    // runs of at most run_blocks(block_elems) consecutive blocks of one tensor: {g0, g1 (end), tensor, 0}
     int64_t n_chunks = 0;
     uint4* d_chunk = nullptr;
     uint64_t* d_tnumel = nullptr;  // elements per tensor [n_tensors]
@@ -63,7 +63,15 @@ struct BlockTable {
     bool tlen_fits = true;
 };
 
-constexpr int kChunkBlocks = 16;
+// Blocks of a run of the tensor-scope TIES passes: 64K elements' worth, so that
+// what a run costs (clearing and adding up its bins) is spread over as many
+// elements for short blocks as for long ones.
+constexpr int kMaxRunBlocks = 256;
+constexpr int64_t run_blocks(int64_t block_elems)
+{
+    const int64_t n = 65536 / block_elems;
+    return n < 16 ? 16 : n > kMaxRunBlocks ? kMaxRunBlocks : n;
+}
 
 // Device control block of the plan (see k_plan.hip).
 struct PlanCtl;
