@@ -307,35 +307,37 @@ __device__ inline void ties_elect_mean(const float (&ps)[E], const float (&ns)[E
 // Two deltas d0, d1 folded into their elements' TIES state with threshold
 // tau: keep d iff d >= tau (positive) or -d >= tau (negative); ps sums the
 // kept positive deltas, ns the kept negative ones, cpn counts them (low half
-// positive, high half negative).  Eight instructions per delta, the positive
-// test being the carry into the count's add (the compiler's own form takes
-// ten).  Every lane mask is read at least three instructions after the
-// compare that writes it (a VALU write of an SGPR needs two wait states
-// before a VALU reads it).  c16 holds 0x10000.
+// positive, high half negative).  Six vector instructions per delta: each test
+// narrows the execution mask to the lanes that keep d, which then add to the
+// sum and the count; lanes that do not keep it are left as they are, which is
+// what adding +0 gave (the sums are never -0).  Selecting d or 0 and adding in
+// every lane took eight.  The mask is restored; the closing s_nop makes five
+// wait states from the last compare to a DPP instruction that may follow.
+// c16 holds 0x10000.
 __device__ inline void ties_fold2(float d0, float d1, float tau, uint32_t c16, float& ps0, float& ns0,
                                   uint32_t& cpn0, float& ps1, float& ns1, uint32_t& cpn1)
 {
-    uint64_t kp0, kn0, kp1, kn1, co;
-    float t0, t1;
-    asm("v_cmp_le_f32_e64 %[kp0], %[tau], %[d0]\n\t"
-        "v_cmp_le_f32_e64 %[kn0], %[tau], -%[d0]\n\t"
-        "v_cmp_le_f32_e64 %[kp1], %[tau], %[d1]\n\t"
-        "v_cmp_le_f32_e64 %[kn1], %[tau], -%[d1]\n\t"
-        "v_cndmask_b32_e64 %[t0], 0, %[d0], %[kp0]\n\t"
-        "v_cndmask_b32_e64 %[t1], 0, %[d0], %[kn0]\n\t"
-        "v_add_f32_e32 %[ps0], %[ps0], %[t0]\n\t"
-        "v_add_f32_e32 %[ns0], %[ns0], %[t1]\n\t"
-        "v_cndmask_b32_e64 %[t0], 0, %[d1], %[kp1]\n\t"
-        "v_cndmask_b32_e64 %[t1], 0, %[d1], %[kn1]\n\t"
-        "v_add_f32_e32 %[ps1], %[ps1], %[t0]\n\t"
-        "v_add_f32_e32 %[ns1], %[ns1], %[t1]\n\t"
-        "v_cndmask_b32_e64 %[t0], 0, %[c16], %[kn0]\n\t"
-        "v_cndmask_b32_e64 %[t1], 0, %[c16], %[kn1]\n\t"
-        "v_addc_co_u32_e64 %[cpn0], %[co], %[cpn0], %[t0], %[kp0]\n\t"
-        "v_addc_co_u32_e64 %[cpn1], %[co], %[cpn1], %[t1], %[kp1]"
+    uint64_t sv, tmp;
+    asm("s_mov_b64 %[sv], exec\n\t"
+        "v_cmpx_le_f32_e64 %[tmp], %[tau], %[d0]\n\t"
+        "v_add_f32_e32 %[ps0], %[ps0], %[d0]\n\t"
+        "v_add_u32_e32 %[cpn0], 1, %[cpn0]\n\t"
+        "s_mov_b64 exec, %[sv]\n\t"
+        "v_cmpx_le_f32_e64 %[tmp], %[tau], %[d1]\n\t"
+        "v_add_f32_e32 %[ps1], %[ps1], %[d1]\n\t"
+        "v_add_u32_e32 %[cpn1], 1, %[cpn1]\n\t"
+        "s_mov_b64 exec, %[sv]\n\t"
+        "v_cmpx_le_f32_e64 %[tmp], %[tau], -%[d0]\n\t"
+        "v_add_f32_e32 %[ns0], %[ns0], %[d0]\n\t"
+        "v_add_u32_e32 %[cpn0], %[c16], %[cpn0]\n\t"
+        "s_mov_b64 exec, %[sv]\n\t"
+        "v_cmpx_le_f32_e64 %[tmp], %[tau], -%[d1]\n\t"
+        "v_add_f32_e32 %[ns1], %[ns1], %[d1]\n\t"
+        "v_add_u32_e32 %[cpn1], %[c16], %[cpn1]\n\t"
+        "s_mov_b64 exec, %[sv]\n\t"
+        "s_nop 1"
         : [ps0] "+v"(ps0), [ns0] "+v"(ns0), [cpn0] "+v"(cpn0), [ps1] "+v"(ps1), [ns1] "+v"(ns1),
-          [cpn1] "+v"(cpn1), [kp0] "=&s"(kp0), [kn0] "=&s"(kn0), [kp1] "=&s"(kp1), [kn1] "=&s"(kn1),
-          [co] "=&s"(co), [t0] "=&v"(t0), [t1] "=&v"(t1)
+          [cpn1] "+v"(cpn1), [sv] "=&s"(sv), [tmp] "=&s"(tmp)
         : [d0] "v"(d0), [d1] "v"(d1), [tau] "v"(tau), [c16] "v"(c16));
 }
 
