@@ -1193,7 +1193,7 @@ static int get_lora_table(const mp_layout* L, const BlockTable& bt, const mp_lor
     }
     // the fused merge's operand-order copy of one expert: per tensor A^T
     // (columns padded to 64) then B (rows padded to 16), prep_rank values each
-    e->t.prep_rank = e->t.max_rank <= 16 ? 16u : (uint32_t)kMaxLoraRank;
+    e->t.prep_rank = e->t.max_rank <= 16 ? 16u : e->t.max_rank <= 32 ? 32u : (uint32_t)kMaxLoraRank;
     uint64_t prep = 0;
     for (LoraDesc& d : desc) {
         const uint64_t z = std::max((uint64_t)(d.cols + 63) / 64 * 64, (uint64_t)(d.rows + 15) / 16 * 16);

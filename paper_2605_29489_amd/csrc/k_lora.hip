@@ -385,11 +385,13 @@ __global__ __launch_bounds__(256) void k_lora_zero(const uint32_t* __restrict__ 
 // never written to memory.
 //
 // First k_lora_prep lays each adapter out in MFMA operand order, zero-padded
-// to the depth RM: A^T (columns padded to a multiple of 64, RM values per
-// column) and B (rows padded to a multiple of 16, RM values per row).  An
-// operand is then one unconditional 8-byte (bf16) or 4-byte (fp32) load per
-// lane, and no staging in LDS is needed.  Zero padding adds exact zero
-// products, so the sums equal the pull's.
+// to the depth RM: A^T (columns padded to a multiple of 64) and B (rows padded
+// to a multiple of 16), in groups of 16 columns or rows and 16 ranks (see
+// lora_operand).  A group is then one unconditional 8-byte (bf16) or 16-byte
+// (fp32) load per lane, and no staging in LDS is needed; more than 16 ranks
+// take group after group, each loaded while the one before computes, so every
+// depth needs the registers of one.  Zero padding adds exact zero products, so
+// the sums equal the pull's.
 //
 // k_lora_ties: one wave takes 16 rows of an adapted tensor (a quarter of a
 // 64-row band) and walks its 64-column tiles, on its own (no workgroup
@@ -420,6 +422,40 @@ constexpr int kFN = 64;  // fused tile columns (four MFMA tiles of 16)
 // contiguous across lanes.
 constexpr int kPrepCols = 128;
 
+// Operand order: of every 16 columns of A^T (or rows of B) and 16 ranks, lane
+// L's four MFMA operands lie together at 4 L, so that a wave's load of one
+// operand group is one contiguous 512 (bf16) or 1024 bytes (fp32).  Lane L has
+// column L % 16 and, with q = L / 16, depths 4q .. 4q + 3 (bf16: one 16-deep
+// MFMA) or q, 4 + q, 8 + q, 12 + q (fp32: four 4-deep ones).  With the ranks of
+// a column together, a load touched sixteen lines for 16 or 8 bytes each, and
+// beyond 16 ranks the lines came from L2 again for every group.  4 layers of
+// the Qwen2.5-1.5B shape, K = 4, that order -> this, us: fused merge (B = 50%) fp32
+// at 16 / 32 / 64 ranks 3018 -> 1500, 5637 -> 1943, 10725 -> 3022, bf16 at 64
+// 3024 -> 1386; pull and catalog fp32 2341 -> 1322, 3610 -> 1520, 6085 -> 2070,
+// bf16 at 64 1827 -> 851.
+// The o-th four operands of RM ranks, from get(column, depth): with VEC the
+// element's address, four consecutive depths together and aligned, else its
+// value.
+template <int DT, int RM, bool VEC, class Get>
+__device__ inline auto lora_operand(uint32_t o, Get get)
+{
+    const uint32_t n = o / (4u * RM) * 16u + (o & 15u), gr = o % (4u * RM) / 64u, q = (o >> 4) & 3u;
+    typename std::conditional<DT == 0, float4_t, short4_t>::type v;
+    if constexpr (VEC && DT == 1) {
+        v = *reinterpret_cast<const short4_t*>(get(n, gr * 16u + 4u * q));
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4u; ++j) {
+            const uint32_t k = gr * 16u + (DT == 0 ? 4u * j + q : 4u * q + j);
+            if constexpr (VEC)
+                v[j] = *get(n, k);
+            else
+                v[j] = get(n, k);
+        }
+    }
+    return v;
+}
+
 template <int DT, int RM>
 __global__ __launch_bounds__(256) void k_lora_prep(const LoraDesc* __restrict__ desc, ExpertPtrs ad, OutPtrs prep,
                                                    int aligned)
@@ -427,7 +463,7 @@ __global__ __launch_bounds__(256) void k_lora_prep(const LoraDesc* __restrict__ 
     using E = typename std::conditional<DT == 0, float, uint16_t>::type;
     constexpr int CV = 16 / sizeof(E);
     constexpr int RS = RM + CV;  // LDS row stride: rows stay 16-byte aligned
-    constexpr int CPC = RM / CV; // chunks per A^T column (and per B row)
+    using E4 = typename std::conditional<DT == 0, float4_t, short4_t>::type;
     __shared__ __align__(16) E T[kPrepCols * RS];
     const LoraDesc D = desc[blockIdx.x];
     const int i = blockIdx.y;
@@ -457,31 +493,46 @@ __global__ __launch_bounds__(256) void k_lora_prep(const LoraDesc* __restrict__ 
         }
         __syncthreads();
         const uint32_t ncol = min((uint32_t)kPrepCols, colsp - c0);
-        for (uint32_t c = t; c < ncol * CPC; c += 256) {
-            const uint32_t n = c / CPC, j = c % CPC;
-            reinterpret_cast<uint4*>(at + (uint64_t)(c0 + n) * RM)[j] =
-                *reinterpret_cast<const uint4*>(&T[n * RS + j * CV]);
-        }
+        for (uint32_t o = t; o < ncol * (RM / 4); o += 256)
+            *reinterpret_cast<E4*>(at + (uint64_t)c0 * RM + 4u * o) =
+                lora_operand<DT, RM, true>(o, [&](uint32_t n, uint32_t k) { return &T[n * RS + k]; });
     }
     if (c0 < rowsp) {
         // B's rows c0 .. with RM values each (zeros past the rank and the rows)
         const uint32_t nrow = min((uint32_t)kPrepCols, rowsp - c0);
-        if (aligned != 0 && D.rank == (uint32_t)RM && D.b_off % CV == 0) {
-            const uint4* src = reinterpret_cast<const uint4*>(B + (uint64_t)c0 * RM);
-            uint4* dst = reinterpret_cast<uint4*>(bp + (uint64_t)c0 * RM);
-            for (uint32_t c = t; c < nrow * CPC; c += 256)
-                dst[c] = (c0 + c / CPC < D.rows) ? src[c] : make_uint4(0u, 0u, 0u, 0u);
+        if (aligned != 0 && D.rank == (uint32_t)RM && D.b_off % CV == 0 && c0 + nrow <= D.rows) {
+            for (uint32_t o = t; o < nrow * (RM / 4); o += 256)
+                *reinterpret_cast<E4*>(bp + (uint64_t)c0 * RM + 4u * o) = lora_operand<DT, RM, true>(
+                    o, [&](uint32_t n, uint32_t k) { return B + (uint64_t)(c0 + n) * RM + k; });
         } else {
-            for (uint32_t c = t; c < nrow * RM; c += 256) {
-                const uint32_t r = c0 + c / RM, k = c % RM;
-                bp[(uint64_t)c0 * RM + c] = (k < D.rank && r < D.rows) ? B[(uint64_t)r * D.rank + k] : E(0);
-            }
+            for (uint32_t o = t; o < nrow * (RM / 4); o += 256)
+                *reinterpret_cast<E4*>(bp + (uint64_t)c0 * RM + 4u * o) =
+                    lora_operand<DT, RM, false>(o, [&](uint32_t n, uint32_t k) {
+                        return (k < D.rank && c0 + n < D.rows) ? B[(uint64_t)(c0 + n) * D.rank + k] : E(0);
+                    });
         }
     }
 }
 
+// One operand group (16 ranks) of a 16 x 64 tile, in increasing depth.
+template <int DT, class Op, int N>
+__device__ inline void lora_mfma(const Op (&a)[N], const Op& b, float4_t (&acc)[N])
+{
+    if constexpr (DT == 1) {
+#pragma unroll
+        for (int ct = 0; ct < N; ++ct)
+            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[ct], b, acc[ct], 0, 0, 0);
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int ct = 0; ct < N; ++ct)
+                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ct][ks], b[ks], acc[ct], 0, 0, 0);
+    }
+}
+
 template <int DT, int RM>
-__global__ __launch_bounds__(64, (DT == 1 && RM == 16) ? 4 : (DT == 0 && RM == 64) ? 1 : 2) void k_lora_ties(const LoraDesc* __restrict__ desc, int n_desc, uint32_t n_bands,
+__global__ __launch_bounds__(64, DT == 0 ? 2 : RM <= 32 ? 4 : 3) void k_lora_ties(const LoraDesc* __restrict__ desc, int n_desc, uint32_t n_bands,
                                                   uint32_t bpx, ExpertPtrs prep, const void* __restrict__ base,
                                                   const uint32_t* __restrict__ mask,
                                                   const uint32_t* __restrict__ tau, int K, uint32_t kmask,
@@ -490,15 +541,14 @@ __global__ __launch_bounds__(64, (DT == 1 && RM == 16) ? 4 : (DT == 0 && RM == 6
                                                   const uint32_t* __restrict__ zlen)
 {
     using E = typename std::conditional<DT == 0, float, uint16_t>::type;
-    constexpr int KS = DT == 0 ? 4 : 16;  // MFMA depth
     constexpr int CV = 16 / sizeof(E);    // elements per 16-byte chunk
-    constexpr int NKS = RM / KS;          // MFMA depth steps
+    constexpr int NG = RM / 16;           // operand groups of 16 ranks, one after another
     constexpr int CPR = kFN / CV;         // chunks per strip row
     constexpr int NS = 16 * CPR / 64;     // chunk slots per lane
     constexpr int EL = NS * CV;           // elements per lane (16)
     constexpr int OSR = kFN + CV;         // strip row stride (elements; rows stay 16-byte aligned)
     constexpr int FC = kFN / 16;          // MFMA tiles per tile
-    using AOp = typename std::conditional<DT == 0, float, short4_t>::type;
+    using AOp = typename std::conditional<DT == 0, float4_t, short4_t>::type;  // a group's operands
     __shared__ __align__(16) E ow[16 * OSR];
     if (blockIdx.x >= 32u * bpx) {
         // the workgroups past the bands take the blocks of tensors without an
@@ -556,11 +606,10 @@ __global__ __launch_bounds__(64, (DT == 1 && RM == 16) ? 4 : (DT == 0 && RM == 6
     E* __restrict__ xo = static_cast<E*>(out) + D.toff + (uint64_t)r0 * cols;
     const uint32_t* __restrict__ mk = mask + D.g0;
     const uint32_t* __restrict__ tk = tau + (uint64_t)D.g0 * (uint32_t)K;
-    // operands: A^T column n0 + ct*16 + lane%16, depth k0 + (bf16) 4*(lane/16) .. +3
-    // or (fp32) lane/16; B row r0 + lane%16, the same depths
-    const uint32_t dk = DT == 1 ? 4u * (uint32_t)(lane >> 4) : (uint32_t)(lane >> 4);
-    const uint64_t aoff = D.at_off + (uint64_t)(lane & 15) * RM + dk;
-    const uint64_t boff = D.bp_off + (uint64_t)(r0 + (uint32_t)(lane & 15)) * RM + dk;
+    // operands in the order of lora_operand: 16 columns from n0 + ct*16, 16
+    // rows from r0
+    const uint64_t aoff = D.at_off + 4u * (uint32_t)lane;
+    const uint64_t boff = D.bp_off + (uint64_t)r0 * RM + 4u * (uint32_t)lane;
     // the lane's chunk slots: strip row srow, column scol; element e of the
     // tensor in block lb, lr elements in
     uint32_t srow[NS], scol[NS], lb[NS], lr[NS];
@@ -590,25 +639,24 @@ __global__ __launch_bounds__(64, (DT == 1 && RM == 16) ? 4 : (DT == 0 && RM == 6
         return wave_or_u32(o);
     };
     struct Ops {
-        AOp a[NKS][FC];
-        AOp b[NKS];
+        AOp a[FC];
+        AOp b;
         uint32_t t[NS];
     };
-    // expert i's operands for the tile at column n0, and its thresholds for
-    // the tile's blocks b
-    auto load_ops = [&](int i, uint32_t n0, const uint32_t (&b)[NS], Ops& o) {
-        const E* __restrict__ pa = static_cast<const E*>(prep.p[i]) + aoff + (uint64_t)n0 * RM;
-        const E* __restrict__ pb = static_cast<const E*>(prep.p[i]) + boff;
+    // group gr of expert i's operands for the tile at column n0, and with the
+    // last one its thresholds for the tile's blocks b
+    auto load_ops = [&](int i, uint32_t n0, int gr, const uint32_t (&b)[NS], Ops& o) {
+        const E* __restrict__ pa = static_cast<const E*>(prep.p[i]) + aoff + (uint64_t)n0 * RM + gr * 256;
+        const E* __restrict__ pb = static_cast<const E*>(prep.p[i]) + boff + gr * 256;
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
+        for (int ct = 0; ct < FC; ++ct)
+            o.a[ct] = *reinterpret_cast<const AOp*>(pa + ct * 16 * RM);
+        o.b = *reinterpret_cast<const AOp*>(pb);
+        if (gr == NG - 1) {
 #pragma unroll
-            for (int ct = 0; ct < FC; ++ct)
-                o.a[ks][ct] = *reinterpret_cast<const AOp*>(pa + ct * 16 * RM + ks * KS);
-            o.b[ks] = *reinterpret_cast<const AOp*>(pb + ks * KS);
+            for (int q = 0; q < NS; ++q)
+                o.t[q] = tk[(uint64_t)min(b[q], nblk - 1u) * (uint32_t)K + (uint32_t)i];
         }
-#pragma unroll
-        for (int q = 0; q < NS; ++q)
-            o.t[q] = tk[(uint64_t)min(b[q], nblk - 1u) * (uint32_t)K + (uint32_t)i];
     };
     uint32_t w[NS];
     words(0u, lb, w);
@@ -618,7 +666,7 @@ __global__ __launch_bounds__(64, (DT == 1 && RM == 16) ? 4 : (DT == 0 && RM == 6
     uint32_t pre_t = 0u;  // and their tile
     if (sel != 0u) {
         pre_i = __builtin_ctz(sel);
-        load_ops(pre_i, 0u, lb, pre);
+        load_ops(pre_i, 0u, 0, lb, pre);
     }
     for (uint32_t tn = 0; tn < tiles; ++tn) {
         const uint32_t n0 = tn * kFN;
@@ -659,35 +707,40 @@ __global__ __launch_bounds__(64, (DT == 1 && RM == 16) ? 4 : (DT == 0 && RM == 6
             const int i = __builtin_ctz(mm);
             mm &= mm - 1u;
             if (pre_i != i || pre_t != tn)  // not prefetched (wave-uniform; not expected)
-                load_ops(i, n0, lb, pre);
-            const Ops cur = pre;
-            // the following expert's operands, in flight while this one computes
+                load_ops(i, n0, 0, lb, pre);
+            float4_t acc[FC];
+            if (NG > 1) {
+#pragma unroll
+                for (int ct = 0; ct < FC; ++ct)
+                    acc[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
+            }
+            Ops cur = pre;
+            // the following group's or expert's operands, in flight while this
+            // group computes
+#pragma unroll
+            for (int gr = 0; gr + 1 < NG; ++gr) {
+                load_ops(i, n0, gr + 1, lb, pre);
+                lora_mfma<DT>(cur.a, cur.b, acc);
+                cur = pre;
+            }
             if (mm != 0u) {
                 pre_i = __builtin_ctz(mm);
                 pre_t = tn;
-                load_ops(pre_i, n0, lb, pre);
+                load_ops(pre_i, n0, 0, lb, pre);
             } else if (more) {
                 const uint32_t sn = tile_set(wn);
                 if (sn != 0u) {
                     pre_i = __builtin_ctz(sn);
                     pre_t = tn + 1;
-                    load_ops(pre_i, n0 + kFN, lbn, pre);
+                    load_ops(pre_i, n0 + kFN, 0, lbn, pre);
                 }
             }
-            float4_t acc[FC];
+            if (NG == 1) {
 #pragma unroll
-            for (int ct = 0; ct < FC; ++ct)
-                acc[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < NKS; ++ks) {
-#pragma unroll
-                for (int ct = 0; ct < FC; ++ct) {
-                    if constexpr (DT == 1)
-                        acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(cur.a[ks][ct], cur.b[ks], acc[ct], 0, 0, 0);
-                    else
-                        acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.a[ks][ct], cur.b[ks], acc[ct], 0, 0, 0);
-                }
+                for (int ct = 0; ct < FC; ++ct)
+                    acc[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
             }
+            lora_mfma<DT>(cur.a, cur.b, acc);
             // the deltas as the pull stores them: scale * acc rounded to the
             // dtype; accumulator j of tile ct is column ct*16 + 4*(lane/16) + j
             // of strip row lane % 16 (the wave's LDS operations run in order)
@@ -767,14 +820,13 @@ __global__ __launch_bounds__(64) void k_lora_pull(const LoraDesc* __restrict__ d
                                                   const uint32_t* __restrict__ mask, uint32_t block_elems)
 {
     using E = typename std::conditional<DT == 0, float, uint16_t>::type;
-    constexpr int KS = DT == 0 ? 4 : 16;
     constexpr int CV = 16 / sizeof(E);
-    constexpr int NKS = RM / KS;
+    constexpr int NG = RM / 16;  // operand groups of 16 ranks
     constexpr int CPR = kFN / CV;
     constexpr int NS = 16 * CPR / 64;
     constexpr int OSR = kFN + CV;
     constexpr int FC = kFN / 16;
-    using AOp = typename std::conditional<DT == 0, float, short4_t>::type;
+    using AOp = typename std::conditional<DT == 0, float4_t, short4_t>::type;  // a group's operands
     __shared__ __align__(16) E ow[16 * OSR];
     const int i = blockIdx.y;
     const int lane = threadIdx.x;
@@ -802,22 +854,19 @@ __global__ __launch_bounds__(64) void k_lora_pull(const LoraDesc* __restrict__ d
     const uint32_t tiles = (cols + kFN - 1) / kFN;
     const float scale = D.scale;
     E* __restrict__ xo = static_cast<E*>(dl.p[i]) + D.toff + (uint64_t)r0 * cols;
-    const uint32_t dk = DT == 1 ? 4u * (uint32_t)(lane >> 4) : (uint32_t)(lane >> 4);
-    const E* __restrict__ pa = static_cast<const E*>(prep.p[i]) + D.at_off + (uint64_t)(lane & 15) * RM + dk;
-    const E* __restrict__ pb = static_cast<const E*>(prep.p[i]) + D.bp_off + (uint64_t)(r0 + (uint32_t)(lane & 15)) * RM + dk;
-    AOp b[NKS];
+    const E* __restrict__ pa = static_cast<const E*>(prep.p[i]) + D.at_off + 4u * (uint32_t)lane;
+    const E* __restrict__ pb = static_cast<const E*>(prep.p[i]) + D.bp_off + (uint64_t)r0 * RM + 4u * (uint32_t)lane;
+    AOp b[NG];
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks)
-        b[ks] = *reinterpret_cast<const AOp*>(pb + ks * KS);
-    auto load_a = [&](uint32_t n0, AOp (&a)[NKS][FC]) {
+    for (int gr = 0; gr < NG; ++gr)
+        b[gr] = *reinterpret_cast<const AOp*>(pb + gr * 256);
+    auto load_a = [&](uint32_t n0, int gr, AOp (&a)[FC]) {
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-            for (int ct = 0; ct < FC; ++ct)
-                a[ks][ct] = *reinterpret_cast<const AOp*>(pa + (uint64_t)(n0 + ct * 16) * RM + ks * KS);
+        for (int ct = 0; ct < FC; ++ct)
+            a[ct] = *reinterpret_cast<const AOp*>(pa + (uint64_t)(n0 + ct * 16) * RM + gr * 256);
     };
-    AOp pre[NKS][FC];
-    load_a(0u, pre);
+    AOp pre[FC];
+    load_a(0u, 0, pre);
     const uint32_t cg = 4u * (uint32_t)(lane >> 4);
     // masked: the lane's chunk slots' blocks (tracked across tiles) and
     // whether expert i is selected there
@@ -857,31 +906,26 @@ __global__ __launch_bounds__(64) void k_lora_pull(const LoraDesc* __restrict__ d
             }
             if (wave_or_u32(any) == 0u) {  // nothing selected in the wave's tile: no compute, no store
                 if (tn + 1 < tiles)
-                    load_a(n0 + kFN, pre);
+                    load_a(n0 + kFN, 0, pre);
                 continue;
             }
         }
-        AOp cur[NKS][FC];
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-            for (int ct = 0; ct < FC; ++ct)
-                cur[ks][ct] = pre[ks][ct];
-        if (tn + 1 < tiles)
-            load_a(n0 + kFN, pre);
         float4_t acc[FC];
 #pragma unroll
         for (int ct = 0; ct < FC; ++ct)
             acc[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
+        for (int gr = 0; gr < NG; ++gr) {
+            AOp cur[FC];
 #pragma unroll
-            for (int ct = 0; ct < FC; ++ct) {
-                if constexpr (DT == 1)
-                    acc[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(cur[ks][ct], b[ks], acc[ct], 0, 0, 0);
-                else
-                    acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur[ks][ct], b[ks], acc[ct], 0, 0, 0);
-            }
+            for (int ct = 0; ct < FC; ++ct)
+                cur[ct] = pre[ct];
+            // the next group's (or tile's) operands, in flight meanwhile
+            if (gr + 1 < NG)
+                load_a(n0, gr + 1, pre);
+            else if (tn + 1 < tiles)
+                load_a(n0 + kFN, 0, pre);
+            lora_mfma<DT>(cur, b[gr], acc);
         }
 #pragma unroll
         for (int ct = 0; ct < FC; ++ct) {
@@ -943,11 +987,15 @@ hipError_t launch_lora(const BlockTable& bt, const LoraTable& lt, const ExpertPt
         if (bt.dtype == 0) {
             if (lt.prep_rank == 16)
                 MP_LORA_PULL(0, 16);
+            else if (lt.prep_rank == 32)
+                MP_LORA_PULL(0, 32);
             else
                 MP_LORA_PULL(0, kMaxLoraRank);
         } else {
             if (lt.prep_rank == 16)
                 MP_LORA_PULL(1, 16);
+            else if (lt.prep_rank == 32)
+                MP_LORA_PULL(1, 32);
             else
                 MP_LORA_PULL(1, kMaxLoraRank);
         }
@@ -1005,11 +1053,15 @@ hipError_t launch_lora_ties(const BlockTable& bt, const LoraTable& lt, const Exp
     if (bt.dtype == 0) {
         if (lt.prep_rank == 16)
             MP_LORA_TIES(0, 16);
+        else if (lt.prep_rank == 32)
+            MP_LORA_TIES(0, 32);
         else
             MP_LORA_TIES(0, kMaxLoraRank);
     } else {
         if (lt.prep_rank == 16)
             MP_LORA_TIES(1, 16);
+        else if (lt.prep_rank == 32)
+            MP_LORA_TIES(1, 32);
         else
             MP_LORA_TIES(1, kMaxLoraRank);
     }

@@ -639,3 +639,14 @@ def test_lora_fused_and_pulls_with_32_experts(mp, dtype):
     got = _fused(mp, spec, recs, [to_dev(a, dtype) for a in ads], to_dev(base_np, dtype), mask, tau_d, 0.9, K)
     want = oracle.merge_ties_tau(blocks, dtype, base_np, d_full, mask, tau, 0.9, delta=True)
     assert assert_merge_equal(got, want, base_np, dtype, "fused K=32") == 0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rank", [17, 31, 32])
+def test_lora_two_operand_groups(mp, dtype, rank):
+    """Ranks 17 to 32: the 32-deep operand-order copy, pulled and fused."""
+    test_lora_materialize_exact_grid_bitwise(mp, dtype, rank)
+    test_lora_fused_ties_exact_grid_bitwise(mp, dtype, rank)
+    if dtype == "bf16" and rank % 8 == 0:
+        test_lora_materialize_exact_grid_bitwise_aligned_rows(mp, rank)
+    test_lora_fused_ties_equals_pull_then_merge(mp, dtype, rank)
