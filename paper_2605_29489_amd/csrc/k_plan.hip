@@ -28,7 +28,8 @@
 // sequence and kernels that are no longer needed return at once.  What bounds
 // it is launches and dependent passes, not bytes: at 1.5M units, eight 8-bit
 // passes of one thread per block took 8.5 us each, the later rounds (reloading
-// their list in each pass) 30 us and fourteen launches in all 143 us.
+// their list in each pass) 30 us and fourteen launches in all 145 us; now 75 us,
+// seven launches, passes of 6-13 us and the later rounds 14 us.
 #include "device_common.h"
 #include "mp_internal.h"
 
@@ -649,7 +650,8 @@ __global__ __launch_bounds__(kT) void k_plan_rest(PlanCtl* ctl, const float* __r
 constexpr int kOneMax = 8192;
 
 // NT threads of PER candidates each.  A round is a chain of barriers, cheaper
-// the fewer waves there are: lists up to 1024 take four waves.
+// the fewer waves there are: lists up to 1024 take four waves (1.5M units'
+// later rounds 14 us, 21 with sixteen).
 template <bool ALL, int NT, int PER>
 __global__ __launch_bounds__(NT) void k_plan_one(PlanCtl* ctl, const float* __restrict__ sumsq, Coeffs w,
                                                     uint32_t flags, int K, const uint32_t* __restrict__ blen,
