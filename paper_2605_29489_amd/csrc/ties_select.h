@@ -247,21 +247,43 @@ __device__ inline uint32_t window_floor(int wb)
 
 // Key of bin 0 of the window anchored at the block maximum's pattern: the
 // top bin holds the last key of the maximum's binade.
-__device__ inline int window_base(uint32_t bmax)
+__host__ __device__ constexpr int window_base(uint32_t bmax)
 {
     using namespace ties;
     return (int)((bmax >> 23) << MB) + (1 << MB) - NBIN;
 }
 
-// Byte offset term of window_add for the lane's copy, given the block
-// maximum's pattern: key kk goes to ((kk - wb) * NC + (lane % NC)) * 4.
-__device__ inline uint32_t window_koff(uint32_t bmax, int lane, int* wb_out)
+// Byte offset term of window_add for the lane's copy, given the key wb of bin
+// 0: key kk goes to ((kk - wb) * NC + (lane % NC)) * 4.  It wraps (for normal
+// floats it is close to 2^32), so it is only ever added to another 32-bit
+// offset, never to a pointer.
+__host__ __device__ constexpr uint32_t window_koff_at(int wb, int lane)
 {
     using namespace ties;
-    const int wb = window_base(bmax);
-    *wb_out = wb;
     return (uint32_t)(lane & (NC - 1)) * 4u - (uint32_t)wb * (uint32_t)(4 * NC);
 }
+__device__ inline uint32_t window_koff(uint32_t bmax, int lane, int* wb_out)
+{
+    *wb_out = window_base(bmax);
+    return window_koff_at(*wb_out, lane);
+}
+
+// Byte offset in the histogram row of a magnitude pattern of the window: the
+// sum wraps back into the row.
+__host__ __device__ constexpr uint32_t window_off(uint32_t mg, uint32_t koff)
+{
+    using namespace ties;
+    return ((mg >> KS) << LG) + koff;
+}
+// first and last word of the row, at both ends of the range of patterns
+static_assert(window_off(0x7f800000u, window_koff_at(window_base(0x7f800000u), 1)) ==
+                  (ties::NBIN - (1u << ties::MB)) * 4u * ties::NC + 4u, "infinity: the top binade's first bin");
+static_assert(window_off(0x3fffffffu, window_koff_at(window_base(0x3f800000u), ties::NC - 1)) == ties::NB * 4u - 4u,
+              "the last key of the maximum's binade: the row's last word");
+static_assert(window_off((uint32_t)window_base(0x3f800000u) << ties::KS, window_koff_at(window_base(0x3f800000u), 0)) ==
+                  0u, "the window's floor: the row's first word");
+static_assert(window_off(0u, window_koff_at(window_base(1u), 0)) == (ties::NBIN - (1u << ties::MB)) * 4u * ties::NC,
+              "subnormals: the window reaches below zero, zero starts its top binade");
 
 // |x|'s pattern, formed where it is used: the rare fallbacks below do not
 // keep a second copy of the values (the compiler would otherwise share one
@@ -363,9 +385,9 @@ __device__ inline uint32_t wave_kth_largest(char* base, int row_off, const float
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const uint32_t mg = mag_bits(d[e]);
+                const uint32_t at = window_off(mg, ko);  // in 32 bits: ko wraps
                 if (mg >= fl && mg < below)
-                    atomicAdd(reinterpret_cast<uint32_t*>(base + ((mg >> KS) << LG) + ko),
-                              (mg & ((1u << KS) - 1u)) != 0u ? 0x10001u : 1u);
+                    atomicAdd(reinterpret_cast<uint32_t*>(base + at), (mg & ((1u << KS) - 1u)) != 0u ? 0x10001u : 1u);
             }
             wave_lds_sync();
             c = wave_find_window(h, r, lane);
