@@ -313,7 +313,9 @@ __device__ inline void ties_elect_mean(const float (&ps)[E], const float (&ns)[E
 // what adding +0 gave (the sums are never -0).  Selecting d or 0 and adding in
 // every lane took eight.  The mask is restored; the closing s_nop makes five
 // wait states from the last compare to a DPP instruction that may follow.
-// c16 holds 0x10000.
+// c16 holds 0x10000.  The state is written while the deltas, tau and c16 are
+// still to be read, so its registers are early-clobbered: without that a state
+// that starts with the value of an input shares the input's register.
 __device__ inline void ties_fold2(float d0, float d1, float tau, uint32_t c16, float& ps0, float& ns0,
                                   uint32_t& cpn0, float& ps1, float& ns1, uint32_t& cpn1)
 {
@@ -336,8 +338,8 @@ __device__ inline void ties_fold2(float d0, float d1, float tau, uint32_t c16, f
         "v_add_u32_e32 %[cpn1], %[c16], %[cpn1]\n\t"
         "s_mov_b64 exec, %[sv]\n\t"
         "s_nop 1"
-        : [ps0] "+v"(ps0), [ns0] "+v"(ns0), [cpn0] "+v"(cpn0), [ps1] "+v"(ps1), [ns1] "+v"(ns1),
-          [cpn1] "+v"(cpn1), [sv] "=&s"(sv), [tmp] "=&s"(tmp)
+        : [ps0] "+&v"(ps0), [ns0] "+&v"(ns0), [cpn0] "+&v"(cpn0), [ps1] "+&v"(ps1), [ns1] "+&v"(ns1),
+          [cpn1] "+&v"(cpn1), [sv] "=&s"(sv), [tmp] "=&s"(tmp)
         : [d0] "v"(d0), [d1] "v"(d1), [tau] "v"(tau), [c16] "v"(c16));
 }
 
