@@ -38,7 +38,7 @@ EXPORTS = ("mp_layout_blocks", "mp_index_blocks", "mp_index_ties", "mp_ties_tens
            "mp_merge_ties",
            "mp_merge_ties_tau", "mp_merge_dare", "mp_lora_materialize", "mp_lora_merge_ties_tau", "mp_stream_copy",
            "mp_set_stage_bytes",
-           "mp_set_workspace_limit", "mp_workspace_bytes", "mp_last_error", "mp_release")
+           "mp_set_workspace_limit", "mp_workspace_bytes", "mp_ties_tensor_left", "mp_last_error", "mp_release")
 
 
 class mp_layout(C.Structure):
@@ -116,6 +116,8 @@ def _load():
     L.mp_set_workspace_limit.restype = i32
     L.mp_workspace_bytes.argtypes = []
     L.mp_workspace_bytes.restype = u64
+    L.mp_ties_tensor_left.argtypes = []
+    L.mp_ties_tensor_left.restype = C.c_int64
     L.mp_last_error.argtypes = []
     L.mp_release.argtypes = []
     for name in ("mp_layout_blocks", "mp_index_blocks", "mp_index_ties", "mp_ties_tensor_thresholds", "mp_plan",
@@ -360,6 +362,12 @@ def mp_set_workspace_limit(nbytes: int):
 
 def mp_workspace_bytes() -> int:
     return int(lib.mp_workspace_bytes())
+
+
+def mp_ties_tensor_left() -> int:
+    """Pairs that the last ``mp_ties_tensor_thresholds`` call left to the digit
+    passes (-1: it took every pair by those)."""
+    return int(lib.mp_ties_tensor_left())
 
 
 def mp_release():

@@ -80,6 +80,7 @@ struct DeviceWs {
 };
 
 std::mutex g_mu;
+int64_t g_tt_left = -1;  // pairs the last tensor-scope threshold call left to the radix passes
 std::map<std::string, std::unique_ptr<BlockTable>> g_tables;
 std::map<int, std::unique_ptr<DeviceWs>> g_ws;
 struct LoraEntry {
@@ -114,6 +115,7 @@ void free_table(BlockTable& bt)
     (void)ws_free_r(bt.d_elem0);
     (void)ws_free_r(bt.d_chunk);
     (void)ws_free_r(bt.d_tnumel);
+    (void)ws_free_r(bt.d_tlist);
     (void)ws_free_r(bt.d_tlen);
     (void)ws_free_r(bt.d_g0);
     (void)hipSetDevice(cur);
@@ -241,10 +243,13 @@ int get_table(const mp_layout* L, int esize, BlockTable** out)
         a = z;
     }
     bt->n_chunks = (int64_t)chunks.size();
-    uint64_t most = 0;
-    for (int32_t t = 0; t < L->n_tensors; ++t)
+    uint64_t most = 0, words = 0;
+    std::vector<uint32_t> tlist((size_t)L->n_tensors + 1, 0);
+    for (int32_t t = 0; t < L->n_tensors; ++t) {
         most = std::max<uint64_t>(most, (uint64_t)L->numel[t]);
-    const uint64_t words = ties_tensor_list_words((uint64_t)L->n_tensors, (uint64_t)bt->P);
+        words += ties_tensor_room((uint64_t)L->numel[t]);
+        tlist[(size_t)t + 1] = (uint32_t)words;
+    }
     if (L->block_elems <= kTiesMaxBlock && words < (1ull << 32) && most < (1ull << 31))
         bt->tt_words = words;
     // the tensor-level plan's table
@@ -265,6 +270,7 @@ int get_table(const mp_layout* L, int esize, BlockTable** out)
             (e = ws_malloc((void**)&bt->d_elem0, sizeof(uint64_t) * (size_t)G)) != hipSuccess ||
             (e = ws_malloc((void**)&bt->d_chunk, sizeof(uint4) * chunks.size())) != hipSuccess ||
             (e = ws_malloc((void**)&bt->d_tnumel, sizeof(uint64_t) * tnumel.size())) != hipSuccess ||
+            (e = ws_malloc((void**)&bt->d_tlist, sizeof(uint32_t) * tlist.size())) != hipSuccess ||
             (e = ws_malloc((void**)&bt->d_tlen, sizeof(uint32_t) * tlen.size())) != hipSuccess ||
             (e = ws_malloc((void**)&bt->d_g0, sizeof(uint32_t) * tg0.size())) != hipSuccess) {
             free_table(*bt);
@@ -276,6 +282,7 @@ int get_table(const mp_layout* L, int esize, BlockTable** out)
             (e = hipMemcpy(bt->d_elem0, e0.data(), sizeof(uint64_t) * (size_t)G, hipMemcpyHostToDevice)) != hipSuccess ||
             (e = hipMemcpy(bt->d_chunk, chunks.data(), sizeof(uint4) * chunks.size(), hipMemcpyHostToDevice)) != hipSuccess ||
             (e = hipMemcpy(bt->d_tnumel, tnumel.data(), sizeof(uint64_t) * tnumel.size(), hipMemcpyHostToDevice)) != hipSuccess ||
+            (e = hipMemcpy(bt->d_tlist, tlist.data(), sizeof(uint32_t) * tlist.size(), hipMemcpyHostToDevice)) != hipSuccess ||
             (e = hipMemcpy(bt->d_tlen, tlen.data(), sizeof(uint32_t) * tlen.size(), hipMemcpyHostToDevice)) != hipSuccess ||
             (e = hipMemcpy(bt->d_g0, tg0.data(), sizeof(uint32_t) * tg0.size(), hipMemcpyHostToDevice)) != hipSuccess) {
             free_table(*bt);
@@ -858,6 +865,8 @@ int mp_ties_tensor_thresholds(const mp_layout* layout, const void* base, const v
             return hip_fail(e, "tensor-scope error word readback");
         if ((e = hipStreamSynchronize(s)) != hipSuccess)
             return hip_fail(e, "hipStreamSynchronize");
+        if (route != TensorTies::Left)
+            g_tt_left = route == TensorTies::Bracket ? (int64_t)ws.h_tt_err[1] : -1;
         again = route == TensorTies::Bracket && ws.h_tt_err[1] != 0u;  // pairs left to the radix passes
         route = TensorTies::Left;
     }
@@ -1428,6 +1437,12 @@ int mp_set_workspace_limit(uint64_t bytes)
     g_err.clear();
     g_ws_limit = bytes;
     return MP_OK;
+}
+
+int64_t mp_ties_tensor_left(void)
+{
+    std::lock_guard<std::mutex> lock(g_mu);
+    return g_tt_left;
 }
 
 uint64_t mp_workspace_bytes(void)

@@ -45,6 +45,7 @@
 // the pairs' holds {error, pairs left by the first route, 0, 0}.  The bracket
 // route adds per pair {lo, hi - lo, bin shift, sampled elements above hi} and
 // {selected elements, elements above hi, listed, 0}.
+#include <algorithm>
 #include <cmath>
 
 #include "device_common.h"
@@ -255,16 +256,12 @@ constexpr uint32_t kSmallTensor = 8192u;  // up to here a pair lists every eleme
 constexpr int kScanBins = 256, kScanCop = 4;
 constexpr uint32_t kScanList = 3584u;  // words of the workgroup's list (with the bins 18 KiB: eight workgroups a CU)
 
-// A pair's list: room for kSmallTensor words (every element of a small tensor)
-// and a 128th of the tensor; brackets typically hold a fraction of that, and a
-// pair that needs more takes the radix route.  first: the tensor's first
-// element in a checkpoint; the tensors before it take at most the words
-// before the offset returned.
-__device__ inline uint64_t tt_list_at(int i, uint32_t lwords, uint32_t t, uint64_t first)
+// A pair's list is words tlist[t] .. tlist[t + 1] of its expert's lwords (see
+// ties_tensor_room); a pair that needs more takes the radix route.
+__device__ inline uint32_t* tt_list(uint32_t* list, int i, uint32_t lwords, const uint32_t* tlist, uint32_t t)
 {
-    return (uint64_t)i * lwords + (uint64_t)t * kSmallTensor + first / 128u;
+    return list + (uint64_t)i * lwords + tlist[t];
 }
-__device__ inline uint32_t tt_list_cap(uint64_t numel) { return kSmallTensor + (uint32_t)(numel / 128u); }
 
 // Adds a workgroup's nonzero sample bins to the pair's histogram and clears them.
 __device__ inline void tt_flush_sample(uint32_t* h, uint32_t* __restrict__ out)
@@ -482,9 +479,8 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
                                                  const uint32_t* __restrict__ blen, const uint32_t* __restrict__ mask,
                                                  const uint4* __restrict__ state, const uint4* __restrict__ br, int T,
                                                  uint32_t* __restrict__ hist, uint4* __restrict__ cnt,
-                                                 uint32_t* __restrict__ list, const uint32_t* __restrict__ g0,
-                                                 const uint64_t* __restrict__ tnumel, uint32_t lwords, uint32_t cpb,
-                                                 uint32_t n_pairs, uint32_t per_xcd)
+                                                 uint32_t* __restrict__ list, const uint32_t* __restrict__ tlist,
+                                                 uint32_t lwords, uint32_t cpb, uint32_t n_pairs, uint32_t per_xcd)
 {
     constexpr int V = Fmt<DT>::V;
     __shared__ __align__(16) uint32_t h[kScanBins * kScanCop];
@@ -510,8 +506,8 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
     const uint4 b = br[pq];
     const uint32_t lo = b.x, width = b.y, sh = b.z, b0 = lo >> sh, hi = lo + width;
     const uint32_t low = (1u << sh) - 1u;
-    uint32_t* const glist = list + tt_list_at(i, lwords, ch.z, boff[g0[ch.z]]);
-    const uint32_t cap = tt_list_cap(tnumel[ch.z]);
+    uint32_t* const glist = tt_list(list, i, lwords, tlist, ch.z);
+    const uint32_t cap = tlist[ch.z + 1u] - tlist[ch.z];
     for (int q = tid; q < kScanBins * kScanCop; q += kTT)
         h[q] = 0u;
     if (tid == 0) {
@@ -624,9 +620,8 @@ constexpr int kPick = 1024;
 // latency that bounds it.
 __global__ __launch_bounds__(kPick) void k_tt_pick(uint4* __restrict__ state, const uint4* __restrict__ br,
                                                    const uint4* __restrict__ cnt, const uint32_t* __restrict__ hist,
-                                                   const uint32_t* __restrict__ list,
-                                                   const uint32_t* __restrict__ g0,
-                                                   const uint64_t* __restrict__ boff, uint32_t lwords,
+                                                   uint32_t* __restrict__ list,
+                                                   const uint32_t* __restrict__ tlist, uint32_t lwords,
                                                    const uint64_t* __restrict__ tnumel, int T, double density,
                                                    uint32_t* __restrict__ left)
 {
@@ -642,13 +637,13 @@ __global__ __launch_bounds__(kPick) void k_tt_pick(uint4* __restrict__ state, co
     const uint32_t k = (uint32_t)((kk >= (double)n) ? n : (uint64_t)kk);
     const uint4 b = br[q], ct = cnt[q];
     const uint32_t nl = ct.z;
-    const uint32_t* __restrict__ L = list + tt_list_at((int)(q / (size_t)T), lwords, (uint32_t)t, boff[g0[t]]);
+    const uint32_t* __restrict__ L = tt_list(list, (int)(q / (size_t)T), lwords, tlist, (uint32_t)t);
     if (tid < kScanBins)
         h[tid] = hist[q * kDigBins + (size_t)tid];
     __syncthreads();
     if (tid < 64) {
         Cut c{0u, 0u, 0u, 0u, 0u, 0u};
-        if (k > ct.y && nl <= tt_list_cap(n))
+        if (k > ct.y && nl <= tlist[t + 1] - tlist[t])
             c = wave_find_from_top(h, kScanBins - 1, k - ct.y, lane);
         if (tid == 0) {
             s_ok = c.found;
@@ -733,10 +728,20 @@ __global__ __launch_bounds__(kTT) void k_tt_expand(const uint4* __restrict__ sta
 
 }  // namespace
 
-// Words of one expert's lists over n_tensors tensors of elems elements.
-uint64_t ties_tensor_list_words(uint64_t n_tensors, uint64_t elems)
+// Room for the list of one expert's pair with a tensor of n elements.  The
+// bracket holds the sample's rank plus and minus m = 5 sqrt(r (1 - p)) + 8
+// with r = N p / kSampleShare, N <= n elements selected, p = k / N: in
+// elements 2 m kSampleShare, at most 28.3 sqrt(N) + 512 (p = 1/2), and up to a
+// sample bin at either end (for smooth data below N / 7000 together).  Nearly
+// all fp32 patterns are listed, so the room grows with the square root: 32
+// sqrt(n), the small tensors' room and a 256th.  A room of the small tensors'
+// and a 128th left every normal fp32 pair of 0.1M to 8M elements at densities
+// 0.2 to 0.8 to the radix passes: 128M elements x 2 experts in tensors of
+// 393,216 / 1M / 4M, density 0.2, 1265 / 1228 / 1214 us (three digit passes
+// alone 852 / 842 / 838).
+uint64_t ties_tensor_room(uint64_t n)
 {
-    return n_tensors * kSmallTensor + elems / 128u + 1u;
+    return std::min<uint64_t>(n, kSmallTensor + 32u * (uint64_t)std::sqrt((double)n) + n / 256u);
 }
 
 hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const ExpertPtrs& ex, int K,
@@ -774,7 +779,7 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
         };
         auto scan = [&](auto kern) {
             hipLaunchKernelGGL(kern, hgrid, dim3(kTT), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask, state,
-                               br, T, hist, cnt, list, bt.d_g0, bt.d_tnumel, lwords, (uint32_t)bt.block_elems / v, n_pairs,
+                               br, T, hist, cnt, list, bt.d_tlist, lwords, (uint32_t)bt.block_elems / v, n_pairs,
                                per_xcd);
         };
         if (bt.dtype == 0)
@@ -792,7 +797,7 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
         else
             delta ? scan(k_tt_scan<1, true>) : scan(k_tt_scan<1, false>);
         hipLaunchKernelGGL(k_tt_pick, dim3((unsigned)pairs), dim3(kPick), 0, s, state, br, cnt, hist, list,
-                           bt.d_g0, bt.d_off, lwords, bt.d_tnumel, T, density, left);
+                           bt.d_tlist, lwords, bt.d_tnumel, T, density, left);
     }
     // the radix passes: over everything, or over the pairs the bracket route left
     for (int pass = 0; pass < 3 && route != TensorTies::Bracket; ++pass) {

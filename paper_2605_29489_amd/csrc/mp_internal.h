@@ -52,8 +52,10 @@ struct BlockTable {
     int64_t n_chunks = 0;
     uint4* d_chunk = nullptr;
     uint64_t* d_tnumel = nullptr;  // elements per tensor [n_tensors]
-    // words of tensor-scope TIES's lists of one expert (0: the layout takes the radix route)
+    // tensor-scope TIES's lists of one expert: its words (0: the layout takes
+    // the radix route), and where each tensor's list starts [n_tensors + 1]
     uint64_t tt_words = 0;
+    uint32_t* d_tlist = nullptr;
     // the tensor-level plan (no block catalog): elements per tensor as u32
     // (valid when every tensor has fewer than 2^32), their distinct values,
     // and the first block of every tensor [n_tensors + 1]
@@ -148,7 +150,7 @@ enum class TensorTies { Radix, Bracket, Left };
 hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const ExpertPtrs& ex, int K,
                               const uint32_t* mask, double density, uint32_t* tau, uint32_t* hist, uint4* state,
                               uint32_t* list, TensorTies route, hipStream_t s, bool delta, bool force_no_cut);
-uint64_t ties_tensor_list_words(uint64_t n_tensors, uint64_t elems);
+uint64_t ties_tensor_room(uint64_t n);
 
 // ---------------------------------------------------------------- LoRA source (k_lora.hip)
 constexpr int kMaxLoraRank = 64;

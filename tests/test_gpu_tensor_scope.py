@@ -75,3 +75,27 @@ def test_tensor_thresholds_without_lists(mp):  # noqa: F811
     finally:
         mp.mp_set_workspace_limit(0)
     _check(mp, "bf16", be, numel, base, exps, mask, 0.3)
+
+
+def _normal(dtype, P, K, seed):
+    rng = np.random.default_rng(seed)
+    base = rng.normal(0.0, 0.02, P).astype(np.float32)
+    exps = [(base + rng.normal(0.0, 1e-3 * (1 + i), P)).astype(np.float32) for i in range(K)]
+    return (base, exps) if dtype == "f32" else (oracle.round_bf16(base), [oracle.round_bf16(x) for x in exps])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("numel", [[16_384] * 3 + [98_304, 393_216], [1 << 20, 2_359_296], [4 << 20]])
+def test_normal_deltas_leave_no_pair(mp, dtype, numel):  # noqa: F811
+    """Normal base and deltas: every bracket holds its k-th largest and fits its
+    list, at any density and share of blocks (fp32 patterns are nearly all
+    listed, so this is what the lists' room is measured by)."""
+    be, K = 4096, 2
+    base, exps = _normal(dtype, sum(numel), K, seed=len(numel))
+    G = oracle.Blocks(numel, be).G
+    half = np.random.default_rng(3).integers(0, 1 << K, G).astype(np.uint32)
+    for mask in (np.full(G, (1 << K) - 1, np.uint32), half):
+        for density in (0.05, 0.2, 0.5, 0.8):
+            _say(f"case {dtype} {numel} density {density}")
+            _check(mp, dtype, be, numel, base, exps, mask, density)
+            assert mp.mp_ties_tensor_left() == 0
