@@ -252,9 +252,17 @@ __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, c
 // ---------------------------------------------------------------- bracket route
 constexpr int kSampleShare = 32;          // the sample: a 32nd of every block
 constexpr uint32_t kSampleRuns = 8;       // runs per sampling workgroup
-constexpr uint32_t kSmallTensor = 8192u;  // up to here a pair lists every element
+constexpr uint32_t kSmallTensor = 8192u;  // a pair's list has room for so many elements at least
 constexpr int kScanBins = 256, kScanCop = 4;
-constexpr uint32_t kScanList = 3584u;  // words of the workgroup's list (with the bins 18 KiB: eight workgroups a CU)
+// Words of the workgroup's list (with the bins 18 KiB: eight workgroups a CU).
+// Up to so many selected elements a pair lists every one; beyond, listing all
+// overflows it into the pair's list, one atomic round trip after another (list
+// all up to 8,192 / up to here: 64M bf16 elements x 2 experts in tensors of
+// 8,192, all selected, density 0.2 / 0.5, 1015 / 1024 us against 454 / 443).
+constexpr uint32_t kScanList = 3584u;
+// Words of an average pair's room from which its list counts as long (tensors
+// of about 200,000 elements; see k_tt_pick).
+constexpr uint64_t kPickLong = 24576u;
 
 // A pair's list is words tlist[t] .. tlist[t + 1] of its expert's lwords (see
 // ties_tensor_room); a pair that needs more takes the radix route.
@@ -351,7 +359,8 @@ __global__ __launch_bounds__(kTT) void k_tt_sample(const void* __restrict__ base
             }
             uint32_t lo = 0u, width = 0x80000000u, sh = 20u;
             if (LV == 1) {
-                if (state[pq].z != 0u)
+                const uint4 st = state[pq];
+                if (st.z != 0u || st.y == 0u)  // decided, or every element is listed
                     continue;
                 const uint4 b = br[pq];
                 lo = b.x;
@@ -386,8 +395,10 @@ __device__ inline uint32_t tt_shift_for(uint32_t lo, uint32_t hi, uint32_t bins,
     return s;
 }
 
-// One wave per pair after sample pass LV: narrows the pair's bracket and
-// clears its sample histogram.  Pass 0 also ends the pairs that keep nothing
+// One wave per pair after sample pass LV: narrows the pair's bracket (a pair of
+// at most kScanList selected elements keeps the whole range: state.y, the
+// sampled elements, stays 0 and every element is listed) and clears its
+// histogram.  Pass 0 also ends the pairs that keep nothing
 // (k = 0: all ones) or whose k-th largest is a completed zero (fewer than k
 // elements selected: 0).
 template <int LV>
@@ -405,24 +416,27 @@ __global__ __launch_bounds__(kTT) void k_tt_bracket(uint4* __restrict__ state, u
     const uint64_t k = (kk >= (double)n) ? n : (uint64_t)kk;
     const uint32_t N = cnt[q].x;
     uint32_t* h = hist + (size_t)q * kDigBins;
-    uint32_t c[per], mine = 0u;
-#pragma unroll
-    for (int j = 0; j < per; j += 4) {
-        uint4* p = reinterpret_cast<uint4*>(h + lane * per + j);
-        const uint4 v = *p;
-        *p = make_uint4(0u, 0u, 0u, 0u);
-        c[j] = v.x;
-        c[j + 1] = v.y;
-        c[j + 2] = v.z;
-        c[j + 3] = v.w;
-        mine += v.x + v.y + v.z + v.w;
-    }
-    if (state[q].z != 0u)
+    if (LV == 1 && state[q].z != 0u)
         return;
     if (LV == 0 && (k == 0u || (uint64_t)N < k)) {
         if (lane == 0)
             state[q] = make_uint4(0u, 0u, 1u, k == 0u ? 0xffffffffu : 0u);
         return;
+    }
+    // the histogram, for pairs that the sample decides: read, and cleared for
+    // the next pass (pass 1 leaves the full pass its bins only)
+    const bool sampled = LV == 0 ? N > kScanList : state[q].y != 0u;
+    uint32_t c[per] = {}, mine = 0u;
+    if (sampled) {
+#pragma unroll
+        for (int j = 0; j < per; j += 4) {
+            const uint4 v = reinterpret_cast<const uint4*>(h + lane * per)[j / 4];
+            c[j] = v.x;
+            c[j + 1] = v.y;
+            c[j + 2] = v.z;
+            c[j + 3] = v.w;
+            mine += v.x + v.y + v.z + v.w;
+        }
     }
     uint4 b = LV == 0 ? make_uint4(0u, 0x80000000u, 20u, 0u) : br[q];
     const uint32_t incl0 = wave_incl_sum(mine);
@@ -432,7 +446,7 @@ __global__ __launch_bounds__(kTT) void k_tt_bracket(uint4* __restrict__ state, u
     // sampled total travels in state.y)
     const uint32_t ns = LV == 0 ? total : state[q].y;
     uint32_t lo = b.x, hi = b.x + b.y, sab = b.w;  // hi: 2^31 at most
-    if (N > kSmallTensor && ns >= 64u) {
+    if (ns >= 64u) {
         const double f = (double)ns / (double)N, p = (double)k / (double)N;
         const double rs = (double)k * f, m = 5.0 * sqrt(rs * (1.0 - p)) + 8.0;
         // ranks counted from the top of the bracket
@@ -464,6 +478,15 @@ __global__ __launch_bounds__(kTT) void k_tt_bracket(uint4* __restrict__ state, u
         br[q] = make_uint4(lo, hi - lo, s, sab);
         if (LV == 0)
             state[q].y = ns;
+    }
+    // clear for the next pass, once every lane's bins have been used
+    if (LV == 1) {
+        static_assert(kScanBins == 64 * 4, "four bins a lane");
+        reinterpret_cast<uint4*>(h)[lane] = make_uint4(0u, 0u, 0u, 0u);
+    } else if (sampled) {
+#pragma unroll
+        for (int j = 0; j < per / 4; ++j)
+            reinterpret_cast<uint4*>(h)[j * 64 + lane] = make_uint4(0u, 0u, 0u, 0u);
     }
 }
 
@@ -612,12 +635,15 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
             glist[at + q] = lst[q];
 }
 
-constexpr int kPick = 1024;
-
 // One workgroup per pair after the full pass (see the top of the file).  The
 // list is read once for patterns whose bin leaves at most 11 bits open, and
 // once more per further 11 bits; four independent loads a thread hide the
-// latency that bounds it.
+// latency that bounds it.  kPick threads: 1024 for long lists, 256 for short
+// ones, which are bound by the barriers and by the workgroups in flight (the
+// call, 256 / 1024 threads, us: 2 fp32 experts of 128M elements in tensors of
+// 4M, density 0.2, 420 / 392, of 393,216 440 / 431, of 98,304 624 / 628; of 64M in
+// bf16 in tensors of 16,384, a quarter selected, density 0.05, 281 / 385).
+template <int kPick>
 __global__ __launch_bounds__(kPick) void k_tt_pick(uint4* __restrict__ state, const uint4* __restrict__ br,
                                                    const uint4* __restrict__ cnt, const uint32_t* __restrict__ hist,
                                                    uint32_t* __restrict__ list,
@@ -638,6 +664,7 @@ __global__ __launch_bounds__(kPick) void k_tt_pick(uint4* __restrict__ state, co
     const uint4 b = br[q], ct = cnt[q];
     const uint32_t nl = ct.z;
     const uint32_t* __restrict__ L = tt_list(list, (int)(q / (size_t)T), lwords, tlist, (uint32_t)t);
+    static_assert(kScanBins <= kPick, "a thread per bin");
     if (tid < kScanBins)
         h[tid] = hist[q * kDigBins + (size_t)tid];
     __syncthreads();
@@ -796,8 +823,11 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
             delta ? scan(k_tt_scan<0, true>) : scan(k_tt_scan<0, false>);
         else
             delta ? scan(k_tt_scan<1, true>) : scan(k_tt_scan<1, false>);
-        hipLaunchKernelGGL(k_tt_pick, dim3((unsigned)pairs), dim3(kPick), 0, s, state, br, cnt, hist, list,
-                           bt.d_tlist, lwords, bt.d_tnumel, T, density, left);
+        auto pick = [&](auto kern, int nth) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)pairs), dim3(nth), 0, s, state, br, cnt, hist, list, bt.d_tlist,
+                               lwords, bt.d_tnumel, T, density, left);
+        };
+        bt.tt_words / (uint64_t)T > kPickLong ? pick(k_tt_pick<1024>, 1024) : pick(k_tt_pick<256>, 256);
     }
     // the radix passes: over everything, or over the pairs the bracket route left
     for (int pass = 0; pass < 3 && route != TensorTies::Bracket; ++pass) {

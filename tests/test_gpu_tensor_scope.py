@@ -50,7 +50,7 @@ def _family(dtype, numel, be, seed):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("be", [64, 520, 4096, 8192])
 def test_tensor_thresholds_edges(mp, dtype, be):  # noqa: F811
-    numel = [8, 8184, 8192, 8200, 17 * be + 8, 300_000, 16 * be, 40 * be - 8]
+    numel = [8, 3576, 3584, 3592, 8184, 8192, 8200, 17 * be + 8, 300_000, 16 * be, 40 * be - 8]
     base, exps = _family(dtype, numel, be, seed=be)
     K, G = len(exps), oracle.Blocks(numel, be).G
     rng = np.random.default_rng(be)
