@@ -37,7 +37,7 @@
  *   they are device memory.  The caller owns every buffer; the library only
  *   reads inputs and writes the named outputs.  The library keeps a
  *   per-device workspace (block tables, plan scratch, byte counters,
- *   staging buffers) that mp_release() frees.
+ *   staging buffers, tensor-scope TIES scratch) that mp_release() frees.
  * Streams.  `stream` is a hipStream_t (NULL = the default stream).  Work is
  *   enqueued on it; calls return once enqueued unless stated otherwise.
  *   Calls that fill a host-side stats struct synchronise the stream first.
@@ -270,7 +270,12 @@ int mp_merge_ties(const mp_layout* layout, const void* base,
  * thresholds are complete: the kernels share one scratch area per device,
  * so calls on different streams run one after the other, and a selection
  * that finds no cut (an internal error, never expected) returns MP_E_HIP
- * with tau unspecified. */
+ * with tau unspecified.  Scratch: 8.2 KB per (expert, tensor) pair, and, for
+ * reading the blocks once instead of three times, lists of 4 (min(n_t, 8192 +
+ * 32 sqrt(n_t) + n_t / 256)) bytes per pair.  Lists of up to 1 GiB are kept
+ * with the workspace, larger ones are freed before the call returns; where the
+ * workspace cap or the device has no room for them, or a later allocation of
+ * the library needs theirs, the call runs without. */
 int mp_ties_tensor_thresholds(const mp_layout* layout, const void* base,
                               const void* const* experts, int32_t K, int32_t residency,
                               const uint32_t* mask, double density, uint32_t* tau,

@@ -99,3 +99,26 @@ def test_normal_deltas_leave_no_pair(mp, dtype, numel):  # noqa: F811
             _say(f"case {dtype} {numel} density {density}")
             _check(mp, dtype, be, numel, base, exps, mask, density)
             assert mp.mp_ties_tensor_left() == 0
+
+
+def test_large_lists_are_given_back(mp):  # noqa: F811
+    """Lists past what the library keeps between calls (1300 tensors of 16,384
+    elements x 32 experts: 2.1 GB) are used and freed: what a call holds
+    afterwards beyond the pairs' fixed scratch stays below 1 GiB."""
+    import torch
+    be, K, numel = 4096, 32, [16_384] * 1300
+    base, exps = _normal("bf16", sum(numel), 1, seed=9)
+    L, G = mp.Layout(numel, be, mp.MP_BF16), oracle.Blocks(numel, be).G
+    b, e = to_dev(base, "bf16"), to_dev(exps[0], "bf16")
+    mask = torch.full((G,), -1, dtype=torch.int32, device="cuda")
+    one = torch.empty(G, dtype=torch.int32, device="cuda")
+    mp.mp_release()
+    mp.mp_ties_tensor_thresholds(L, b, [e], mask, 0.2, one)
+    before = mp.mp_workspace_bytes()
+    tau = torch.empty(G * K, dtype=torch.int32, device="cuda")
+    mp.mp_ties_tensor_thresholds(L, b, [e] * K, mask, 0.2, tau)
+    assert mp.mp_ties_tensor_left() == 0  # the route with lists
+    assert torch.equal(tau.view(G, K), one[:, None].expand(G, K))
+    held, fixed = mp.mp_workspace_bytes() - before, len(numel) * K * (2048 * 4 + 3 * 16)
+    assert held < fixed + (1 << 30), f"{held >> 20} MiB more held after the call"
+    mp.mp_release()
