@@ -99,7 +99,8 @@ typedef struct mp_plan_stats {
 } mp_plan_stats;
 
 typedef struct mp_io_stats {
-    uint64_t expert_bytes; /* expert bytes the merge kernels loaded */
+    uint64_t expert_bytes; /* expert bytes the merge kernels loaded (counted at the loads;
+                              bytes that a kernel reads a second time count once) */
     uint64_t base_bytes;   /* base bytes read */
     uint64_t out_bytes;    /* output bytes written */
     uint64_t h2d_bytes;    /* expert bytes moved over PCIe (MP_HOST_PINNED: read by

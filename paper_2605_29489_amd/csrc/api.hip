@@ -74,8 +74,8 @@ constexpr uint64_t kListKeep = (uint64_t)1 << 30;
 
 struct DeviceWs {
     PlanScratch plan;
-    unsigned long long* counters = nullptr;  // [256]
-    unsigned long long* h_counters = nullptr;  // pinned [256]
+    unsigned long long* counters = nullptr;    // [2 * kCounters]
+    unsigned long long* h_counters = nullptr;  // pinned [2 * kCounters]
     unsigned long long* cov = nullptr;         // coverage counters, grown on demand
     int64_t cov_cap = 0;
     uint32_t* tt_hist = nullptr;               // tensor-scope TIES: digit histograms per (expert, tensor)
@@ -315,8 +315,8 @@ int get_ws(DeviceWs** out)
     auto w = std::make_unique<DeviceWs>();
     if ((e = plan_ctl_alloc(&w->plan.ctl)) != hipSuccess ||
         (e = ws_host_malloc((void**)&w->plan.h_stats, sizeof(uint64_t) * 8)) != hipSuccess ||
-        (e = ws_malloc((void**)&w->counters, sizeof(unsigned long long) * 256)) != hipSuccess ||
-        (e = ws_host_malloc((void**)&w->h_counters, sizeof(unsigned long long) * 256)) != hipSuccess ||
+        (e = ws_malloc((void**)&w->counters, sizeof(unsigned long long) * 2 * kCounters)) != hipSuccess ||
+        (e = ws_host_malloc((void**)&w->h_counters, sizeof(unsigned long long) * 2 * kCounters)) != hipSuccess ||
         (e = ws_host_malloc((void**)&w->h_tt_err, 2 * sizeof(uint32_t))) != hipSuccess) {
         free_ws(dev, *w);
         return fail(MP_E_NOMEM, "workspace allocation failed: %s", hipGetErrorString(e));
@@ -581,14 +581,15 @@ int run_merge(const mp_layout* L, const void* base, const void* const* experts, 
         return fail(MP_E_UNSUPPORTED, "TIES supports blocks of at most %d elements", kTiesMaxBlock);
     if (a.op == Op::TIES_TAU && (rc = check_device_buffer(a.tau, sizeof(uint32_t) * (size_t)(bt.G * K), "tau")))
         return rc;
+    a.pcie = residency == MP_HOST_PINNED;
     unsigned long long* ctr = io ? c.ws->counters : nullptr;
+    const int n_ctr = ties_reads_twice(bt, a, K) ? 2 * kCounters : kCounters1;
     hipError_t e;
     if (ctr) {
-        hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, ctr, 256);
+        hipLaunchKernelGGL(k_zero_u64, dim3((unsigned)(n_ctr / 256)), dim3(256), 0, s, ctr, n_ctr);
         if ((e = hipGetLastError()) != hipSuccess)
             return hip_fail(e, "counter reset");
     }
-    a.pcie = residency == MP_HOST_PINNED;
     mp_io_stats st{};
     uint64_t staged_bytes = 0;
     if (staged(residency)) {
@@ -603,15 +604,18 @@ int run_merge(const mp_layout* L, const void* base, const void* const* experts, 
         return hip_fail(e, "merge launch");
     }
     if (io) {
-        if ((e = hipMemcpyAsync(c.ws->h_counters, ctr, sizeof(unsigned long long) * 256,
+        if ((e = hipMemcpyAsync(c.ws->h_counters, ctr, sizeof(unsigned long long) * (size_t)n_ctr,
                                 hipMemcpyDeviceToHost, s)) != hipSuccess)
             return hip_fail(e, "counter readback");
         if ((e = hipStreamSynchronize(s)) != hipSuccess)
             return hip_fail(e, "hipStreamSynchronize");
         unsigned long long sum = 0;
-        for (int q = 0; q < 256; ++q) {  // slot (block mod 8) * 32 + expert
-            st.expert_bytes_by_expert[q & 31] += c.ws->h_counters[q];
-            sum += c.ws->h_counters[q];
+        for (int i = 0; i < kMaxK; ++i) {
+            unsigned long long first = 0, again = 0;  // the two readings
+            for (int q = i; q < n_ctr; q += kMaxK)    // slot * 32 + expert
+                (q < kCounters ? first : again) += c.ws->h_counters[q];
+            st.expert_bytes_by_expert[i] = std::max(first, again);
+            sum += st.expert_bytes_by_expert[i];
         }
         st.expert_bytes = sum;
         if (residency == MP_HOST_PINNED)

@@ -67,6 +67,7 @@ constexpr int NW = NT / 64;              // waves per workgroup
 constexpr int GS = 4;                    // experts trimmed together (one scanning wave each)
 constexpr uint32_t RETRY = 4u;           // state: the cut lies below the first pass's floor
 }  // namespace ties
+constexpr int kTrimGroup = ties::GS;
 
 // Sum over the 64 lanes of a wave, returned wave-uniform: the butterfly of
 // wave_max_u32 (quad permutes, row mirrors, row broadcasts) with adds.  The
@@ -728,7 +729,13 @@ __global__ __launch_bounds__(ties::NT, MULTI ? ties::NT / 128 : MP_TIES_WAVES) v
 // carried between groups of experts by k_merge_ties (three registers per
 // element at two waves per SIMD, each group's loads behind the last one's
 // barriers) is not needed.
-template <int DT, int R, int NW, int W, bool DELTA, class Src>
+//
+// COUNT: count the realized reads, both readings by themselves.  An instance of
+// its own, since the branches alone cost the other calls 2-10%.  100M elements,
+// K = 8, B = 50%, blocks of 512 / 2048 / 4096, the call with its counts: bf16 697 /
+// 350 / 371 us, fp32 734 / 577 / 655 (one reading counted in 8 words per expert
+// instead of two in 64: 4757 / 770 / 457 and 2730 / 581 / 616, the atomics).
+template <int DT, int R, int NW, int W, bool DELTA, bool COUNT, class Src>
 __global__ __launch_bounds__(64 * NW, W) void k_ties_two(
     Src src, const void* __restrict__ base, const uint32_t* __restrict__ mask, const uint64_t* __restrict__ boff,
     const uint32_t* __restrict__ blen, double density, uint32_t n_full, uint32_t k_full, float lambda, uint32_t kmask,
@@ -741,6 +748,7 @@ __global__ __launch_bounds__(64 * NW, W) void k_ties_two(
     constexpr int EM = CPT * V;
     __shared__ __align__(16) uint32_t rows[NW][ties::NB];
     __shared__ uint32_t s_tau[kMaxK];
+    __shared__ uint32_t s_read[COUNT ? kMaxK : 1];  // bytes the merge has loaded of each selected expert
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t b = blockIdx.x;
@@ -755,6 +763,8 @@ __global__ __launch_bounds__(64 * NW, W) void k_ties_two(
     const uint32_t m = (k != 0u) ? (mask[g] & kmask) : 0u;  // density 0 keeps nothing: no expert is read
     const uint32_t nbytes = n / (uint32_t)V * 16u;
     const __amdgpu_buffer_rsrc_t rb = block_rsrc(chunk_ptr(base, off, ES), nbytes);
+    if (COUNT && t < kMaxK)
+        s_read[t] = 0u;
     // ---- thresholds
     {
         int r = 0;
@@ -762,15 +772,16 @@ __global__ __launch_bounds__(64 * NW, W) void k_ties_two(
             if (r % NW != wave)
                 continue;
             const int i = __builtin_ctz(mm);
-            if (ctr != nullptr && lane == 0)  // the expert's bytes, counted at their first read
-                atomicAdd(&ctr[(((blockIdx.x * 4u) + (uint32_t)wave) & 7u) << 5 | (uint32_t)i],
-                          (unsigned long long)nbytes);
             if (k == n) {  // keep every nonzero
                 if (lane == 0)
                     s_tau[r] = 1u;
                 continue;
             }
             const __amdgpu_buffer_rsrc_t re = block_rsrc(src.expert(i, r, b, off, n, ES), nbytes);
+            if constexpr (COUNT) {  // the rows' chunks that lie in the block
+                if (lane == 0)
+                    atomicAdd(&ctr[count_slot<64>(wave, i)], (unsigned long long)min(nbytes, (uint32_t)R * 1024u));
+            }
             float d[E];
             float p = 0.0f;
 #pragma unroll
@@ -843,7 +854,8 @@ __global__ __launch_bounds__(64 * NW, W) void k_ties_two(
 #pragma unroll
         for (int q = 0; q < CPT; ++q)
             Fmt<DT>::unpack(xr[q], &x0[q * V]);
-        for (int r = 0; mm != 0u; ++r) {
+        int r = 0;
+        for (; mm != 0u; ++r) {
             float x[EM];
 #pragma unroll
             for (int q = 0; q < CPT; ++q)
@@ -857,6 +869,10 @@ __global__ __launch_bounds__(64 * NW, W) void k_ties_two(
                 ties_fold2(DELTA ? x[e] : x[e] - x0[e], DELTA ? x[e + 1] : x[e + 1] - x0[e + 1], tauf, c16, ps[e],
                            ns[e], cpn[e], ps[e + 1], ns[e + 1], cpn[e + 1]);
         }
+        if constexpr (COUNT) {  // the pass's chunks that lie in the block, of each of the r experts folded in
+            if (lane < r)
+                atomicAdd(&s_read[lane], min(nbytes - c0 * 16u, 1024u * CPT));
+        }
         float mean[EM];
         ties_elect_mean<EM>(ps, ns, cpn, mean, lane);
 #pragma unroll
@@ -867,6 +883,13 @@ __global__ __launch_bounds__(64 * NW, W) void k_ties_two(
                 y[v] = fmaf(lambda, mean[q * V + v], x0[q * V + v]);
             bst16s(ro, bo[q], Fmt<DT>::pack(y));  // dropped past the block's end
         }
+    }
+    if constexpr (COUNT) {  // the second reading's counters follow the first's
+        __syncthreads();
+        int r = 0;
+        for (uint32_t mm = m; mm != 0u; mm &= mm - 1u, ++r)
+            if (t == r)
+                atomicAdd(&ctr[kCounters + count_slot<64>(0, __builtin_ctz(mm))], (unsigned long long)s_read[r]);
     }
 }
 
@@ -885,14 +908,7 @@ hipError_t launch_ties_typed(const BlockTable& bt, const MergeArgs& a, const Src
     // the first histogram pass's guess at tau: 0.8 of the rho-tail quantile
     // of a normal with the deltas' RMS, as in the catalog pass
     const float gcoef = (float)(0.8 * normal_two_sided_quantile(a.density));
-    // Select-then-merge for experts in device memory, except at most four
-    // experts on blocks over 2048 elements.  4 layers of the Qwen2.5-1.5B
-    // shape, k_merge_ties -> k_ties_two, us: K = 4, B = 50%, bf16 blocks of 512 /
-    // 1024 / 2048 / 4096: 2222 -> 549, 1206 -> 479, 656 -> 464, 409 (500), fp32:
-    // 2545 -> 833, 1397 -> 733, 807 -> 780, 638 (864); K = 8, B = 25%, bf16: 5817 ->
-    // 563, 2955 -> 481, 1509 -> 472, 835 -> 507, fp32: 6449 -> 891, 3438 -> 781,
-    // 1807 -> 820, 1046 -> 871.  The second read would cross PCIe for pinned experts.
-    if (!a.pcie && (K > ties::GS || bt.max_len <= 2048)) {
+    if (ties_reads_twice(bt, a, K)) {
         auto go = [&](auto kern, int nw) {
             hipLaunchKernelGGL(kern, grid, dim3(64 * nw), 0, s, src, base, mask, bt.d_off, bt.d_len, a.density, n_full,
                                k_full, a.lambda, kmask, out, ctr, gcoef);
@@ -901,8 +917,10 @@ hipError_t launch_ties_typed(const BlockTable& bt, const MergeArgs& a, const Src
         // workgroup: the fewer, the fewer idle at the barrier; the more, the
         // less one wave merges alone (bf16 512-element blocks, K = 4: one / two /
         // four waves 549 / 661 / 907 us; fp32 4096: 1072 / 936 / 864 us)
-#define MP_TWO(RV, NWV, WV)                                                                                            \
-    (a.bsub == 0.0f ? go(k_ties_two<DT, RV, NWV, WV, true, Src>, NWV) : go(k_ties_two<DT, RV, NWV, WV, false, Src>, NWV))
+#define MP_TWO_C(RV, NWV, WV, CV)                                                                                      \
+    (a.bsub == 0.0f ? go(k_ties_two<DT, RV, NWV, WV, true, CV, Src>, NWV)                                              \
+                    : go(k_ties_two<DT, RV, NWV, WV, false, CV, Src>, NWV))
+#define MP_TWO(RV, NWV, WV) (ctr != nullptr ? MP_TWO_C(RV, NWV, WV, true) : MP_TWO_C(RV, NWV, WV, false))
         if constexpr (DT == 1) {
             if (bt.max_len <= 512)
                 MP_TWO(1, 1, 6);
@@ -923,6 +941,7 @@ hipError_t launch_ties_typed(const BlockTable& bt, const MergeArgs& a, const Src
                 MP_TWO(16, 4, 4);
         }
 #undef MP_TWO
+#undef MP_TWO_C
         return hipGetLastError();
     }
     if (K <= ties::GS)
@@ -935,6 +954,18 @@ hipError_t launch_ties_typed(const BlockTable& bt, const MergeArgs& a, const Src
 }
 
 }  // namespace
+
+// Select-then-merge for experts in device memory, except at most four
+// experts on blocks over 2048 elements.  4 layers of the Qwen2.5-1.5B
+// shape, k_merge_ties -> k_ties_two, us: K = 4, B = 50%, bf16 blocks of 512 /
+// 1024 / 2048 / 4096: 2222 -> 549, 1206 -> 479, 656 -> 464, 409 (500), fp32:
+// 2545 -> 833, 1397 -> 733, 807 -> 780, 638 (864); K = 8, B = 25%, bf16: 5817 ->
+// 563, 2955 -> 481, 1509 -> 472, 835 -> 507, fp32: 6449 -> 891, 3438 -> 781,
+// 1807 -> 820, 1046 -> 871.  The second read would cross PCIe for pinned experts.
+bool ties_reads_twice(const BlockTable& bt, const MergeArgs& a, int K)
+{
+    return a.op == Op::TIES && !a.pcie && (K > kTrimGroup || bt.max_len <= 2048);
+}
 
 hipError_t launch_merge_ties(const BlockTable& bt, const MergeArgs& a, const void* base, const ExpertPtrs& ex, int K,
                              const uint32_t* mask, void* out, unsigned long long* counters, hipStream_t s)

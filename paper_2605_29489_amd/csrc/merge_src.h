@@ -56,8 +56,17 @@ struct StagedSrc {
 // Realized expert reads (Prop. 1's N^run), counted where the loads are
 // issued: after loading expert i's chunks q * NT + t (q < CPT) of a block of
 // nch chunks, each wave adds the bytes its lanes loaded into slot
-// ((workgroup * 4 + wave) mod 8) * 32 + i, so the 256 counters sum per
-// expert and the atomics spread over 8 words each.  No-op when ctr is null.
+// ((workgroup * 4 + wave) mod SLOTS) * 32 + i, so the counters sum per
+// expert and the atomics spread over SLOTS words each.  No-op when ctr is null.
+// A kernel that reads its blocks a second time counts that reading in a set
+// of kCounters of its own; an expert's bytes are the larger of the two sums,
+// so that neither reading can leave the plan unseen.
+template <int SLOTS>
+__device__ inline uint32_t count_slot(int wave, int i)
+{
+    static_assert(SLOTS * kMaxK <= kCounters, "slots of a set");
+    return (((blockIdx.x * 4u) + (uint32_t)wave) & (uint32_t)(SLOTS - 1)) * (uint32_t)kMaxK + (uint32_t)i;
+}
 template <int NT, int CPT>
 __device__ inline void count_loaded(unsigned long long* ctr, int i, uint32_t nch)
 {
@@ -69,7 +78,7 @@ __device__ inline void count_loaded(unsigned long long* ctr, int i, uint32_t nch
     for (int q = 0; q < CPT; ++q)
         nl += (uint32_t)__popcll(__ballot(q * NT + t < nch));
     if ((t & 63u) == 0u)
-        atomicAdd(&ctr[(((blockIdx.x * 4u) + (t >> 6)) & 7u) << 5 | (uint32_t)i], (unsigned long long)nl * 16ull);
+        atomicAdd(&ctr[count_slot<8>((int)(t >> 6), i)], (unsigned long long)nl * 16ull);
 }
 
 }  // namespace

@@ -21,6 +21,11 @@ struct ExpertPtrs {
     const void* p[kMaxK];
 };
 
+// Counters of one reading of the expert blocks: 64 words per expert (see
+// count_slot).  A merge that reads its blocks twice has two sets, any other
+// uses the first kCounters1 words (8 per expert).
+constexpr int kCounters = 64 * kMaxK, kCounters1 = 8 * kMaxK;
+
 // Per-expert fp32 coefficients, passed to kernels by value.
 struct Coeffs {
     float v[kMaxK];
@@ -229,6 +234,10 @@ struct MergeArgs {
     float bsub = 1.0f;  // d = x_i - bsub * x_0: 1 for fine-tuned weights, 0 for explicit deltas
     bool pcie = false;  // the experts are pinned host memory, read over PCIe: every byte once
 };
+
+// Whether the merge reads its selected blocks twice, and so counts its reads in
+// both sets of counters.
+bool ties_reads_twice(const BlockTable& bt, const MergeArgs& a, int K);
 
 hipError_t launch_merge(const BlockTable& bt, const MergeArgs& a, const void* base,
                         const ExpertPtrs& ex, int K, const uint32_t* mask, void* out,
