@@ -916,7 +916,9 @@ hipError_t launch_ties_typed(const BlockTable& bt, const MergeArgs& a, const Src
         // Rows of 64 chunks per unit from the layout's longest block.  Waves per
         // workgroup: the fewer, the fewer idle at the barrier; the more, the
         // less one wave merges alone (bf16 512-element blocks, K = 4: one / two /
-        // four waves 549 / 661 / 907 us; fp32 4096: 1072 / 936 / 864 us)
+        // four waves 549 / 661 / 907 us; fp32 4096: 1072 / 936 / 864 us; fp32 2048, K = 1
+        // over 100M elements at B = 10 / 50 / 100%: 134 / 178 / 273, 130 / 172 / 216,
+        // 130 / 180 / 251, and k_merge_ties 137 / 184 / 234)
 #define MP_TWO_C(RV, NWV, WV, CV)                                                                                      \
     (a.bsub == 0.0f ? go(k_ties_two<DT, RV, NWV, WV, true, CV, Src>, NWV)                                              \
                     : go(k_ties_two<DT, RV, NWV, WV, false, CV, Src>, NWV))
@@ -936,7 +938,7 @@ hipError_t launch_ties_typed(const BlockTable& bt, const MergeArgs& a, const Src
             else if (bt.max_len <= 1024)
                 MP_TWO(4, 2, 6);
             else if (bt.max_len <= 2048)
-                MP_TWO(8, 4, 6);
+                K == 1 ? MP_TWO(8, 2, 6) : MP_TWO(8, 4, 6);  // one expert: three of four waves idle at the barrier
             else
                 MP_TWO(16, 4, 4);
         }
