@@ -26,25 +26,52 @@ def _check(mp, dtype, be, numel, base, exps, mask, density, delta=False):  # noq
     assert np.array_equal(tau.cpu().numpy().view(np.uint32), want), f"{dtype} be={be} density={density}"
 
 
+def _sampled(dtype, numel, be):
+    """The elements that the sample reads of whole-mask units: of block g (over
+    all tensors) slice g mod 32 of max(1, 1/32 of a full block) 16-byte chunks,
+    the first slice where the block is too short to have that one."""
+    v = 4 if dtype == "f32" else 8
+    segc, seen, g = max(1, be // v // 32), [], 0
+    for n in numel:
+        for x in range(0, n, be):
+            nch = min(be, n - x) // v
+            first = g % 32 * segc
+            first = 0 if nch <= first else first
+            c = np.arange(nch)
+            seen.append(np.repeat((c >= first) & (c < first + segc), v))
+            g += 1
+    return np.concatenate(seen)
+
+
+def _encode(dtype, deltas, seed):
+    deltas = [d.astype(np.float32) for d in deltas]
+    P = len(deltas[0])
+    if dtype == "f32":  # a zero base keeps the fp32 patterns
+        return np.zeros(P, np.float32), deltas
+    base = oracle.round_bf16(np.random.default_rng(seed).normal(0.0, 0.02, P).astype(np.float32))
+    x0 = (base.astype(np.uint32) << 16).view(np.float32)
+    return base, [oracle.round_bf16(x0 + d) for d in deltas]
+
+
+def _misleading(dtype, numel, be, seed):
+    """Large only where the sample reads (it sees nothing else), and large only
+    where it does not."""
+    rng = np.random.default_rng(seed)
+    seen = _sampled(dtype, numel, be)
+    return [np.where(where, 1.0, 1e-3) * rng.normal(0.0, 1.0, len(seen)) for where in (seen, ~seen)]
+
+
 def _family(dtype, numel, be, seed):
-    """Six experts: normal, a few repeated values, mostly zero, all equal,
-    large only in the slices that the sample reads (they see
-    far too many), and magnitudes that share their top 16 bits."""
+    """Seven experts: normal, a few repeated values, mostly zero, all equal, the
+    two that mislead the sample, and magnitudes that share their top 16 bits."""
     P = sum(numel)
     rng = np.random.default_rng(seed)
     sign = rng.choice([-1.0, 1.0], P)
-    pos = np.arange(P)
-    seen = (pos % be) // max(1, be // 32) == (pos // be) % 32
     deltas = [rng.normal(0.0, 1e-3, P), rng.choice([0.5, 1.0, 1.5], P) * 2.0 ** -10 * sign,
               np.where(rng.random(P) < 0.05, rng.normal(0.0, 1e-3, P), 0.0), np.full(P, 2.0 ** -9),
-              np.where(seen, 1.0, 1e-3) * rng.normal(0.0, 1.0, P),
+              *_misleading(dtype, numel, be, seed + 1),
               1e-3 * (1.0 + rng.integers(0, 1 << 14, P) * 2.0 ** -23) * sign]
-    deltas = [d.astype(np.float32) for d in deltas]
-    if dtype == "f32":  # a zero base keeps the fp32 patterns
-        return np.zeros(P, np.float32), deltas
-    base = oracle.round_bf16(rng.normal(0.0, 0.02, P).astype(np.float32))
-    x0 = (base.astype(np.uint32) << 16).view(np.float32)
-    return base, [oracle.round_bf16(x0 + d) for d in deltas]
+    return _encode(dtype, deltas, seed + 2)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
@@ -54,27 +81,53 @@ def test_tensor_thresholds_edges(mp, dtype, be):  # noqa: F811
     base, exps = _family(dtype, numel, be, seed=be)
     K, G = len(exps), oracle.Blocks(numel, be).G
     rng = np.random.default_rng(be)
-    some = (rng.integers(0, 1 << K, G) & 0x3f).astype(np.uint32)
+    some = rng.integers(0, 1 << K, G).astype(np.uint32)
     for mask in (some, np.full(G, (1 << K) - 1, np.uint32), np.zeros(G, np.uint32)):
         for density in (0.0, 1e-6, 0.01, 0.2, 0.5, 0.9, 1.0):
             _say(f"case {dtype} block {be} density {density}")
             _check(mp, dtype, be, numel, base, exps, mask, density)
+            assert (mp.mp_ties_tensor_left() == -1) == (be > 4096)  # longer blocks have no one-pass route
     _check(mp, dtype, be, numel, base, exps, some, 0.2, delta=True)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("be", [64, 520, 4096])
+def test_misleading_samples_are_left_over(mp, dtype, be):  # noqa: F811
+    """Samples that see only the large deltas, or none of them: every pair's k-th
+    largest lies outside its bracket (below it, above it), and the digit passes
+    finish both pairs.  A normal expert beside them needs no such pass."""
+    numel = [300_000]
+    rng = np.random.default_rng(5)
+    base, exps = _encode(dtype, [*_misleading(dtype, numel, be, 6), rng.normal(0.0, 1e-3, numel[0])], 7)
+    G = oracle.Blocks(numel, be).G
+    for density in (0.01, 0.2):
+        for bits in (1, 2, 4, 7):
+            _say(f"case {dtype} block {be} density {density} experts {bits:03b}")
+            mask = np.full(G, bits, np.uint32)
+            _check(mp, dtype, be, numel, base, exps, mask, density)
+            assert mp.mp_ties_tensor_left() == bin(bits & 3).count("1")
+
+
 def test_tensor_thresholds_without_lists(mp):  # noqa: F811
-    """A workspace limit that leaves no room for the lists: the same thresholds."""
+    """A workspace limit that leaves no room for the lists: the library gives them
+    back, every pair takes the digit passes, and the thresholds are the same."""
     be, numel = 4096, [300_000, 8192]
     base, exps = _family("bf16", numel, be, seed=1)
-    mask = np.full(oracle.Blocks(numel, be).G, 63, np.uint32)
+    mask = np.full(oracle.Blocks(numel, be).G, 127, np.uint32)
+    mp.mp_release()
     _check(mp, "bf16", be, numel, base, exps, mask, 0.2)
+    assert mp.mp_ties_tensor_left() >= 0
     held = mp.mp_workspace_bytes()
+    lists = 4 * len(exps) * (8192 + 32 * 547 + 300_000 // 256 + 8192)
     try:
         mp.mp_set_workspace_limit(held)
         _check(mp, "bf16", be, numel[::-1], base, exps, mask, 0.2)  # its table takes the lists' place
+        assert mp.mp_ties_tensor_left() == -1
+        assert mp.mp_workspace_bytes() < held and held - lists < mp.mp_workspace_bytes()
     finally:
         mp.mp_set_workspace_limit(0)
     _check(mp, "bf16", be, numel, base, exps, mask, 0.3)
+    assert mp.mp_ties_tensor_left() >= 0
 
 
 def _normal(dtype, P, K, seed):
