@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int s
     __shared__ unsigned long long sw[kHistT / 64];
     __shared__ Digit dg;
     __shared__ float s_w[kMaxK];
-    if (ctl->done || ctl->all_fit)
+    if (ctl->all_fit)
         return;
     const int t = threadIdx.x;
     if (t < K)
@@ -317,13 +317,13 @@ __global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int s
 }
 
 // After the last digit pass d (key bits from sh up): resolve its digit; the
-// cut key p is among the at most 2^open uids (kMarkUids at most) that share all
-// bits above (open = sh, or fewer where the uids need no more), found by a prefix sum of their costs in uid order.  Then mark:
+// cut key p is among the 2^sh uids (kMarkUids at most) that share all bits
+// above, found by a prefix sum of their costs in uid order.  Then mark:
 // select the candidates below the cut and list the next round's (above p, and
 // not dearer than what is left).  In the all-fit case select every candidate.
 // Per workgroup: the selected cost and count, and the mask's digest terms.
 constexpr int kMarkBits = 12, kMarkUids = 1 << kMarkBits;
-__global__ __launch_bounds__(kHistT) void k_plan_mark(PlanCtl* ctl, int d, int sh, int open, const float* __restrict__ sumsq,
+__global__ __launch_bounds__(kHistT) void k_plan_mark(PlanCtl* ctl, int d, int sh, const float* __restrict__ sumsq,
                                                       Coeffs w, uint32_t flags, int K,
                                                       const uint32_t* __restrict__ blen, uint32_t esize, int64_t G,
                                                       uint32_t* __restrict__ mask, uint32_t* __restrict__ next,
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kHistT) void k_plan_mark(PlanCtl* ctl, int d, int s
             constexpr int per = kMarkUids / kHistT;
             unsigned long long c[per], run = 0ull;
             const int64_t n = G * K;
-            const int m = 1 << open, per_t = (m + kHistT - 1) / kHistT;
+            const int m = 1 << sh, per_t = (m + kHistT - 1) / kHistT;
 #pragma unroll
             for (int q = 0; q < per; ++q) {
                 c[q] = 0ull;
@@ -474,8 +474,6 @@ __global__ __launch_bounds__(kT) void k_plan_advance(PlanCtl* ctl, int next_list
 {
     // takes in the selections of k_plan_mark's n_part workgroups
     const int t = threadIdx.x;
-    if (ctl->done)
-        return;
     const unsigned long long cs = block_sum_parts(ctl, 0, n_part);
     const unsigned long long cn = block_sum_parts(ctl, 1, n_part);
     if (t != 0)
@@ -918,11 +916,9 @@ bool enqueue_select(const PlanIn& p, bool tensor_level, unsigned long long* stat
         open -= wd;
         pass(open, wd);
     }
-    // the uid bits above `bits` are zero in every key; with few units the
-    // whole uid is left to the marking pass
-    const int open = psh == 32 ? bits : psh;
+    static_assert(kOneMax >= kMarkUids, "more than kOneMax units: a uid pass has run");
     const unsigned mgrid = (unsigned)std::min<int64_t>((p.G + kHistT - 1) / kHistT, kPlanGrid);
-    hipLaunchKernelGGL(k_plan_mark, dim3(mgrid), dim3(kHistT), 0, s, ctl, d - 1, psh, open, p.sumsq, p.w, p.flags, p.K,
+    hipLaunchKernelGGL(k_plan_mark, dim3(mgrid), dim3(kHistT), 0, s, ctl, d - 1, psh, p.sumsq, p.w, p.flags, p.K,
                        p.blen, p.es, p.G, p.mask, p.list1, &ctl->list_n[1], p.cap);
     if (!tensor_level && p.cap <= (unsigned)kOneMax) {
         auto one = [&](auto kern, int nt) {
