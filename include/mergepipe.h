@@ -189,10 +189,11 @@ int mp_plan(const mp_layout* layout, int32_t K, const float* sumsq,
  * other allocation routine and keeps no per-layout cache.  Instead, the
  * control block, the layout's tensor sizes (twice), the first block of
  * each tensor, the tensors' selection words, the block lengths and the two
- * candidate lists live in one fixed device array of 16 MiB (16,777,216
- * bytes), which each device the library runs on holds until the process
- * ends.  A layout needs the sum of these sizes, each rounded up to 256
- * bytes: about 19 KB for the control block, 8 * n_tensors, 4 * (n_tensors +
+ * candidate lists live in one fixed device array (16.2 MiB), which each
+ * device the library runs on holds until the process ends.  A layout may
+ * take 16 MiB (16,777,216 bytes): the sum of these sizes, each rounded up to
+ * 256 bytes: 18,688 for the control block (what it takes beyond those is
+ * added to the array), 8 * n_tensors, 4 * (n_tensors +
  * 1), twice 4 * n_tensors, 4 * G, and twice 4 * K * max(1, n_tensors) --
  * 1.6 MB for a 1.5B-parameter layout cut into 4096-element blocks, so up
  * to about four million blocks fit.  A larger layout

@@ -123,8 +123,9 @@ constexpr int cat_waves()
 // the base staged in LDS (4 layers of the Qwen2.5-1.5B shape, us): bf16 K = 4
 // blocks of 4096 / 2048 / 1024 / 512: 358 -> 330, 522 -> 308, 964 -> 354,
 // 1836 -> 465; K = 1: 190 -> 126; K = 6: 529 -> 455; fp32 blocks of 2048 /
-// 1024 (K = 6) / 512: 811 -> 594, 2733 -> 870, 3045 -> 727.  All 28 layers,
-// bf16, K = 4: 2480 -> 2200-2420 (6.4-7.0 TB/s).
+// 1024 (K = 6) / 512: 811 -> 594, 2733 -> 870, 3045 -> 727.  1.54B elements in
+// bf16, K = 1 / 2 / 4, blocks of 4096: 1385 -> 902, 1639 -> 1313, 2523 -> 2274 (6.8
+// TB/s); explicit deltas 662 -> 458, 1033 -> 895, 1892 -> 1796 (6.9 TB/s).
 // Two blocks per wave hide the loads of a 1 KiB unit (512 bf16 elements: 536
 // -> 465 us); for larger units they cost registers and were slower.
 template <int DT, bool DELTA, int R, int U>
@@ -139,9 +140,10 @@ __global__ __launch_bounds__(64, (cat_waves<DT, DELTA, R * U>())) void k_index_t
     const int lane = threadIdx.x;
     // id -> (run of U blocks, expert), the expert fastest, a run's experts on
     // one XCD (x = id mod 8) so that they read its base through one L2.  Each
-    // XCD takes a contiguous range of runs (1887 against 1994 us for the
-    // runs x, x + 8, ... on 28 layers in bf16), except with 16 KiB units,
-    // where the interleaved order is faster (K = 2: 358 against 378 us)
+    // XCD takes a contiguous range of runs (1.54B elements in bf16, K = 4: 2275
+    // against 2358 us for the runs x, x + 8, ...; explicit deltas 1796 against
+    // 1855), except with 16 KiB units, where the interleaved order is faster
+    // (K = 2: 358 against 378 us)
     const uint32_t pos = blockIdx.x >> 3, xcd = blockIdx.x & 7u;
     const uint32_t q8 = K > 1 ? (uint32_t)__umul64hi((uint64_t)pos, k_magic) : pos;
     const uint32_t i = pos - q8 * (uint32_t)K;

@@ -723,12 +723,20 @@ __global__ __launch_bounds__(ties::NT, MULTI ? ties::NT / 128 : MP_TIES_WAVES) v
 // (R chunks per lane), finds the trim threshold by itself as the catalog does
 // (no barrier) and leaves it in LDS.  Then all lanes merge: the base and the
 // selected experts are read again, eight elements per lane and pass, each
-// expert folded in as it arrives.  The second read is served by L2 and the
-// last-level cache (a workgroup's blocks are at most a few hundred KiB, and the
-// resident ones together fit), so HBM sees each byte once, and the state
-// carried between groups of experts by k_merge_ties (three registers per
-// element at two waves per SIMD, each group's loads behind the last one's
-// barriers) is not needed.
+// expert folded in as it arrives.  The state carried between groups of experts
+// by k_merge_ties (three registers per element at two waves per SIMD, each
+// group's loads behind the last one's barriers) is not needed.
+//
+// The second reading misses L2 wherever the resident workgroups' blocks exceed
+// its 4 MiB: blocks of 4096, K = 8 to 32 at B = 100% and K = 16 at 25%, the L2s
+// read 1.9-2.1 times the algorithmic bytes, at 5.7-7.2 TB/s; blocks of 1024, K =
+// 4, B = 50%, 1.3 times.  How much of that the last-level cache (256 MB; ten
+// workgroups a CU hold 184 MB at K = 8, B = 100%, 350 MB at K = 16) serves the
+// counters do not show.  That traffic bounds many experts, with vector issue
+// (0.47-0.79 of the cycles) beside it; it is still the faster form (100M
+// elements, blocks of 4096, B = 100%, k_merge_ties -> this, us: bf16 K = 5 / 16 / 32
+// (50M) 645 -> 371, 1570 -> 1027, 1512 -> 1147; fp32 858 -> 726, 2205 -> 1916,
+// 2148 -> 1973).
 //
 // COUNT: count the realized reads, both readings by themselves.  An instance of
 // its own, since the branches alone cost the other calls 2-10%.  100M elements,

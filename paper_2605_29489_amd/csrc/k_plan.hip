@@ -28,24 +28,39 @@
 // sequence and kernels that are no longer needed return at once.  What bounds
 // it is launches and dependent passes, not bytes: at 1.5M units, eight 8-bit
 // passes of one thread per block took 8.5 us each, the later rounds (reloading
-// their list in each pass) 30 us and fourteen launches in all 145 us; now 75 us,
-// seven launches, passes of 6-13 us and the later rounds 14 us.
+// their list in each pass) 30 us and fourteen launches in all 145 us; now 80 us,
+// seven launches, passes of 7-12 us and the later rounds 15 us.
+//
+// Above kOneMax units a plan also has to run beside another stream's merge,
+// whose waves refill every slot as it frees: a workgroup is placed only once
+// its waves' slots and registers are free on one CU together.  So these
+// kernels have four waves (one per SIMD) of at most 64 registers (a merge
+// wave's).  Workgroups of 512 and 1024 threads waited for the whole merge: the
+// plans of the 1.5B-parameter step's second and third budgets took 1.52 and
+// 1.95 ms, now 0.30 and 0.23.  (Later rounds over lists of more than 1,024 units
+// keep 1024 threads: that last kernel waits for the merge.)
 #include "device_common.h"
 #include "mp_internal.h"
 
 namespace mp {
 
-// Workgroups of the round-0 kernels (at most).  Each workgroup ends a pass
-// with device-scope atomic adds into the shared histogram, which serialize
-// per address.
-constexpr int kPlanGrid = 512;
-constexpr int kHistGrid = 256, kHistT = 512;  // the digit passes: one workgroup per CU
-constexpr int kPlanBins = 2048;               // 11-bit digits
+// Workgroups of the marking pass (at most).  Each workgroup ends a digit pass
+// with device-scope atomic adds into the shared histogram, which serialize per
+// address: 512 workgroups up to 8M units (at 1.5M, 512 / 256 of twice the loads
+// in flight: 80 / 84 us), 1024 above (32M: 336 / 355 with 512).
+constexpr int kPlanGrid = 1024;
+constexpr int kHistT = 256, kHistU = 4;  // threads, and units' loads in flight per thread
+constexpr int kPlanBins = 2048;          // 11-bit digits
+// Copies of the first digit's histogram: scores share few of its bins, so the
+// workgroups' adds queue up at those (pass 0 at 1.5M units: 21 us with one copy,
+// 11 with four).
+constexpr int kFirst = 4;
 
 struct PlanCtl {
     unsigned long long brem[9];       // remaining budget before resolving digit d
     unsigned long long prefix[9];     // key prefix with digits < d resolved
     unsigned long long hist[3][kPlanBins];  // rotating cost histograms of digit passes
+    unsigned long long first[kFirst][kPlanBins];  // pass 0's, workgroup b adding to copy b mod kFirst
     unsigned long long total0;        // candidate cost of the round (all-fit case)
     unsigned long long sel_cost;
     unsigned long long sel_count;
@@ -142,11 +157,15 @@ __device__ inline void resolve_digit(const unsigned long long* h, unsigned long 
     *total_out = total;
 }
 
-__global__ __launch_bounds__(1024) void k_plan_init(PlanCtl* ctl, unsigned long long budget)
+constexpr int kInitGrid = (3 + kFirst) * kPlanBins / kT;  // one bin a thread
+__global__ __launch_bounds__(kT) void k_plan_init(PlanCtl* ctl, unsigned long long budget)
 {
-    const int t = threadIdx.x;
-    for (int q = t; q < 3 * kPlanBins; q += 1024)
-        (&ctl->hist[0][0])[q] = 0ull;
+    const int t = (int)blockIdx.x * kT + (int)threadIdx.x;
+    static_assert(kPlanBins % kT == 0, "whole workgroups");
+    if (t < 3 * kPlanBins)
+        (&ctl->hist[0][0])[t] = 0ull;
+    else
+        (&ctl->first[0][0])[t - 3 * kPlanBins] = 0ull;
     if (t == 0) {
         ctl->brem[0] = budget;
         ctl->prefix[0] = 0ull;
@@ -199,7 +218,7 @@ struct Digit {
     int v;  // -1: the total fits
 };
 __device__ inline void block_resolve(const unsigned long long* __restrict__ h, unsigned long long brem,
-                                     unsigned long long* sw, Digit* out)
+                                     unsigned long long* sw, Digit* out, int copies = 1)
 {
     constexpr int per = kPlanBins / kHistT;
     const int t = threadIdx.x;
@@ -208,6 +227,14 @@ __device__ inline void block_resolve(const unsigned long long* __restrict__ h, u
     for (int q = 0; q < per; ++q) {
         c[q] = h[t * per + q];
         run += c[q];
+    }
+    for (int y = 1; y < copies; ++y) {
+#pragma unroll
+        for (int q = 0; q < per; ++q) {
+            const unsigned long long v = h[y * kPlanBins + t * per + q];
+            c[q] += v;
+            run += v;
+        }
     }
     unsigned long long total;
     unsigned long long at = block_excl_sum<kHistT>(run, sw, &total);
@@ -235,8 +262,8 @@ __device__ inline void block_resolve(const unsigned long long* __restrict__ h, u
 // those from psh up): resolve the pass before (every workgroup does it
 // redundantly from its histogram; workgroup 0 publishes it), then histogram
 // this digit of the units matching the resolved prefix.  One thread per unit,
-// four units' loads in flight.
-__global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int sh, int wd, int psh,
+// kHistU units' loads in flight.  copies: those of pass 0's histogram.
+__global__ __launch_bounds__(kHistT, 8) void k_plan_hist(PlanCtl* ctl, int d, int sh, int wd, int psh, int copies,
                                                       const float* __restrict__ sumsq, Coeffs w, uint32_t flags,
                                                       int K, const uint32_t* __restrict__ blen, uint32_t esize,
                                                       int64_t G)
@@ -256,7 +283,7 @@ __global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int s
     unsigned long long prefix = 0ull;
     if (d > 0) {
         const unsigned long long brem = ctl->brem[d - 1];
-        block_resolve(ctl->hist[(d - 1) % 3], brem, sw, &dg);
+        block_resolve(d == 1 ? ctl->first[0] : ctl->hist[(d - 1) % 3], brem, sw, &dg, d == 1 ? copies : 1);
         if (dg.v < 0) {  // digit 0: every candidate fits; later digits: cannot happen
             if (blockIdx.x == 0 && t == 0) {
                 if (d == 1) {
@@ -283,11 +310,11 @@ __global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int s
     }
     const int64_t n = G * K, step = (int64_t)gridDim.x * kHistT;
     const unsigned long long dm = (1ull << wd) - 1ull;
-    for (int64_t u0 = (int64_t)blockIdx.x * kHistT + t; u0 < n; u0 += 4 * step) {
-        float S[4];
-        uint32_t len[4], ex[4];
+    for (int64_t u0 = (int64_t)blockIdx.x * kHistT + t; u0 < n; u0 += kHistU * step) {
+        float S[kHistU];
+        uint32_t len[kHistU], ex[kHistU];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < kHistU; ++q) {
             const int64_t u = u0 + q * step;
             const uint32_t uid = (uint32_t)(u < n ? u : 0);
             const uint32_t g = uid / (uint32_t)K;
@@ -296,7 +323,7 @@ __global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int s
             len[q] = blen[g];
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < kHistU; ++q) {
             const int64_t u = u0 + q * step;
             const unsigned long long c = (unsigned long long)len[q] * esize;
             if (u >= n || plan_skips(S[q], c, flags))
@@ -307,7 +334,7 @@ __global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int s
         }
     }
     __syncthreads();
-    unsigned long long* out = ctl->hist[d % 3];
+    unsigned long long* out = d == 0 ? ctl->first[blockIdx.x % (unsigned)copies] : ctl->hist[d % 3];
 #pragma unroll
     for (int q = 0; q < kPlanBins / kHistT; ++q) {
         const unsigned long long v = lh[q * kHistT + t];
@@ -323,7 +350,7 @@ __global__ __launch_bounds__(kHistT) void k_plan_hist(PlanCtl* ctl, int d, int s
 // not dearer than what is left).  In the all-fit case select every candidate.
 // Per workgroup: the selected cost and count, and the mask's digest terms.
 constexpr int kMarkBits = 12, kMarkUids = 1 << kMarkBits;
-__global__ __launch_bounds__(kHistT) void k_plan_mark(PlanCtl* ctl, int d, int sh, const float* __restrict__ sumsq,
+__global__ __launch_bounds__(kHistT, 8) void k_plan_mark(PlanCtl* ctl, int d, int sh, const float* __restrict__ sumsq,
                                                       Coeffs w, uint32_t flags, int K,
                                                       const uint32_t* __restrict__ blen, uint32_t esize, int64_t G,
                                                       uint32_t* __restrict__ mask, uint32_t* __restrict__ next,
@@ -334,6 +361,7 @@ __global__ __launch_bounds__(kHistT) void k_plan_mark(PlanCtl* ctl, int d, int s
     __shared__ unsigned long long s_keyp, s_rem;
     __shared__ unsigned long long s_sum[3][kHistT / 64];
     __shared__ float s_w[kMaxK];
+    __shared__ uint32_t s_len[kMarkUids];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     if (t < K)
         s_w[t] = w.v[t];
@@ -350,38 +378,34 @@ __global__ __launch_bounds__(kHistT) void k_plan_mark(PlanCtl* ctl, int d, int s
         if (ok) {
             const unsigned long long pre = ctl->prefix[d] | ((unsigned long long)dg.v << sh);
             const unsigned long long left = ctl->brem[d] - dg.below;
-            constexpr int per = kMarkUids / kHistT;
-            unsigned long long c[per], run = 0ull;
+            unsigned long long run = 0ull;
             const int64_t n = G * K;
             const int m = 1 << sh, per_t = (m + kHistT - 1) / kHistT;
-#pragma unroll
-            for (int q = 0; q < per; ++q) {
-                c[q] = 0ull;
+#pragma unroll 4
+            for (int q = 0; q < per_t; ++q) {
                 const int j = t * per_t + q;
                 const int64_t u = (int64_t)(uint32_t)pre + j;
-                if (q < per_t && j < m && u < n) {
-                    const uint32_t g = (uint32_t)u / (uint32_t)K;
-                    const unsigned long long cc = (unsigned long long)blen[g] * esize;
+                uint32_t len = 0u;  // stays 0 where the uid is no candidate
+                if (j < m && u < n) {
+                    const uint32_t g = (uint32_t)u / (uint32_t)K, bl = blen[g];
+                    const unsigned long long cc = (unsigned long long)bl * esize;
                     const float S = plan_stat(sumsq, (uint32_t)u);
                     if (!plan_skips(S, cc, flags) &&
                         unit_key(S, s_w[(uint32_t)u - g * (uint32_t)K], (uint32_t)u, cc, flags) == pre + (unsigned)j)
-                        c[q] = cc;
+                        len = bl;
                 }
-                run += c[q];
+                if (j < m)
+                    s_len[j] = len;
+                run += (unsigned long long)len * esize;
             }
             unsigned long long total;
             unsigned long long at = block_excl_sum<kHistT>(run, sw, &total);
             if (at <= left && at + run > left) {  // exactly one thread
-                bool found = false;
-#pragma unroll
-                for (int q = 0; q < per; ++q) {
-                    if (!found && at + c[q] > left) {
-                        found = true;
-                        s_keyp = pre + (unsigned)(t * per_t + q);
-                        s_rem = left - at;
-                    }
-                    at += found ? 0ull : c[q];
-                }
+                int q = t * per_t;
+                for (; at + (unsigned long long)s_len[q] * esize <= left; ++q)  // ends: the run passes what is left
+                    at += (unsigned long long)s_len[q] * esize;
+                s_keyp = pre + (unsigned)q;
+                s_rem = left - at;
             }
         }
         __syncthreads();
@@ -649,9 +673,9 @@ constexpr int kOneMax = 8192;
 
 // NT threads of PER candidates each.  A round is a chain of barriers, cheaper
 // the fewer waves there are: lists up to 1024 take four waves (1.5M units'
-// later rounds 14 us, 21 with sixteen).
+// later rounds 15 us, 21 with sixteen), held to 64 registers (see the top).
 template <bool ALL, int NT, int PER>
-__global__ __launch_bounds__(NT) void k_plan_one(PlanCtl* ctl, const float* __restrict__ sumsq, Coeffs w,
+__global__ __launch_bounds__(NT, NT == 256 ? 8 : 1) void k_plan_one(PlanCtl* ctl, const float* __restrict__ sumsq, Coeffs w,
                                                     uint32_t flags, int K, const uint32_t* __restrict__ blen,
                                                     uint32_t esize, int64_t G, const uint32_t* __restrict__ list,
                                                     const unsigned int* __restrict__ list_n, unsigned int cap,
@@ -706,6 +730,9 @@ __global__ __launch_bounds__(NT) void k_plan_one(PlanCtl* ctl, const float* __re
                 alive |= 1u << q;
         }
     }
+    // candidates taken: noted, and written after the rounds, off their chain
+    // (ALL: at once, in LDS)
+    uint32_t taken = 0u;
     auto take = [&](int q) {
         const uint32_t uid = (uint32_t)key[q], g = uid / (uint32_t)K, bit = 1u << (uid - g * (uint32_t)K);
         cost += c[q];
@@ -716,6 +743,12 @@ __global__ __launch_bounds__(NT) void k_plan_one(PlanCtl* ctl, const float* __re
             const uint32_t old = atomicOr(&mask[g], bit);
             dig += mix64(((unsigned long long)g << 32) | (old | bit)) - mix64(((unsigned long long)g << 32) | old);
         }
+    };
+    auto note = [&](int q) {
+        if constexpr (ALL)
+            take(q);
+        else
+            taken |= 1u << q;
     };
     for (;;) {
         unsigned long long mine = 0ull, total;
@@ -730,7 +763,7 @@ __global__ __launch_bounds__(NT) void k_plan_one(PlanCtl* ctl, const float* __re
 #pragma unroll
             for (int q = 0; q < PER; ++q)
                 if ((alive >> q) & 1u)
-                    take(q);
+                    note(q);
             break;
         }
         unsigned long long prefix = 0ull, brem = rem;
@@ -786,11 +819,17 @@ __global__ __launch_bounds__(NT) void k_plan_one(PlanCtl* ctl, const float* __re
         for (int q = 0; q < PER; ++q) {
             if (((alive >> q) & 1u) && key[q] <= prefix) {
                 if (key[q] < prefix)
-                    take(q);
+                    note(q);
                 alive &= ~(1u << q);
             }
         }
         rem = brem;
+    }
+    if constexpr (!ALL) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if ((taken >> q) & 1u)
+                take(q);
     }
     __syncthreads();
     if (ALL) {
@@ -894,17 +933,19 @@ bool enqueue_select(const PlanIn& p, bool tensor_level, unsigned long long* stat
         n <= 4096 ? one(k_plan_one<true, 1024, 4>) : one(k_plan_one<true, 1024, 8>);
         return !tensor_level;
     }
-    hipLaunchKernelGGL(k_plan_init, dim3(1), dim3(1024), 0, s, ctl, budget);
+    hipLaunchKernelGGL(k_plan_init, dim3(kInitGrid), dim3(kT), 0, s, ctl, budget);
     // round 0 over every unit; its candidates for round 1 go to list1.  The
     // score's digits, then the uid's until at most kMarkBits are open
-    const unsigned hgrid = (unsigned)std::min<int64_t>((n + kHistT - 1) / kHistT, kHistGrid);
     int bits = 0;
     while (bits < 32 && (n - 1) >> bits)
         ++bits;
     int d = 0, psh = 0;
+    const int64_t per_wg = kHistT * kHistU;
+    const int64_t hgrid = std::min<int64_t>((n + per_wg - 1) / per_wg, n <= ((int64_t)1 << 23) ? 512 : 1024);
+    const int copies = hgrid > 64 ? kFirst : 1;  // few workgroups: reading the copies costs more
     auto pass = [&](int sh, int wd) {
-        hipLaunchKernelGGL(k_plan_hist, dim3(hgrid), dim3(kHistT), 0, s, ctl, d, sh, wd, psh, p.sumsq, p.w, p.flags,
-                           p.K, p.blen, p.es, p.G);
+        hipLaunchKernelGGL(k_plan_hist, dim3((unsigned)hgrid), dim3(kHistT), 0, s, ctl, d, sh, wd, psh, copies, p.sumsq,
+                           p.w, p.flags, p.K, p.blen, p.es, p.G);
         psh = sh;
         ++d;
     };

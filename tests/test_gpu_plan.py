@@ -72,3 +72,33 @@ def test_tensor_level_plan_routes(mp, T, K):  # noqa: F811
     full = 2 * K * sum(numel)
     _say(f"case {T} tensors, K {K}")
     _plans(mp, numel, 64, K, None, _budgets(full, rng), w=[1.0 + (i % 3) for i in range(K)])
+
+
+def test_plan_runs_beside_a_merge(mp):  # noqa: F811
+    """A plan on a second stream ends while a merge of 18 GB (3 ms) still runs on
+    the first: its workgroups fit into the slots that the merge's waves leave one
+    by one.  Its mask is the one of a plan alone."""
+    import torch
+    be, K, G = 4096, 4, 376_989
+    L = mp.Layout([be * G], be, mp.MP_BF16)
+    base, *exps = [torch.zeros(be * G, dtype=torch.bfloat16, device="cuda") for _ in range(1 + K)]
+    out = torch.empty_like(base)
+    S = torch.from_numpy(_scores("spread", G * K, np.random.default_rng(2))).cuda()
+    alone, beside = (torch.empty(G, dtype=torch.int32, device="cuda") for _ in range(2))
+    every = torch.full((G,), (1 << K) - 1, dtype=torch.int32, device="cuda")
+    tau = torch.ones(G * K, dtype=torch.int32, device="cuda")
+    budget = be * G * K
+    side = torch.cuda.Stream()
+    st = mp.mp_plan(L, K, S, [1.0] * K, budget, alone)
+    mp.mp_merge_ties_tau(L, base, exps, every, tau, 1.0, out)
+    torch.cuda.synchronize()
+    early = 0
+    for _ in range(5):
+        done = torch.cuda.Event()
+        mp.mp_merge_ties_tau(L, base, exps, every, tau, 1.0, out)
+        done.record()
+        assert mp.mp_plan(L, K, S, [1.0] * K, budget, beside, stream=side) == st  # returns when its stream has ended
+        early += not done.query()
+        torch.cuda.synchronize()
+        assert torch.equal(beside, alone)
+    assert early >= 3, f"the plan ended before the merge in {early} of 5 tries"
