@@ -598,9 +598,9 @@ def run_sweep(args):
         fid = fidelity(out, m_full, blen, st["n_selected"], K * G) if args.fidelity else None
         alg = 2 * P * es + st["cost_bytes"] + 4 * G if not host else st["cost_bytes"]
         pass_bytes = 0
-        if op == "ties_tensor":  # three digit passes, each reading every selected expert block and, once, the base under it
+        if op == "ties_tensor":  # one full pass over every selected expert block and, once, the base under it (the samples are not counted)
             m_np = mask.cpu().numpy()
-            pass_bytes = 3 * (st["cost_bytes"] + (0 if dl else int(blen_np[m_np != 0].sum()) * es))
+            pass_bytes = st["cost_bytes"] + (0 if dl else int(blen_np[m_np != 0].sum()) * es)
             alg += pass_bytes
         rows.append({"budget_frac": round(f, 4), "budget_bytes": B, "cost_bytes": st["cost_bytes"],
                      "h2d_bytes": io["h2d_bytes"], "n_selected": st["n_selected"], "plan_ms": round(plan_ms, 4),

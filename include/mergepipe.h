@@ -189,7 +189,7 @@ int mp_plan(const mp_layout* layout, int32_t K, const float* sumsq,
  * other allocation routine and keeps no per-layout cache.  Instead, the
  * control block, the layout's tensor sizes (twice), the first block of
  * each tensor, the tensors' selection words, the block lengths and the two
- * candidate lists live in one fixed device array (16.2 MiB), which each
+ * candidate lists live in one fixed device array (16.1 MiB), which each
  * device the library runs on holds until the process ends.  A layout may
  * take 16 MiB (16,777,216 bytes): the sum of these sizes, each rounded up to
  * 256 bytes: 18,688 for the control block (what it takes beyond those is
