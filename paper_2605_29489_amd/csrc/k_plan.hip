@@ -31,14 +31,13 @@
 // their list in each pass) 30 us and fourteen launches in all 145 us; now 80 us,
 // seven launches, passes of 7-12 us and the later rounds 15 us.
 //
-// Above kOneMax units a plan also has to run beside another stream's merge,
-// whose waves refill every slot as it frees: a workgroup is placed only once
-// its waves' slots and registers are free on one CU together.  So these
-// kernels have four waves (one per SIMD) of at most 64 registers (a merge
+// A plan also has to run beside another stream's merge, whose waves refill
+// every slot as it frees: a workgroup is placed only once its waves' slots and
+// registers are free on one CU together.  So the kernels have four waves (one per SIMD) of at most 64 registers (a merge
 // wave's).  Workgroups of 512 and 1024 threads waited for the whole merge: the
 // plans of the 1.5B-parameter step's second and third budgets took 1.52 and
-// 1.95 ms, now 0.30 and 0.23.  (Later rounds over lists of more than 1,024 units
-// keep 1024 threads: that last kernel waits for the merge.)
+// 1.95 ms, now 0.30 and 0.23.  (One-launch plans and later rounds over more than
+// 1,024 units keep 1024 threads: that kernel waits for the merge.)
 #include "device_common.h"
 #include "mp_internal.h"
 
@@ -672,8 +671,9 @@ __global__ __launch_bounds__(kT) void k_plan_rest(PlanCtl* ctl, const float* __r
 constexpr int kOneMax = 8192;
 
 // NT threads of PER candidates each.  A round is a chain of barriers, cheaper
-// the fewer waves there are: lists up to 1024 take four waves (1.5M units'
-// later rounds 15 us, 21 with sixteen), held to 64 registers (see the top).
+// the fewer waves there are: up to 1024 candidates take four waves (1.5M units'
+// later rounds 15 us, 21 with sixteen; a plan of 256 / 1,000 units 33 / 27 us, 41 /
+// 30 with sixteen), held to 64 registers (see the top).
 template <bool ALL, int NT, int PER>
 __global__ __launch_bounds__(NT, NT == 256 ? 8 : 1) void k_plan_one(PlanCtl* ctl, const float* __restrict__ sumsq, Coeffs w,
                                                     uint32_t flags, int K, const uint32_t* __restrict__ blen,
@@ -925,12 +925,15 @@ bool enqueue_select(const PlanIn& p, bool tensor_level, unsigned long long* stat
     const int64_t n = p.G * p.K;
     const unsigned long long budget = p.budget, full = p.full;
     if (n <= kOneMax) {
-        auto one = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen, p.es, p.G,
+        auto one = [&](auto kern, int nt) {
+            hipLaunchKernelGGL(kern, dim3(1), dim3(nt), 0, s, ctl, p.sumsq, p.w, p.flags, p.K, p.blen, p.es, p.G,
                                nullptr, nullptr, 0u, p.mask, 0, budget, full, (unsigned long long)n, tensor_level,
                                stats);
         };
-        n <= 4096 ? one(k_plan_one<true, 1024, 4>) : one(k_plan_one<true, 1024, 8>);
+        if (n <= 1024)
+            one(k_plan_one<true, 256, 4>, 256);
+        else
+            n <= 4096 ? one(k_plan_one<true, 1024, 4>, 1024) : one(k_plan_one<true, 1024, 8>, 1024);
         return !tensor_level;
     }
     hipLaunchKernelGGL(k_plan_init, dim3(kInitGrid), dim3(kT), 0, s, ctl, budget);

@@ -48,9 +48,9 @@ def _budgets(full, rng):
                   | {int(x) for x in rng.integers(0, full, 3)})
 
 
-# (full blocks, short tensors, K): 8191/8192/8193 units; 4096-uid ranges on both
+# (full blocks, short tensors, K): 1024/1025 and 8191/8192/8193 units; 4096-uid ranges on both
 # sides; 300 thousand units; 8,192 and more listed candidates
-@pytest.mark.parametrize("blocks,short,K", [(8191, 0, 1), (4092, 4, 2), (8190, 3, 1), (8000, 193, 1), (2000, 60, 5),
+@pytest.mark.parametrize("blocks,short,K", [(1020, 4, 1), (1021, 4, 1), (8191, 0, 1), (4092, 4, 2), (8190, 3, 1), (8000, 193, 1), (2000, 60, 5),
                                             (9000, 300, 32), (70_000, 500, 4), (3000, 2048, 4), (3000, 2049, 4)])
 def test_plan_routes(mp, blocks, short, K):  # noqa: F811
     be = 64
@@ -74,8 +74,9 @@ def test_tensor_level_plan_routes(mp, T, K):  # noqa: F811
     _plans(mp, numel, 64, K, None, _budgets(full, rng), w=[1.0 + (i % 3) for i in range(K)])
 
 
-def test_plan_runs_beside_a_merge(mp):  # noqa: F811
-    """A plan on a second stream ends while a merge of 18 GB (3 ms) still runs on
+@pytest.mark.parametrize("blocks", [376_989, 250])
+def test_plan_runs_beside_a_merge(mp, blocks):  # noqa: F811
+    """A plan (of 1.5M units, of 1,000) on a second stream ends while a merge of 18 GB (3 ms) still runs on
     the first: its workgroups fit into the slots that the merge's waves leave one
     by one.  Its mask is the one of a plan alone."""
     import torch
@@ -83,13 +84,14 @@ def test_plan_runs_beside_a_merge(mp):  # noqa: F811
     L = mp.Layout([be * G], be, mp.MP_BF16)
     base, *exps = [torch.zeros(be * G, dtype=torch.bfloat16, device="cuda") for _ in range(1 + K)]
     out = torch.empty_like(base)
-    S = torch.from_numpy(_scores("spread", G * K, np.random.default_rng(2))).cuda()
-    alone, beside = (torch.empty(G, dtype=torch.int32, device="cuda") for _ in range(2))
+    P = mp.Layout([be * blocks], be, mp.MP_BF16)  # what is planned
+    S = torch.from_numpy(_scores("spread", blocks * K, np.random.default_rng(2))).cuda()
+    alone, beside = (torch.empty(blocks, dtype=torch.int32, device="cuda") for _ in range(2))
     every = torch.full((G,), (1 << K) - 1, dtype=torch.int32, device="cuda")
     tau = torch.ones(G * K, dtype=torch.int32, device="cuda")
-    budget = be * G * K
+    budget = be * blocks * K
     side = torch.cuda.Stream()
-    st = mp.mp_plan(L, K, S, [1.0] * K, budget, alone)
+    st = mp.mp_plan(P, K, S, [1.0] * K, budget, alone)
     mp.mp_merge_ties_tau(L, base, exps, every, tau, 1.0, out)
     torch.cuda.synchronize()
     early = 0
@@ -97,7 +99,7 @@ def test_plan_runs_beside_a_merge(mp):  # noqa: F811
         done = torch.cuda.Event()
         mp.mp_merge_ties_tau(L, base, exps, every, tau, 1.0, out)
         done.record()
-        assert mp.mp_plan(L, K, S, [1.0] * K, budget, beside, stream=side) == st  # returns when its stream has ended
+        assert mp.mp_plan(P, K, S, [1.0] * K, budget, beside, stream=side) == st  # returns when its stream has ended
         early += not done.query()
         torch.cuda.synchronize()
         assert torch.equal(beside, alone)
