@@ -410,9 +410,9 @@ int mp_set_workspace_limit(uint64_t bytes);
 
 /* Test and measurement aid: how the last mp_ties_tensor_thresholds call that
  * launched kernels found its thresholds.  n >= 0: it read the selected blocks
- * once, after a sample of them, and left n (expert, tensor) pairs to the three
- * digit passes (their k-th largest lay outside the bracket taken from the
- * sample, or the bracket held more elements than the pair's list); -1: every
+ * once, after a sample of them, and left n (expert, tensor) pairs to the digit
+ * passes (their k-th largest lay outside the bracket taken from the sample, or
+ * the bracket held more elements than the pair's list); -1: every
  * pair took the digit passes (blocks over 4096 elements, or no room for the
  * lists).  The thresholds are the same either way. */
 int64_t mp_ties_tensor_left(void);

@@ -13,13 +13,16 @@
 //                 k-th largest, five standard deviations of the sample's rank
 //                 to either side;
 //   k_tt_scan     the full pass: counts the elements at or above hi, counts
-//                 the bracket's elements in 256 bins, and lists those of them
+//                 the bracket's elements in 256 bins (512 in fp32, if that
+//                 is a bin per pattern), and lists those of them
 //                 that do not equal their bin's floor (coarse bf16 deltas repeat
 //                 a few floors millions of times; those need no listing);
 //   k_tt_pick     one workgroup per pair: the bin that holds the k-th largest;
 //                 it is the bin's floor, or one of the listed elements.
 // Nothing depends on the sample being right: a pair whose k-th largest lies
-// outside its bracket, or whose list overflows, is left to the second route.
+// outside its bracket, or whose list overflows, is left to the second route
+// (in the second case from the bin on: each digit pass fixes up to 11 of the
+// bin's at most 23 open bits, and skips the pair once it is resolved).
 // The full pass is bound by memory (base and selected experts once, 1.46 ms of
 // the 1.5B-parameter case against 4.5 ms for three digit passes).
 //
@@ -41,7 +44,8 @@
 //                 fewer than k selected elements give 0 (the k-th largest
 //                 is a completed zero);
 //   k_tt_expand   tau[g*K + i] = the pair's threshold for every unit.
-// State per pair (uint4): {prefix, remaining rank, done, tau}; the entry after
+// State per pair (uint4): {prefix, remaining rank, done, tau, or the bits of
+// the prefix until done}; the entry after
 // the pairs' holds {error, pairs left by the first route, 0, 0}.  The bracket
 // route adds per pair {lo, hi - lo, bin shift, sampled elements above hi} and
 // {selected elements, elements above hi, listed, 0}.
@@ -69,8 +73,9 @@ constexpr int kDigBins = 2048;  // 11-bit digits (the last pass uses 9 bits)
 constexpr int kTH0 = 512, kCop0 = 4;
 constexpr int kTH = 256, kCop = 2;
 
-__host__ __device__ inline int tt_shift(int pass) { return pass == 0 ? 20 : (pass == 1 ? 9 : 0); }
-__host__ __device__ inline int tt_width(int pass) { return pass == 2 ? 9 : 11; }
+// The lowest bit of the next digit, with `open` bits of the pattern left: from
+// 31, the digits 30..20, 19..9 and 8..0.
+__device__ inline int tt_shift(int open) { return open > 11 ? open - 11 : 0; }
 
 __global__ __launch_bounds__(kTT) void k_tt_zero(uint32_t* __restrict__ p, int64_t n)
 {
@@ -84,7 +89,7 @@ __global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, 
                                                   const uint64_t* __restrict__ boff,
                                                   const uint32_t* __restrict__ blen,
                                                   const uint32_t* __restrict__ mask,
-                                                  const uint4* __restrict__ state, int T, int pass,
+                                                  const uint4* __restrict__ state, int T,
                                                   uint32_t* __restrict__ hist, uint32_t n_pairs, uint32_t per_xcd)
 {
     constexpr int V = Fmt<DT>::V;
@@ -110,9 +115,8 @@ __global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, 
         reinterpret_cast<uint4*>(h)[q] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     const uint32_t cp = (uint32_t)(tid % kCopies);
-    const int sh = tt_shift(pass), wd = tt_width(pass);
-    const uint32_t dmask = (1u << wd) - 1u;
-    const int hsh = sh + wd;  // the bits above the digit must match the prefix
+    const int hsh = 31 - (int)st.w, sh = tt_shift(hsh);  // the bits above the digit must match the prefix
+    const uint32_t dmask = (1u << (hsh - sh)) - 1u;
     const uint32_t prefix = st.x;
     for (uint32_t g = ch.x; g < ch.y; ++g) {
         if (!((mask[g] >> i) & 1u))
@@ -143,7 +147,7 @@ __global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, 
                 for (int v = 0; v < V; ++v) {
                     const float d = DELTA ? fe[v] : fe[v] - fb[v];
                     const uint32_t mg = __float_as_uint(d) & 0x7fffffffu;
-                    if (pass == 0 || (mg >> hsh) == prefix)
+                    if ((mg >> hsh) == prefix)
                         atomicAdd(&h[((mg >> sh) & dmask) * kCopies + cp], 1u);
                 }
             }
@@ -169,7 +173,7 @@ __global__ __launch_bounds__(kTH) void k_tt_hist(const void* __restrict__ base, 
 
 __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, const uint32_t* __restrict__ hist,
                                                      const uint64_t* __restrict__ tnumel, int K, int T,
-                                                     double density, int pass, uint32_t* __restrict__ err,
+                                                     double density, uint32_t* __restrict__ err,
                                                      int force_no_cut)
 {
     const int lane = threadIdx.x & 63;
@@ -181,8 +185,8 @@ __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, c
     if (st.z != 0u)
         return;
     const uint32_t* h = hist + (size_t)q * kDigBins;
-    const int wd = tt_width(pass);
-    constexpr int per = kDigBins / 64;  // lane l holds bins [l*per, (l+1)*per) (the 9-bit pass leaves the top ones 0)
+    const int open = 31 - (int)st.w, wd = open - tt_shift(open);
+    constexpr int per = kDigBins / 64;  // lane l holds bins [l*per, (l+1)*per) (a narrower digit leaves the top ones 0)
     uint32_t c[per];
     uint32_t mine = 0u;
 #pragma unroll
@@ -200,7 +204,7 @@ __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, c
     }
     const uint32_t total = __shfl(incl, 0);
     uint32_t rank = st.y;
-    if (pass == 0) {
+    if (st.w == 0u) {  // the first digit
         const uint64_t n = tnumel[t];
         const double kk = ceil(density * (double)n);
         const uint64_t k = (kk >= (double)n) ? n : (uint64_t)kk;
@@ -241,7 +245,8 @@ __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, c
     if (lane == 0) {
         st.x = (st.x << wd) | (uint32_t)bin;
         st.y = rank - before;
-        if (pass == 2) {
+        st.w += (uint32_t)wd;
+        if (wd == open) {
             st.z = 1u;
             st.w = st.x;
         }
@@ -253,7 +258,13 @@ __global__ __launch_bounds__(kTT) void k_tt_resolve(uint4* __restrict__ state, c
 constexpr int kSampleShare = 32;          // the sample: a 32nd of every block
 constexpr uint32_t kSampleRuns = 8;       // runs per sampling workgroup
 constexpr uint32_t kSmallTensor = 8192u;  // a pair's list has room for so many elements at least
-constexpr int kScanBins = 256, kScanCop = 4;
+// Bins of the full pass: up to 256 of four copies, or for an fp32 bracket of up
+// to 512 patterns one bin each of two copies (nothing is off its bin's floor
+// then: a quantised expert's repeated magnitude needs no list).  Not in bf16,
+// whose repeated magnitudes end in zero bits and are on a floor already.  Two
+// experts of 128M fp32 deltas of one magnitude, in tensors of 64M: 0.45 ms, 33.9
+// with 256 bins and a list (0.91 by three digit passes alone).
+constexpr int kScanBins = 512, kScanWords = 1024;
 // Words of the workgroup's list (with the bins 18 KiB: eight workgroups a CU).
 // Up to so many selected elements a pair lists every one; beyond, listing all
 // overflows it into the pair's list, one atomic round trip after another (list
@@ -400,11 +411,12 @@ __device__ inline uint32_t tt_shift_for(uint32_t lo, uint32_t hi, uint32_t bins,
 // sampled elements, stays 0 and every element is listed) and clears its
 // histogram.  Pass 0 also ends the pairs that keep nothing
 // (k = 0: all ones) or whose k-th largest is a completed zero (fewer than k
-// elements selected: 0).
+// elements selected: 0).  Brackets of up to `single` patterns get a bin each.
 template <int LV>
 __global__ __launch_bounds__(kTT) void k_tt_bracket(uint4* __restrict__ state, uint4* __restrict__ br,
                                                     const uint4* __restrict__ cnt, uint32_t* __restrict__ hist,
-                                                    const uint64_t* __restrict__ tnumel, int K, int T, double density)
+                                                    const uint64_t* __restrict__ tnumel, int K, int T, double density,
+                                                    uint32_t single)
 {
     constexpr int per = kDigBins / 64;
     const int lane = threadIdx.x & 63;
@@ -474,15 +486,19 @@ __global__ __launch_bounds__(kTT) void k_tt_bracket(uint4* __restrict__ state, u
             lo = b.x + ((uint32_t)__shfl(blo, __ffsll((long long)ml) - 1) << b.z);
     }
     if (lane == 0) {
-        const uint32_t s = LV == 0 ? tt_shift_for(lo, hi, kDigBins, false) : tt_shift_for(lo, hi, kScanBins, true);
+        const uint32_t s = LV == 0           ? tt_shift_for(lo, hi, kDigBins, false)
+                           : hi - lo <= single ? 0u
+                                             : tt_shift_for(lo, hi, kScanWords / 4, true);
         br[q] = make_uint4(lo, hi - lo, s, sab);
         if (LV == 0)
             state[q].y = ns;
     }
     // clear for the next pass, once every lane's bins have been used
     if (LV == 1) {
-        static_assert(kScanBins == 64 * 4, "four bins a lane");
+        static_assert(kScanBins == 2 * 64 * 4, "eight bins a lane, or four");
         reinterpret_cast<uint4*>(h)[lane] = make_uint4(0u, 0u, 0u, 0u);
+        if (single != 0u)
+            reinterpret_cast<uint4*>(h)[64 + lane] = make_uint4(0u, 0u, 0u, 0u);
     } else if (sampled) {
 #pragma unroll
         for (int j = 0; j < per / 4; ++j)
@@ -494,8 +510,11 @@ __global__ __launch_bounds__(kTT) void k_tt_bracket(uint4* __restrict__ state, u
 // element two compares and a subtraction; the bracket's elements add to the
 // bins (four copies) and, off their bin's floor, to the workgroup's list,
 // which is appended to the pair's at the end (entries past the LDS list go
-// there directly; past the pair's room they are only counted, and the pair is
-// left to the radix route).
+// there directly; a thread that finds the pair's room used up lists nothing
+// more, for the pair is left to the radix route: going on, the elements queue up
+// at the pair's counter).  No workgroup asks beforehand whether the list is full:
+// reading the counter that the others add to made ordinary fp32 tensors of 64M
+// 17% slower (409 -> 476 us).
 template <int DT, bool DELTA>
 __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, ExpertPtrs ex, int K,
                                                  const uint4* __restrict__ chunks, const uint64_t* __restrict__ boff,
@@ -506,9 +525,9 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
                                                  uint32_t lwords, uint32_t cpb, uint32_t n_pairs, uint32_t per_xcd)
 {
     constexpr int V = Fmt<DT>::V;
-    __shared__ __align__(16) uint32_t h[kScanBins * kScanCop];
+    __shared__ __align__(16) uint32_t h[kScanWords];
     __shared__ uint32_t lst[kScanList];
-    __shared__ uint32_t s_n, s_at, s_above;
+    __shared__ uint32_t s_n, s_at, s_above, s_over;
     __shared__ unsigned long long s_sel[kTT / 64];  // the run's selected blocks
     const uint32_t pr = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (pr >= n_pairs)
@@ -528,17 +547,20 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
         return;
     const uint4 b = br[pq];
     const uint32_t lo = b.x, width = b.y, sh = b.z, b0 = lo >> sh, hi = lo + width;
-    const uint32_t low = (1u << sh) - 1u;
+    uint32_t low = (1u << sh) - 1u;  // 0 once the thread knows that the list is full
     uint32_t* const glist = tt_list(list, i, lwords, tlist, ch.z);
     const uint32_t cap = tlist[ch.z + 1u] - tlist[ch.z];
-    for (int q = tid; q < kScanBins * kScanCop; q += kTT)
+    for (int q = tid; q < kScanWords; q += kTT)
         h[q] = 0u;
     if (tid == 0) {
         s_n = 0u;
         s_above = 0u;
+        s_over = 0u;
     }
     __syncthreads();
-    const uint32_t cp = (uint32_t)(tid % kScanCop);
+    const uint32_t nb = ((hi - 1u) >> sh) - b0 + 1u;  // bins in use
+    const uint32_t cl = DT == 0 && nb > (uint32_t)kScanWords / 4u ? 1u : 2u;  // log2 of their copies
+    const uint32_t cp = (uint32_t)tid & ((1u << cl) - 1u);
     uint32_t above = 0u;
     // one chunk's elements
     auto take = [&](const uint4& e16, const uint4& b16) {
@@ -551,7 +573,7 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
             const uint32_t mg = __float_as_uint(DELTA ? fe[v] : fe[v] - fb[v]) & 0x7fffffffu;
             above += mg >= hi ? 1u : 0u;
             if (mg - lo < width) {
-                atomicAdd(&h[((mg >> sh) - b0) * kScanCop + cp], 1u);
+                atomicAdd(&h[(((mg >> sh) - b0) << cl) + cp], 1u);
                 if ((mg & low) != 0u) {
                     const uint32_t at = atomicAdd(&s_n, 1u);
                     if (at < kScanList) {
@@ -560,6 +582,9 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
                         const uint32_t to = atomicAdd(&cnt[pq].z, 1u);
                         if (to < cap)
                             glist[to] = mg;
+                        else
+                            s_over = 1u;
+                        low = s_over == 0u ? low : 0u;
                     }
                 }
             }
@@ -622,9 +647,15 @@ __global__ __launch_bounds__(kTT) void k_tt_scan(const void* __restrict__ base, 
             atomicAdd(&cnt[pq].y, s_above);
     }
     uint32_t* out = hist + pq * kDigBins;
-    for (int q = tid; q < kScanBins; q += kTT) {
-        const uint4 w = reinterpret_cast<const uint4*>(h)[q];
-        const uint32_t v = w.x + w.y + w.z + w.w;
+    for (uint32_t q = (uint32_t)tid; q < nb; q += kTT) {
+        uint32_t v;
+        if (cl == 2u) {
+            const uint4 w = reinterpret_cast<const uint4*>(h)[q];
+            v = w.x + w.y + w.z + w.w;
+        } else {
+            const uint2 w = reinterpret_cast<const uint2*>(h)[q];
+            v = w.x + w.y;
+        }
         if (v != 0u)
             atomicAdd(&out[q], v);
     }
@@ -664,14 +695,15 @@ __global__ __launch_bounds__(kPick) void k_tt_pick(uint4* __restrict__ state, co
     const uint4 b = br[q], ct = cnt[q];
     const uint32_t nl = ct.z;
     const uint32_t* __restrict__ L = tt_list(list, (int)(q / (size_t)T), lwords, tlist, (uint32_t)t);
-    static_assert(kScanBins <= kPick, "a thread per bin");
-    if (tid < kScanBins)
-        h[tid] = hist[q * kDigBins + (size_t)tid];
+    // only a bracket of a bin per pattern uses (and has cleared) more than 256
+    const int bins = b.z == 0u && b.y > (uint32_t)kScanWords / 4u ? kScanBins : kScanWords / 4;
+    for (int x = tid; x < bins; x += kPick)
+        h[x] = hist[q * kDigBins + (size_t)x];
     __syncthreads();
     if (tid < 64) {
         Cut c{0u, 0u, 0u, 0u, 0u, 0u};
-        if (k > ct.y && nl <= tlist[t + 1] - tlist[t])
-            c = wave_find_from_top(h, kScanBins - 1, k - ct.y, lane);
+        if (k > ct.y)
+            c = wave_find_from_top(h, bins - 1, k - ct.y, lane);
         if (tid == 0) {
             s_ok = c.found;
             s_bin = c.bin;
@@ -680,12 +712,21 @@ __global__ __launch_bounds__(kPick) void k_tt_pick(uint4* __restrict__ state, co
         }
     }
     __syncthreads();
-    if (s_ok == 0u) {  // outside the bracket, or the list overflowed
-        if (tid == 0)
+    if (s_ok == 0u) {  // outside the bracket
+        if (tid == 0) {
+            state[q] = make_uint4(0u, 0u, 0u, 0u);
             atomicAdd(left, 1u);
+        }
         return;
     }
     uint32_t sb = b.z, pref = (b.x >> b.z) + s_bin, rank = s_rank;
+    if (sb != 0u && nl > tlist[t + 1] - tlist[t]) {  // the list overflowed: the bin is known, its bits are open
+        if (tid == 0) {
+            state[q] = make_uint4(pref, rank, 0u, 31u - sb);
+            atomicAdd(left, 1u);
+        }
+        return;
+    }
     bool first = true;
     while (sb != 0u) {
         const uint32_t wd = min(sb, 11u), up = sb;
@@ -730,8 +771,10 @@ __global__ __launch_bounds__(kPick) void k_tt_pick(uint4* __restrict__ state, co
         }
         __syncthreads();
         if (s_ok == 0u) {  // cannot happen: the list holds the rank-th largest
-            if (tid == 0)
+            if (tid == 0) {
+                state[q] = make_uint4(0u, 0u, 0u, 0u);
                 atomicAdd(left, 1u);
+            }
             return;
         }
         pref = (pref << wd) | s_bin;
@@ -813,12 +856,14 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
             delta ? sample(k_tt_sample<0, true, 0>) : sample(k_tt_sample<0, false, 0>);
         else
             delta ? sample(k_tt_sample<1, true, 0>) : sample(k_tt_sample<1, false, 0>);
-        hipLaunchKernelGGL(k_tt_bracket<0>, pgrid, dim3(kTT), 0, s, state, br, cnt, hist, bt.d_tnumel, K, T, density);
+        hipLaunchKernelGGL(k_tt_bracket<0>, pgrid, dim3(kTT), 0, s, state, br, cnt, hist, bt.d_tnumel, K, T, density,
+                           0u);
         if (bt.dtype == 0)
             delta ? sample(k_tt_sample<0, true, 1>) : sample(k_tt_sample<0, false, 1>);
         else
             delta ? sample(k_tt_sample<1, true, 1>) : sample(k_tt_sample<1, false, 1>);
-        hipLaunchKernelGGL(k_tt_bracket<1>, pgrid, dim3(kTT), 0, s, state, br, cnt, hist, bt.d_tnumel, K, T, density);
+        hipLaunchKernelGGL(k_tt_bracket<1>, pgrid, dim3(kTT), 0, s, state, br, cnt, hist, bt.d_tnumel, K, T, density,
+                           bt.dtype == 0 ? (uint32_t)kScanBins : 0u);
         if (bt.dtype == 0)
             delta ? scan(k_tt_scan<0, true>) : scan(k_tt_scan<0, false>);
         else
@@ -834,7 +879,7 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
         hipLaunchKernelGGL(k_tt_zero, zgrid, dim3(kTT), 0, s, hist, nh);
         auto go = [&](auto kern, int nth) {
             hipLaunchKernelGGL(kern, hgrid, dim3(nth), 0, s, base, ex, K, bt.d_chunk, bt.d_off, bt.d_len, mask, state,
-                               T, pass, hist, n_pairs, per_xcd);
+                               T, hist, n_pairs, per_xcd);
         };
         if (pass == 0) {
             if (bt.dtype == 0)
@@ -847,7 +892,7 @@ hipError_t launch_ties_tensor(const BlockTable& bt, const void* base, const Expe
             else
                 delta ? go(k_tt_hist<1, true, kTH, kCop>, kTH) : go(k_tt_hist<1, false, kTH, kCop>, kTH);
         }
-        hipLaunchKernelGGL(k_tt_resolve, pgrid, dim3(kTT), 0, s, state, hist, bt.d_tnumel, K, T, density, pass, err,
+        hipLaunchKernelGGL(k_tt_resolve, pgrid, dim3(kTT), 0, s, state, hist, bt.d_tnumel, K, T, density, err,
                            force_no_cut ? 1 : 0);
     }
     hipLaunchKernelGGL(k_tt_expand, dim3((unsigned)((bt.G * K + kTT - 1) / kTT)), dim3(kTT), 0, s, state,

@@ -175,3 +175,41 @@ def test_large_lists_are_given_back(mp):  # noqa: F811
     held, fixed = mp.mp_workspace_bytes() - before, len(numel) * K * (2048 * 4 + 3 * 16)
     assert held < fixed + (1 << 30), f"{held >> 20} MiB more held after the call"
     mp.mp_release()
+
+
+def test_repeated_values_overflow_their_lists(mp):  # noqa: F811
+    """fp32 deltas of few values, more of them in the bracket than a list holds.
+    One value off its bin's floor: the sample leaves at most 512 patterns, a bin
+    each, and no pair is left; 127 levels: either way.  Two values with the cut at
+    the end of the larger's share: the bracket reaches over both, its lists
+    overflow, and the digit passes resolve the bin's open bits of every pair."""
+    be, numel = 4096, [300_000, 40_000]
+    P, rng = sum(numel), np.random.default_rng(11)
+    bits = lambda v: (np.float32(v).view(np.uint32) | np.uint32(1)).view(np.float32)  # noqa: E731
+    G = oracle.Blocks(numel, be).G
+    base = np.zeros(P, np.float32)
+    some = rng.integers(0, 4, G).astype(np.uint32)
+    levels = np.clip(np.round(rng.normal(0.0, 30.0, P)), -127, 127) * np.float32(3.3e-5)
+    exps = [(bits(1.2345e-3) * rng.choice([-1.0, 0.0, 1.0], P)).astype(np.float32), levels.astype(np.float32)]
+    for density in (0.05, 0.2, 0.5, 0.9):
+        _say(f"case density {density}")
+        _check(mp, "f32", be, numel, base, exps[:1], np.full(G, 1, np.uint32), density)
+        assert mp.mp_ties_tensor_left() == 0, mp.mp_ties_tensor_left()
+        _check(mp, "f32", be, numel, base, exps, np.full(G, 3, np.uint32), density)
+        _check(mp, "f32", be, numel, base, exps, some, density)
+        _check(mp, "f32", be, numel, base, exps, some, density, delta=True)
+    for one, two in ((bits(2.5e-3), bits(1.2345e-3)), (bits(3.1e-3), bits(3.0e-3))):
+        exps = []
+        for _ in range(2):
+            e = np.zeros(P, np.float32)
+            for lo, n in zip(np.cumsum([0] + numel[:-1]), numel):
+                # exactly a fifth of the larger, so that the cut is at its end
+                v = np.repeat(np.array([one, two, 0.0], np.float32), [n // 5, n // 2, n - n // 5 - n // 2])
+                e[lo:lo + n] = rng.permutation(v) * rng.choice([-1.0, 1.0], n).astype(np.float32)
+            exps.append(e)
+        for density in (0.2, 0.2 + 4 / 300_000):
+            _say(f"case two values, density {density}")
+            _check(mp, "f32", be, numel, base, exps, np.full(G, 3, np.uint32), density)
+            assert mp.mp_ties_tensor_left() == 4, mp.mp_ties_tensor_left()
+        _check(mp, "f32", be, numel, base, exps, some, 0.1)
+        _check(mp, "f32", be, numel, base, exps, some, 0.1, delta=True)
